@@ -1255,12 +1255,9 @@ int adv_store(ptk_ctx* c, double* X, void* rhs_hist, hipStream_t s) {
   const bool vf64 = st.vb == 8;
   const size_t v3 = (size_t)Np * 3 * st.vb;
   Timed t(c, s, PTK_T_PERMUTE);
-  const double* x = st.xcur;
-  if (st.xrow) {
-    PTK_HIP(c, gather3_f64(st.xcur, st.xrow, Np, st.xnext, s), "gather positions");
-    x = st.xnext;
-  }
-  PTK_HIP(c, scatter_f64(x, st.orig, Np, 3, X, s), "scatter positions");
+  PTK_HIP(c,
+          st.xrow ? move3_f64(st.xcur, st.xrow, st.orig, Np, X, s) : scatter_f64(st.xcur, st.orig, Np, 3, X, s),
+          "scatter positions");
   for (int j = 0; j < st.hl; ++j) {
     char* out = (char*)rhs_hist + j * v3;
     PTK_HIP(c,
