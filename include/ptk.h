@@ -203,7 +203,9 @@ int ptk_locate(ptk_ctx *ctx, const double *X, int64_t Np, int32_t *cell, double 
  * X: device [Np][3] binary64.  out: device [Np][3] of out_dtype (PTK_F64 or
  * PTK_F32), in the order of X.  Internally particles are binned by cell with a
  * stable sort (tile columns cut into x3 windows, see ptk_binning_info), as the
- * paper groups particles by x3 slice (Sec. 3.3.1). */
+ * paper groups particles by x3 slice (Sec. 3.3.1), and swept column by column;
+ * particles that are few for the grid are read from the field one by one, with
+ * the same results bit for bit. */
 int ptk_interpolate(ptk_ctx *ctx, const double *X, int64_t Np, void *out, int out_dtype,
                     void *stream);
 
@@ -263,8 +265,9 @@ int ptk_interpolate_noalloc(ptk_ctx *ctx, const double *X, int64_t Np, void *out
  *    steps.
  * Particles are re-binned after every position update to the stable order of
  * their new bins (only the particles whose bin changed are sorted, then merged
- * with the others) and kept in bin order internally; results are returned in
- * the order of X. */
+ * with the others) and kept in bin order internally (particles that are few for
+ * the grid need no bins and are stepped in place); results are returned in the
+ * order of X. */
 int ptk_advance_particles(ptk_ctx *ctx, double *X, int64_t Np, void *rhs_hist, int *hist_len,
                           int scheme, double dt, int nsteps, void *grad_out, void *stream);
 
@@ -404,7 +407,9 @@ int ptk_binning_info(const ptk_ctx *ctx, int64_t *np, int64_t *n_bins, int *tile
 /* Copy that binning to device buffers: perm[k] (uint32 [np]) = index in X of
  * the k-th particle in bin order (a stable sort of the keys), offsets (uint32
  * [n_bins+1]) with offsets[b] = number of particles with key < b and
- * offsets[n_bins] = np (the paper's offset array, Sec. 3.3.1). */
+ * offsets[n_bins] = np (the paper's offset array, Sec. 3.3.1).  After a call
+ * that evaluated its particles without sorting them, this sorts the keys that
+ * the call left. */
 int ptk_get_binning(ptk_ctx *ctx, uint32_t *perm, uint32_t *offsets, void *stream);
 
 /* Kernel timing, a tracing aid.  While enabled, the library brackets its main

@@ -303,6 +303,48 @@ InterpArgs base_args(const ptk_ctx* c, bool next_field = false) {
   return a;
 }
 
+// How a launch evaluates its particles.
+enum class Route {
+  kSweep,        // binned, by the tile-column sweep (interp.hip)
+  kDirect,       // in the order given, straight from the field (direct.hip)
+  kDirectSorted  // the same in bin order
+};
+
+// The way that takes the least time for Np particles on the context's field,
+// by estimates in microseconds fitted to single calls on grids of 32^3 to 1024^3
+// with 0.001 to 1 particles a cell (I = 4, 6, 8; every storage type).  Results
+// do not depend on the choice (the kernels agree bit for bit), only time does.
+//   direct: a launch, then each particle's I^2 stencil rows, which come from HBM
+//     or the memory-side cache (31 ns per 10^3 rows with FP32 nodes), or from L2
+//     where the field fits it.  In bin order neighbouring particles share
+//     rows: 0.4 to 0.62 of that from 0.007 particles a cell on, nothing gained
+//     below 0.002.
+//   binned routes: the sort, about 70 us of launches and 35 us per 10^6.
+//   sweep: every plane of the field staged (6 us per 10^6 FP32 nodes), then
+//     120 us per 10^6 particles once there are about 512 workgroups.
+// Measured, FP32, I = 8, values (direct / in bin order / sweep): 512^3 with
+// 134217 particles 318 / 361 / 974 us, 402653: 861 / 644 / 1074, 1342177: 2712 /
+// 1197 / 1180; 1024^3 with 3.2e6: 7348 / 4288 / 6995; 64^3 with 78643: 71 / 138 /
+// 119, 262144: 163 / 204 / 149.
+Route route_of(const ptk_ctx* c, int64_t Np, bool grad) {
+  const BinGeom g = bin_geom(c);
+  const bool f64 = c->storage == PTK_F64, f32 = c->storage == PTK_F32;
+  const double n = 1e-6 * (double)Np, nodes = 1e-6 * (double)c->geom.N * (double)c->geom.N * (double)c->geom.N;
+  const double row = f64 ? (grad ? 69.0 : 48.0) : f32 ? 31.0 : 22.0;
+  const double bytes = (double)c->geom.plane_pitch * (double)c->geom.P;
+  const double rows = n * row * c->I * c->I * (bytes <= 8e6 ? 0.4 : 1.0);
+  const double sort = 70.0 + 35.0 * n;
+  const double groups = (double)n_bins_of(g);  // of at least one window
+  const double direct = 30.0 + rows;
+  const bool wide = f32 && c->I == 8;
+  const double shared = n < 0.002 * nodes ? 1.0 : n < 0.007 * nodes ? (wide ? 0.65 : 0.8) : wide ? 0.4 : 0.62;
+  const double sorted = 30.0 + sort + rows * shared;
+  const double sweep = 30.0 + sort + nodes * (f64 ? 15.0 : grad ? 8.0 : 6.0) +
+                       n * (f64 ? 250.0 : grad ? 170.0 : 120.0) * (groups < 512.0 ? 512.0 / groups : 1.0);
+  if (direct <= sorted && direct <= sweep) return Route::kDirect;
+  return sorted <= sweep ? Route::kDirectSorted : Route::kSweep;
+}
+
 // Device scratch of one interpolate call: sort keys and values (double
 // buffered), radix histograms, scan partials, bin offsets.
 struct InterpScratch {
@@ -333,17 +375,19 @@ int interp_core(ptk_ctx* c, const InterpScratch& w, const double* X, int64_t Np,
       c->bin_np = 0;
       c->bin_nbins = n_bins;
       c->bin_perm = nullptr;
+      c->bin_from_keys = false;
       c->bin_valid = true;
     }
     return PTK_OK;
   }
   PTK_HIP(c, launch_fill_i32((int*)c->flag.ptr, 1, 0, s), "flag clear");
-  {
-    Timed t(c, s, PTK_T_KEYS);
-    PTK_HIP(c, launch_keys(X, Np, (int)N, invd_of(N), bg, w.keys_a, (int*)c->flag.ptr, s), "keys");
-  }
+  const Route route = route_of(c, Np, grad != nullptr);
   uint32_t* perm = nullptr;
-  {
+  if (route != Route::kDirect) {
+    {
+      Timed t(c, s, PTK_T_KEYS);
+      PTK_HIP(c, launch_keys(X, Np, (int)N, invd_of(N), bg, w.keys_a, (int*)c->flag.ptr, s), "keys");
+    }
     Timed t(c, s, PTK_T_SORT);
     uint32_t* sk = nullptr;
     PTK_HIP(c,
@@ -365,12 +409,19 @@ int interp_core(ptk_ctx* c, const InterpScratch& w, const double* X, int64_t Np,
   a.out_f64 = out_dtype == PTK_F64;
   {
     Timed t(c, s, grad ? PTK_T_INTERP_GRAD : PTK_T_INTERP);
-    PTK_HIP(c, launch_interp(c->storage, c->I, a, s), "interpolate");
+    if (route == Route::kSweep)
+      PTK_HIP(c, launch_interp(c->storage, c->I, a, s), "interpolate");
+    else
+      PTK_HIP(c,
+              launch_direct(c->storage, c->I, a, bg,
+                            record && route == Route::kDirect ? (uint32_t*)c->bin_keys.ptr : nullptr, s),
+              "interpolate");
   }
   if (record) {
     c->bin_perm = perm;
     c->bin_np = Np;
     c->bin_nbins = n_bins;
+    c->bin_from_keys = route == Route::kDirect;
     c->bin_valid = true;
   }
   return check_flag(c, s);
@@ -390,6 +441,10 @@ int interp_common(ptk_ctx* c, const double* X, int64_t Np, void* u_out, void* gr
   } else {
     PTK_TRY(ensure_binning(c, Np, n_bins));
     PTK_TRY(check_binning_caps(c, Np, n_bins));
+    if (route_of(c, Np, grad != nullptr) == Route::kDirect) {
+      PTK_TRY(ensure(c, c->bin_keys, (size_t)Np * 4));
+      PTK_TRY(need(c, c->bin_keys, (size_t)Np * 4, "bin keys"));
+    }
   }
   PTK_TRY(need(c, c->offsets, (size_t)(n_bins + 1) * 4, "bin offsets"));
   InterpScratch w{(uint32_t*)c->keys_a.ptr, (uint32_t*)c->keys_b.ptr, (uint32_t*)c->vals_a.ptr,
@@ -558,7 +613,7 @@ void ptk_destroy(ptk_ctx* c) {
   {
     DeviceGuard g(c->device);
     (void)hipDeviceSynchronize();
-    DevBuf* bufs[] = {&c->field, &c->field_next, &c->coef, &c->keys_a, &c->keys_b, &c->vals_a, &c->vals_b, &c->offsets,
+    DevBuf* bufs[] = {&c->field, &c->field_next, &c->coef, &c->bin_keys, &c->keys_a, &c->keys_b, &c->vals_a, &c->vals_b, &c->offsets,
                       &c->hist, &c->scan_tmp, &c->flag, &c->xs, &c->xn, &c->orig, &c->orig_b, &c->k1,
                       &c->k2, &c->abh[0], &c->abh[1], &c->abh[2], &c->abh[3], &c->abh_b[0], &c->abh_b[1],
                       &c->abh_b[2], &c->abh_b[3], &c->gint, &c->stage, &c->lparams,
@@ -851,6 +906,14 @@ int ptk_get_binning(ptk_ctx* c, uint32_t* perm, uint32_t* offsets, void* stream)
   if ((c->bin_np > 0 && !perm) || !offsets) return fail(c, PTK_EINVAL, "NULL pointer");
   DeviceGuard g(c->device);
   hipStream_t s = S(stream);
+  if (c->bin_from_keys) {
+    // (sorted from a copy, so that a further call finds the keys)
+    PTK_TRY(check_binning_caps(c, c->bin_np, c->bin_nbins));
+    PTK_HIP(c,
+            hipMemcpyAsync(c->keys_a.ptr, c->bin_keys.ptr, (size_t)c->bin_np * 4, hipMemcpyDeviceToDevice, s),
+            "copy keys");
+    PTK_TRY(bin_sorted(c, c->bin_np, c->bin_nbins, &c->bin_perm, s));
+  }
   if (c->bin_np > 0)
     PTK_HIP(c, hipMemcpyAsync(perm, c->bin_perm, (size_t)c->bin_np * 4, hipMemcpyDeviceToDevice, s), "copy perm");
   PTK_HIP(c,
@@ -910,11 +973,20 @@ int adv_load(ptk_ctx* c, const double* X, int64_t Np, const void* rhs_hist, int 
   uint32_t* keys = (uint32_t*)c->keys_a.ptr;
   int* flag = (int*)c->flag.ptr;
   PTK_HIP(c, launch_fill_i32(flag, 1, 0, s), "flag clear");
+  const bool binned = route_of(c, Np, false) != Route::kDirect;
   if (Np > 0) {
-    {
-      Timed t(c, s, PTK_T_KEYS);
-      PTK_HIP(c, launch_keys(X, Np, (int)N, invd_of(N), bg, keys, flag, s), "keys");
-    }
+    Timed t(c, s, PTK_T_KEYS);
+    PTK_HIP(c, launch_keys(X, Np, (int)N, invd_of(N), bg, keys, flag, s), "keys");  // (and the domain check)
+  }
+  if (Np > 0 && !binned) {
+    // the caller's order
+    Timed t(c, s, PTK_T_PERMUTE);
+    PTK_HIP(c, hipMemcpyAsync(c->xs.ptr, X, (size_t)Np * 24, hipMemcpyDeviceToDevice, s), "copy positions");
+    PTK_HIP(c, launch_iota((uint32_t*)c->orig.ptr, Np, s), "caller order");
+    for (int j = 0; j < hl; ++j)
+      PTK_HIP(c, hipMemcpyAsync(c->abh[j].ptr, (const char*)rhs_hist + j * v3, v3, hipMemcpyDeviceToDevice, s),
+              "copy history");
+  } else if (Np > 0) {
     uint32_t* perm = nullptr;
     {
       Timed t(c, s, PTK_T_SORT);
@@ -935,6 +1007,7 @@ int adv_load(ptk_ctx* c, const double* X, int64_t Np, const void* rhs_hist, int 
   }
   st.ori = false;
   st.inert = false;
+  st.binned = binned;
   st.Np = Np;
   st.N = N;
   st.vb = vb;
@@ -951,6 +1024,60 @@ int adv_load(ptk_ctx* c, const double* X, int64_t Np, const void* rhs_hist, int 
     st.hb[j] = j < K ? c->abh_b[j].ptr : nullptr;
   }
   st.valid = true;
+  return PTK_OK;
+}
+
+// the loaded positions (and history) in the caller's order
+int adv_store(ptk_ctx* c, double* X, void* rhs_hist, hipStream_t s) {
+  auto& st = c->adv;
+  const int64_t Np = st.Np;
+  if (Np == 0) return PTK_OK;
+  const bool vf64 = st.vb == 8;
+  const size_t v3 = (size_t)Np * 3 * st.vb;
+  Timed t(c, s, PTK_T_PERMUTE);
+  PTK_HIP(c,
+          st.xrow ? move3_f64(st.xcur, st.xrow, st.orig, Np, X, s) : scatter_f64(st.xcur, st.orig, Np, 3, X, s),
+          "scatter positions");
+  for (int j = 0; j < st.hl; ++j) {
+    char* out = (char*)rhs_hist + j * v3;
+    PTK_HIP(c,
+            vf64 ? scatter_f64((const double*)st.h[j], st.orig, Np, 3, (double*)out, s)
+                 : scatter_f32((const float*)st.h[j], st.orig, Np, 3, (float*)out, s),
+            "scatter history");
+  }
+  return PTK_OK;
+}
+
+// The arguments of a direct advance; Heun's second stage sees next's field.
+// X and the history are the caller's to set.
+DirectSteps direct_steps(int scheme, double dt, int hl, const InterpArgs& next) {
+  DirectSteps d;
+  std::memset(&d, 0, sizeof(d));
+  const int K = ab_order(scheme);
+  d.kind = scheme == PTK_HEUN ? kHeunCorrect : K ? kAB : kEulerOrPredict;
+  d.dt = dt;
+  d.field2 = next.field;
+  for (int q = 0; q < 3; ++q) d.scale2[q] = next.scale[q];
+  d.depth = K ? K : 1;
+  d.hl = K ? hl : 0;
+  for (int q = 1; q <= 4; ++q)
+    for (int j = 0; j < 4; ++j) d.b[q - 1][j] = kABW[q][j];
+  return d;
+}
+
+// The steps in launches of at most kStepsPerLaunch, so that no launch holds the
+// GPU for long; the last one evaluates the gradient.  d.hl is brought up to
+// date.
+constexpr int kStepsPerLaunch = 64;
+int run_direct_steps(ptk_ctx* c, InterpArgs a, DirectSteps& d, int nsteps, hipStream_t s) {
+  void* const grad = a.grad;
+  Timed t(c, s, grad ? PTK_T_INTERP_GRAD : PTK_T_INTERP);
+  for (int done = 0; done < nsteps; done += d.nsteps) {
+    d.nsteps = nsteps - done < kStepsPerLaunch ? nsteps - done : kStepsPerLaunch;
+    a.grad = done + d.nsteps == nsteps ? grad : nullptr;
+    PTK_HIP(c, launch_direct_steps(c->storage, c->I, a, d, s), "steps");
+    if (d.kind == kAB) d.hl = d.hl + d.nsteps < d.depth ? d.hl + d.nsteps : d.depth;
+  }
   return PTK_OK;
 }
 
@@ -1086,8 +1213,79 @@ int adv_steps(ptk_ctx* c, int scheme, double dt, int nsteps, void* grad_out, hip
     std::swap(c->skeys, c->skeys2);
     std::swap(c->aoff, c->offsets2);
   };
+  // everything that belongs to the particles but their positions into the
+  // order perm (each array's other buffer takes it)
+  auto carry = [&](const uint32_t* perm) -> int {
+    Timed t(c, s, PTK_T_PERMUTE);
+    PTK_HIP(c, gather_u32(st.orig, perm, Np, st.orig_b, s), "gather order");
+    std::swap(st.orig, st.orig_b);
+    for (int j = 0; j < hl; ++j) {
+      PTK_HIP(c, gather_v(st.h[j], perm, st.hb[j]), "gather history");
+      std::swap(st.h[j], st.hb[j]);
+    }
+    if (pst) {
+      PTK_HIP(c, gather3_f64(st.p, perm, Np, st.pn, s), "gather axes");
+      std::swap(st.p, st.pn);
+      for (int j = 0; j < hl; ++j) {
+        PTK_HIP(c, gather3_f64(st.ph[j], perm, Np, st.phb[j], s), "gather axis history");
+        std::swap(st.ph[j], st.phb[j]);
+      }
+    }
+    if (inert)
+      for (int j = 0; j < hl; ++j) {
+        PTK_HIP(c, gather3_f64(st.vh[j], perm, Np, st.vhb[j], s), "gather velocity history");
+        std::swap(st.vh[j], st.vhb[j]);
+      }
+    return PTK_OK;
+  };
 
   PTK_HIP(c, launch_fill_i32(flag, 1, 0, s), "flag clear");
+  const bool direct = route_of(c, Np, false) != Route::kSweep;
+  if (!direct && !st.binned) {
+    // the particles were stepped without bins (on another field): sort them
+    // (in the re-binning's buffers; a recorded interpolate binning stays)
+    if (st.xrow) {
+      PTK_HIP(c, gather3_f64(st.xcur, st.xrow, Np, st.xnext, s), "gather positions");
+      std::swap(st.xcur, st.xnext);
+      st.xrow = nullptr;
+    }
+    uint32_t *perm = nullptr, *sk = nullptr;
+    {
+      Timed t(c, s, PTK_T_SORT);
+      PTK_HIP(c, launch_keys(st.xcur, Np, (int)N, invd, bg, (uint32_t*)c->mk_a.ptr, flag, s), "keys");
+      PTK_HIP(c,
+              radix_sort_keys((uint32_t*)c->mk_a.ptr, (uint32_t*)c->mk_b.ptr, (uint32_t*)c->mv_a.ptr,
+                              (uint32_t*)c->mv_b.ptr, Np, nullptr, false, bits_for(n_bins), (uint32_t*)c->hist.ptr,
+                              (uint32_t*)c->scan_tmp.ptr, &sk, &perm, s),
+              "radix sort");
+      PTK_HIP(c, launch_offsets(sk, Np, n_bins, (uint32_t*)c->aoff.ptr, s), "bin offsets");
+      PTK_HIP(c, hipMemcpyAsync(c->skeys.ptr, sk, (size_t)Np * 4, hipMemcpyDeviceToDevice, s), "sorted keys");
+      PTK_HIP(c, hipMemcpyAsync(c->aperm.ptr, perm, (size_t)Np * 4, hipMemcpyDeviceToDevice, s), "copy order");
+    }
+    PTK_TRY(carry((const uint32_t*)c->aperm.ptr));
+    st.xrow = (uint32_t*)c->aperm.ptr;
+  }
+  st.binned = !direct;
+  if (direct && !pst) {
+    // tracers: the whole call in one launch, positions and history in place
+    InterpArgs a = base_args(c);
+    a.xrow = st.xrow;
+    a.np = Np;
+    a.grad = grad_out;
+    a.grad_orig = st.orig;
+    a.out_f64 = vf64;
+    const InterpArgs next = base_args(c, stage2_next);
+    DirectSteps d = direct_steps(scheme, dt, hl, next);
+    d.X = st.xcur;
+    for (int j = 0; j < K; ++j) d.hist[j] = st.h[j];
+    PTK_TRY(run_direct_steps(c, a, d, nsteps, s));
+    if (K) st.hl = hl = d.hl;
+    if (final_X) {
+      PTK_TRY(adv_store(c, final_X, final_hist, s));
+      st.valid = false;
+    }
+    return check_flag(c, s);
+  }
   for (int step = 0; step < nsteps; ++step) {
     const bool last = step == nsteps - 1;
     void* k1 = st.k1;
@@ -1107,7 +1305,9 @@ int adv_steps(ptk_ctx* c, int scheme, double dt, int nsteps, void* grad_out, hip
       a.out_f64 = vf64;
       {
         Timed t(c, s, a.grad ? PTK_T_INTERP_GRAD : PTK_T_INTERP);
-        PTK_HIP(c, launch_interp(c->storage, c->I, a, s), "interpolate");
+        PTK_HIP(c,
+                direct ? launch_direct(c->storage, c->I, a, bg, nullptr, s) : launch_interp(c->storage, c->I, a, s),
+                "interpolate");
       }
       if (ori) {
         Timed t(c, s, PTK_T_UPDATE);
@@ -1135,8 +1335,8 @@ int adv_steps(ptk_ctx* c, int scheme, double dt, int nsteps, void* grad_out, hip
       // back in the step's bin order
       PTK_TRY(update(kEulerOrPredict, inert ? vel(st.p, nullptr) : vel(k1, nullptr)));
       if (pst) PTK_TRY(orient(kEulerOrPredict, vel(st.r1, nullptr), st.ps, 0));
-      uint32_t* pp = (uint32_t*)c->aperm_p.ptr;
-      PTK_TRY(rebin(pp));
+      uint32_t* pp = direct ? nullptr : (uint32_t*)c->aperm_p.ptr;
+      if (!direct) PTK_TRY(rebin(pp));
       {
         // the kernel reads the predictor positions through pp, the order it
         // also writes u in: no gathered copy.  With stage2_next the second
@@ -1151,7 +1351,9 @@ int adv_steps(ptk_ctx* c, int scheme, double dt, int nsteps, void* grad_out, hip
         b.grad = ori ? c->gint2.ptr : nullptr;  // the axes' second stage needs the gradient there
         b.out_f64 = vf64;
         Timed t(c, s, ori ? PTK_T_INTERP_GRAD : PTK_T_INTERP);
-        PTK_HIP(c, launch_interp(c->storage, c->I, b, s), "interpolate predictor");
+        PTK_HIP(c,
+                direct ? launch_direct(c->storage, c->I, b, bg, nullptr, s) : launch_interp(c->storage, c->I, b, s),
+                "interpolate predictor");
       }
       PTK_TRY(update(kHeunCorrect, inert ? vel(st.p, st.ps) : vel(k1, k2)));
       if (pst) {
@@ -1216,56 +1418,25 @@ int adv_steps(ptk_ctx* c, int scheme, double dt, int nsteps, void* grad_out, hip
       st.valid = false;
       break;
     }
+    if (direct) {
+      // nothing moves: the new positions are in the same order in xnext
+      st.xrow = nullptr;
+      std::swap(st.xcur, st.xnext);
+      if (pst) std::swap(st.p, st.pn);
+      continue;
+    }
     // re-bin the new positions and carry the per-particle state along (the
     // positions stay where they are: the next step reads them through perm)
     uint32_t* perm = (uint32_t*)c->aperm.ptr;
     PTK_TRY(rebin(perm));
-    {
-      Timed t(c, s, PTK_T_PERMUTE);
-      PTK_HIP(c, gather_u32(st.orig, perm, Np, st.orig_b, s), "gather order");
-      for (int j = 0; j < hl; ++j) PTK_HIP(c, gather_v(st.h[j], perm, st.hb[j]), "gather history");
-      if (pst) {
-        // the new axes (velocities) into the new bin order (the old ones'
-        // buffer takes them)
-        PTK_HIP(c, gather3_f64(st.pn, perm, Np, st.p, s), "gather axes");
-        for (int j = 0; j < hl; ++j) PTK_HIP(c, gather3_f64(st.ph[j], perm, Np, st.phb[j], s), "gather axis history");
-        for (int j = 0; j < hl; ++j) std::swap(st.ph[j], st.phb[j]);
-      }
-      if (inert) {
-        for (int j = 0; j < hl; ++j)
-          PTK_HIP(c, gather3_f64(st.vh[j], perm, Np, st.vhb[j], s), "gather velocity history");
-        for (int j = 0; j < hl; ++j) std::swap(st.vh[j], st.vhb[j]);
-      }
-    }
+    if (pst) std::swap(st.p, st.pn);
+    PTK_TRY(carry(perm));
     st.xrow = perm;
     std::swap(st.xcur, st.xnext);
     swap_bins();
-    std::swap(st.orig, st.orig_b);
-    for (int j = 0; j < hl; ++j) std::swap(st.h[j], st.hb[j]);
   }
   st.hl = hl;
   return check_flag(c, s);
-}
-
-// the loaded positions (and history) in the caller's order
-int adv_store(ptk_ctx* c, double* X, void* rhs_hist, hipStream_t s) {
-  auto& st = c->adv;
-  const int64_t Np = st.Np;
-  if (Np == 0) return PTK_OK;
-  const bool vf64 = st.vb == 8;
-  const size_t v3 = (size_t)Np * 3 * st.vb;
-  Timed t(c, s, PTK_T_PERMUTE);
-  PTK_HIP(c,
-          st.xrow ? move3_f64(st.xcur, st.xrow, st.orig, Np, X, s) : scatter_f64(st.xcur, st.orig, Np, 3, X, s),
-          "scatter positions");
-  for (int j = 0; j < st.hl; ++j) {
-    char* out = (char*)rhs_hist + j * v3;
-    PTK_HIP(c,
-            vf64 ? scatter_f64((const double*)st.h[j], st.orig, Np, 3, (double*)out, s)
-                 : scatter_f32((const float*)st.h[j], st.orig, Np, 3, (float*)out, s),
-            "scatter history");
-  }
-  return PTK_OK;
 }
 
 }  // namespace
@@ -1292,6 +1463,21 @@ int ptk_advance_particles(ptk_ctx* c, double* X, int64_t Np, void* rhs_hist, int
   hipStream_t s = S(stream);
   // the one-shot form runs on the buffers of the loaded state
   c->adv.valid = false;
+  if (route_of(c, Np, false) == Route::kDirect) {
+    // on the caller's arrays, in their order
+    InterpArgs a = base_args(c);
+    a.np = Np;
+    a.grad = grad_out;
+    a.out_f64 = vel_bytes(c) == 8;
+    DirectSteps d = direct_steps(scheme, dt, K ? *hist_len : 0, a);
+    d.X = X;
+    for (int j = 0; j < K; ++j) d.hist[j] = (char*)rhs_hist + (size_t)j * Np * 3 * vel_bytes(c);
+    PTK_HIP(c, launch_fill_i32((int*)c->flag.ptr, 1, 0, s), "flag clear");
+    PTK_TRY(run_direct_steps(c, a, d, nsteps, s));
+    PTK_TRY(check_flag(c, s));
+    if (K) *hist_len = d.hl;
+    return PTK_OK;
+  }
   PTK_TRY(adv_load(c, X, Np, rhs_hist, K ? *hist_len : 0, K, s));
   const int r = adv_steps(c, scheme, dt, nsteps, grad_out, s, X, rhs_hist);
   if (K && r == PTK_OK) *hist_len = c->adv.hl;

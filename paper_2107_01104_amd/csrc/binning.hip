@@ -603,6 +603,17 @@ hipError_t launch_fill_i32(int* p, int64_t n, int value, hipStream_t s) {
   return hipGetLastError();
 }
 
+__global__ __launch_bounds__(256) void k_iota(uint32_t* __restrict__ p, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) p[i] = (uint32_t)i;
+}
+
+hipError_t launch_iota(uint32_t* p, int64_t n, hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  k_iota<<<blocks_for(n, 256), 256, 0, s>>>(p, n);
+  return hipGetLastError();
+}
+
 hipError_t launch_offsets(const uint32_t* skeys, int64_t n, int64_t n_bins, uint32_t* offsets,
                           hipStream_t s) {
   k_offsets<<<blocks_for(n + 1, 256), 256, 0, s>>>(skeys, n, n_bins, offsets);

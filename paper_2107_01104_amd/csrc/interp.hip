@@ -30,43 +30,9 @@
 // row_newbcast.  (Folding the broadcast into the FMAs as their DPP operand
 // issues fewer instructions but measures slower.)  Sums are FP64 for FP64
 // storage and FP32 otherwise.
-#include <type_traits>
-
-#include "device_common.h"
-#include "launch.h"
-#include "ptk_internal.h"
+#include "interp_device.h"
 
 namespace ptk {
-
-enum { ST_F64 = 0, ST_F32 = 1, ST_BF16 = 2, ST_F16 = 3 };
-
-// 16-bit storage: the nodes are widened to FP32 (exactly) when they are staged
-// into the LDS ring, so the sums read the same 16-byte nodes as FP32 storage
-// and spend no instruction on conversions; HBM moves the 6-byte nodes.
-template <int ST>
-struct StoreT {
-  using acc = float;
-  static constexpr int T = kTileF32;   // tile edge in cells
-  static constexpr int NB = 16;        // LDS bytes per node
-  static constexpr int GB = 6;         // global (stored) bytes per node
-  static constexpr int THREADS = 512;
-};
-template <>
-struct StoreT<ST_F32> {
-  using acc = float;
-  static constexpr int T = kTileF32;
-  static constexpr int NB = 16;
-  static constexpr int GB = 12;
-  static constexpr int THREADS = 512;
-};
-template <>
-struct StoreT<ST_F64> {
-  using acc = double;
-  static constexpr int T = kTileF64;
-  static constexpr int NB = 32;
-  static constexpr int GB = 24;
-  static constexpr int THREADS = 512;
-};
 
 template <int ST, int I>
 struct Geom {
@@ -91,81 +57,6 @@ struct Geom {
   static constexpr int THREADS = StoreT<ST>::THREADS;
   static constexpr int PRE = (kWindow * UNITS_PER_PLANE + THREADS - 1) / THREADS;  // chunks per thread
 };
-
-// ---- DPP helpers (rows of 16 lanes = one particle group).  Every control
-// used here reads a lane of the same row, so no lane keeps an old value and
-// the moves need no initialised destination.
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
-// 64-bit moves: one v_mov_b64_dpp for row_newbcast (the only control DPP
-// has for 64-bit operands; the compiler splits the others into two 32-bit
-// moves).  A 64-bit broadcast issues as fast as a 32-bit one.
-// (the builtin's result is given a 64-bit type explicitly: inside a
-// template the front end types the generic builtin's call as int)
-template <int CTRL>
-__device__ __forceinline__ long dpp64(long v) {
-  const long r = __builtin_amdgcn_update_dpp(0L, v, CTRL, 0xF, 0xF, true);
-  return r;
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp(double v) {
-  return __builtin_bit_cast(double, dpp64<CTRL>(__builtin_bit_cast(long, v)));
-}
-// value of lane L of this row
-template <int L, typename V>
-__device__ __forceinline__ V bcast(V v) {
-  return dpp<0x150 + L>(v);
-}
-// lanes 0-7 of the row get lane L0's value, lanes 8-15 lane L1's: the second
-// move writes only DPP banks 2 and 3 (lanes 8-15) over the first
-template <int L0, int L1>
-__device__ __forceinline__ float bcast2(float v) {
-  const int a = __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x150 + L0, 0xF, 0xF, true);
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(a, __builtin_bit_cast(int, v), 0x150 + L1, 0xF, 0xC, false));
-}
-template <int L0, int L1>
-__device__ __forceinline__ long bcast2_64(long b) {
-  const long a = __builtin_amdgcn_update_dpp(0L, b, 0x150 + L0, 0xF, 0xF, true);
-  const long r = __builtin_amdgcn_update_dpp(a, b, 0x150 + L1, 0xF, 0xC, false);
-  return r;
-}
-template <int L0, int L1>
-__device__ __forceinline__ double bcast2(double v) {
-  return __builtin_bit_cast(double, bcast2_64<L0, L1>(__builtin_bit_cast(long, v)));
-}
-
-// sum over the 16 lanes of the row (every lane gets the total)
-template <typename V>
-__device__ __forceinline__ V rowsum(V v) {
-  v += dpp<0xB1>(v);   // quad_perm [1,0,3,2]
-  v += dpp<0x4E>(v);   // quad_perm [2,3,0,1]
-  v += dpp<0x141>(v);  // row_half_mirror
-  v += dpp<0x140>(v);  // row_mirror
-  return v;
-}
-
-// Reduce-scatter of a particle's three value partials over the 16 lanes of a
-// row (lane l16 = j + 8h): after it, lane (h, j) holds the row's total of
-// value 2h + (j >> 2) (value 3 is the zero padding), summed over all 16 lanes.
-// Five DPP additions instead of three full row sums (twelve).
-template <typename V>
-__device__ __forceinline__ V rowsum_scatter3(const V* e, int j, int h) {
-  const V z = (V)0;
-  // lanes l and l^8 (row_ror:8): the h = 0 half keeps values 0, 1, the h = 1
-  // half keeps 2 and the padding
-  const V k0 = h ? e[2] : e[0], k1 = h ? z : e[1];
-  const V s0 = h ? e[0] : e[2], s1 = h ? e[1] : z;
-  const V f0 = k0 + dpp<0x128>(s0);
-  const V f1 = k1 + dpp<0x128>(s1);
-  // lanes j and 7 - j of a half (row_half_mirror): j < 4 keeps f0, j >= 4 f1
-  const bool hi = (j & 4) != 0;
-  V g = (hi ? f1 : f0) + dpp<0x141>(hi ? f0 : f1);
-  g += dpp<0xB1>(g);  // quad_perm [1,0,3,2]
-  g += dpp<0x4E>(g);  // quad_perm [2,3,0,1]
-  return g;
-}
 
 // ---- node access
 // copy node q of a 48-byte chunk (12 words) into LDS at byte offset `off`.
@@ -246,15 +137,6 @@ __device__ __forceinline__ void settle(const uint4& v) {
   settle(v.w);
 }
 
-// f(integral_constant<int, K>) for K = B .. E-1
-template <int B, int E, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    static_for<B + 1, E>(f);
-  }
-}
-
 // Row of I coefficients of the lane's node from the workgroup's LDS copy of
 // the table, read when a round needs it instead of being held in registers
 // for the whole launch (the registers go to LDS reads in flight).  The row's
@@ -283,14 +165,6 @@ __device__ __forceinline__ void coef_row(const V* tab, int off, V* c) {
       c[p + 1] = f.y;
     }
   }
-}
-
-template <int NC, typename V>
-__device__ __forceinline__ V horner(const V* c, V t) {
-  V acc = c[NC - 1];
-#pragma unroll
-  for (int p = NC - 2; p >= 0; --p) acc = fma(acc, t, c[p]);
-  return acc;
 }
 
 // load unit u (one chunk of G nodes of a halo row of plane zp) from HBM.  The
@@ -370,39 +244,13 @@ __device__ __forceinline__ void particle_sums(const unsigned char* smem, const f
   // planes of this lane: k = 2m + h, m = 0..I/2-1; the two halves read planes
   // one ring slot apart (or R - 1 apart across the wrap; R is even), an odd
   // number of plane pitches
-  // weights: lanes 0-7 evaluate beta_j(t2), lanes 8-15 beta_j(t3); all lanes beta_j(t1)
-  const V tsel = h ? t3 : t2;
   // the gradient kernels read their coefficient rows from LDS here (their
   // registers are needed for the sums); the value kernels pass register rows
   V cvl[GRAD ? I : 1];
   if constexpr (GRAD) coef_row<I>(ctab, jj * I, cvl);
   const V* cv = GRAD ? cvl : cvreg;
-  const V wsel = horner<I>(cv, tsel);
-  V w1 = horner<I>(cv, t1);
-  if (j >= I) w1 = (V)0;
-  V w2[I], w3[HALF];
-  V d1 = (V)0, dw2[I], dw3[HALF];
-  {
-#define PTK_B2(k) if constexpr ((k) < I) w2[k] = bcast<k>(wsel);
-    PTK_B2(0) PTK_B2(1) PTK_B2(2) PTK_B2(3) PTK_B2(4) PTK_B2(5) PTK_B2(6) PTK_B2(7)
-#undef PTK_B2
-#define PTK_B3(m) if constexpr ((m) < HALF) w3[m] = bcast2<8 + 2 * (m), 9 + 2 * (m)>(wsel);
-    PTK_B3(0) PTK_B3(1) PTK_B3(2) PTK_B3(3)
-#undef PTK_B3
-    if constexpr (GRAD) {
-      V cd[I];
-      coef_row<I>(ctab, I * I + jj * I, cd);
-      const V dsel = horner<I - 1>(cd, tsel);
-      d1 = horner<I - 1>(cd, t1);
-      if (j >= I) d1 = (V)0;
-#define PTK_D2(k) if constexpr ((k) < I) dw2[k] = bcast<k>(dsel);
-      PTK_D2(0) PTK_D2(1) PTK_D2(2) PTK_D2(3) PTK_D2(4) PTK_D2(5) PTK_D2(6) PTK_D2(7)
-#undef PTK_D2
-#define PTK_D3(m) if constexpr ((m) < HALF) dw3[m] = bcast2<8 + 2 * (m), 9 + 2 * (m)>(dsel);
-      PTK_D3(0) PTK_D3(1) PTK_D3(2) PTK_D3(3)
-#undef PTK_D3
-    }
-  }
+  Weights<I, GRAD, V> wt;
+  lane_weights(cv, [&](V* cd) { coef_row<I>(ctab, I * I + jj * I, cd); }, j, h, t1, t2, t3, wt);
   // contraction: x2 over all rows per plane, x3 over this lane's planes
   const int noff = l2 * RP + (l1 + jj) * NB;
   const int s0 = (z3 + h) % R;
@@ -449,75 +297,28 @@ __device__ __forceinline__ void particle_sums(const unsigned char* smem, const f
       for (int k = 0; k < G; ++k) {
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-          s[q] = fma(w2[g + k], v[k][q], s[q]);
-          if constexpr (GRAD) sd[q] = fma(dw2[g + k], v[k][q], sd[q]);
+          s[q] = fma(wt.w2[g + k], v[k][q], s[q]);
+          if constexpr (GRAD) sd[q] = fma(wt.dw2[g + k], v[k][q], sd[q]);
         }
         asm("" : "+v"(sink) : "v"(keep[k]));
       }
     }
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-      acc[q] = fma(w3[m], s[q], acc[q]);
+      acc[q] = fma(wt.w3[m], s[q], acc[q]);
       if constexpr (GRAD) {
-        ad3[q] = fma(dw3[m], s[q], ad3[q]);
-        ad2[q] = fma(w3[m], sd[q], ad2[q]);
+        ad3[q] = fma(wt.dw3[m], s[q], ad3[q]);
+        ad2[q] = fma(wt.w3[m], sd[q], ad2[q]);
       }
     }
   }
   asm volatile("" ::"v"(sink));
-  // x1 weight, then the sum over the group's 16 lanes.  Values: r[q] = u_q,
-  // r[3 + 3q + b] = d u_q / d x_b (before the 1/delta factor).
-  V e[GRAD ? 12 : 3];
-#pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    e[q] = w1 * acc[q];
-    if constexpr (GRAD) {
-      e[3 + 3 * q + 0] = d1 * acc[q];
-      e[3 + 3 * q + 1] = w1 * ad2[q];
-      e[3 + 3 * q + 2] = w1 * ad3[q];
-    }
-  }
-  if constexpr (!GRAD) {
-    // lane (h, j) gets the total of value 2h + (j >> 2)
-    r[0] = rowsum_scatter3(e, j, h);
-  } else {
-    // reduce-scatter: lanes l and l^8 split the 12 values 6/6, then lanes j and
-    // 7-j of each half split their 6 values 3/3, then each quad sums its 3.
-    // Lane l16 ends with the totals of values 6*(l16/8) + 3*((l16/4)&1) + k,
-    // k = 0..2, in r[k].
-    const int b2 = (j >> 2) & 1;
-    V f[6];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      const V keep = h ? e[6 + k] : e[k];
-      const V send = h ? e[k] : e[6 + k];
-      f[k] = keep + dpp<0x128>(send);  // row_ror:8, the lane 8 away
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const V keep = b2 ? f[3 + k] : f[k];
-      const V send = b2 ? f[k] : f[3 + k];
-      V g = keep + dpp<0x141>(send);   // row_half_mirror, lane 7-j
-      g += dpp<0xB1>(g);
-      g += dpp<0x4E>(g);
-      r[k] = g;
-    }
-    // lanes 0-3 hold the values: add back the particle plane's reference
-    if constexpr (SHIFT) {
-      if (h == 0 && b2 == 0) {
-        r[0] += uc.x;
-        r[1] += uc.y;
-        r[2] += uc.z;
-      }
-    }
-  }
+  lane_sums<GRAD, SHIFT>(wt.w1, wt.d1, acc, ad2, ad3, uc, j, h, r);
 }
 
-// SPARSE: for launches with few particles per window -- visit only the
-// non-empty windows of each segment and fill the ring afresh for each,
-// instead of sweeping every plane.  Two workgroups per CU for FP32 and 16-bit
-// storage; FP64 nodes fill the LDS of one.
-template <int ST, int I, bool GRAD, bool SPARSE>
+// Two workgroups per CU for FP32 and 16-bit storage; FP64 nodes fill the LDS
+// of one.
+template <int ST, int I, bool GRAD>
 // the second bound is waves per SIMD: two 512-thread workgroups per CU are 4
 // (at most 128 VGPRs), one is 2
 __global__ __launch_bounds__(StoreT<ST>::THREADS, ST == ST_F64 ? 2 : 4) void k_interp(InterpArgs a) {
@@ -981,33 +782,7 @@ __global__ __launch_bounds__(StoreT<ST>::THREADS, ST == ST_F64 ? 2 : 4) void k_i
     }
   };
 
-  {
-    if (woff[0] == woff[w_end - w_begin]) return;  // no particle in this segment
-    if constexpr (SPARSE) {
-      for (int64_t w = w_begin; w < w_end; ++w) {
-        const uint32_t start = woff[w - w_begin], end = woff[w + 1 - w_begin];
-        if (start == end) continue;
-        fill(w);
-        for (uint32_t c0 = start; c0 < end; c0 += CH) {
-          const int m = (int)min((int64_t)CH, (int64_t)end - (int64_t)c0);
-          double xm;
-          uint32_t qm;
-          issue_pos(c0, m, xm, qm);
-          write_rec(w, m, xm, qm);
-          __syncthreads();  // ring and records complete
-          if constexpr (PAIR) {
-            const int kr = rank_kappa(m);
-            __syncthreads();
-            place(m, kr);
-            __syncthreads();
-          }
-          compute_chunk(m);
-          __syncthreads();  // every read done before the next fill
-        }
-      }
-      return;
-    }
-  }
+  if (woff[0] == woff[w_end - w_begin]) return;  // no particle in this segment
   fill(w_begin);
   __syncthreads();
 
@@ -1057,19 +832,10 @@ static hipError_t launch_one(const InterpArgs& a, hipStream_t s) {
   const int64_t grid = (nblk + 7) / 8 * 8;
   if (grid == 0) return hipSuccess;
   constexpr int NT = StoreT<ST>::THREADS;
-  // sparse when one fresh ring per particle loads fewer planes than the sweep
-  const bool sparse = a.np * (kWindow + I - 1) < a.n_tiles * a.nw * kWindow;
-  if (a.grad) {
-    if (sparse)
-      k_interp<ST, I, true, true><<<(unsigned)grid, NT, 0, s>>>(a);
-    else
-      k_interp<ST, I, true, false><<<(unsigned)grid, NT, 0, s>>>(a);
-  } else {
-    if (sparse)
-      k_interp<ST, I, false, true><<<(unsigned)grid, NT, 0, s>>>(a);
-    else
-      k_interp<ST, I, false, false><<<(unsigned)grid, NT, 0, s>>>(a);
-  }
+  if (a.grad)
+    k_interp<ST, I, true><<<(unsigned)grid, NT, 0, s>>>(a);
+  else
+    k_interp<ST, I, false><<<(unsigned)grid, NT, 0, s>>>(a);
   return hipGetLastError();
 }
 

@@ -46,6 +46,7 @@ hipError_t rebin_incremental(const uint32_t* okeys, const uint32_t* ooff, const 
                              int64_t n_bins, int key_bits, const RebinScratch& w, uint32_t* perm, uint32_t* skeys,
                              uint32_t* noff, hipStream_t s);
 hipError_t launch_fill_i32(int* p, int64_t n, int value, hipStream_t s);
+hipError_t launch_iota(uint32_t* p, int64_t n, hipStream_t s);  // p[i] = i
 hipError_t launch_offsets(const uint32_t* skeys, int64_t n, int64_t n_bins, uint32_t* offsets,
                           hipStream_t s);
 hipError_t gather3_f64(const double* in, const uint32_t* perm, int64_t n, double* out, hipStream_t s);
@@ -107,6 +108,25 @@ struct InterpArgs {
   int* flag;                // device status word (kFlag* bits)
 };
 hipError_t launch_interp(int storage, int I, const InterpArgs& a, hipStream_t s);
+
+// direct.hip: the same sums read straight from the field, particle by particle
+// (X, xrow, np, orig, grad_orig, out, grad, out_f64, coef, scale and flag of
+// the arguments as above; no bins).  keys (optional): the particles' bin keys.
+hipError_t launch_direct(int storage, int I, const InterpArgs& a, const BinGeom& g, uint32_t* keys, hipStream_t s);
+// nsteps steps of the tracers in one launch: positions (row xrow[i], or i) and
+// history in place; a.grad (optional): the last step's gradient
+struct DirectSteps {
+  double* X;
+  int kind;               // kEulerOrPredict, kHeunCorrect (a Heun step) or kAB
+  int nsteps;
+  double dt;
+  const void* field2;     // Heun's second stage
+  float scale2[3];
+  int depth, hl;          // kAB: order, valid history entries
+  void* hist[4];          // [n][3] each, most recent first, in the storage's velocity type
+  double b[4][4];         // weights by order - 1
+};
+hipError_t launch_direct_steps(int storage, int I, const InterpArgs& a, const DirectSteps& st, hipStream_t s);
 
 // step.hip
 enum UpdateKind { kEulerOrPredict = 0, kHeunCorrect = 1, kAB = 2 };

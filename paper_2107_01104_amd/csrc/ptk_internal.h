@@ -100,6 +100,10 @@ struct ptk_ctx {
   int64_t bin_np = 0, bin_nbins = 0;
   uint32_t* bin_perm = nullptr;
   bool bin_valid = false;
+  // the last call evaluated its particles without binning them: their keys
+  // are in bin_keys, and ptk_get_binning sorts them when it is asked
+  bool bin_from_keys = false;
+  ptk::DevBuf bin_keys;
   // scratch
   ptk::DevBuf keys_a, keys_b, vals_a, vals_b, offsets, hist, scan_tmp, flag;
   ptk::DevBuf xs, xn, orig, orig_b, k1, k2, gint, stage;
@@ -114,6 +118,9 @@ struct ptk_ctx {
   // which buffers hold what, in the current bin order
   struct {
     bool valid = false;
+    // the particles are in bin order, with skeys and aoff their sorted keys
+    // and offsets (not while they are stepped without bins)
+    bool binned = false;
     int64_t Np = 0, N = 0;
     int vb = 0;   // bytes per velocity component of the history
     int K = 0;    // history depth (Adams-Bashforth order) it was loaded for
