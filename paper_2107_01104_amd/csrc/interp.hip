@@ -144,6 +144,13 @@ __device__ __forceinline__ void settle(const uint4& v) {
 // cannot hoist the reads out of the particle loop; the pointer itself stays
 // visibly an LDS pointer (laundering it would turn the reads into flat loads,
 // whose waits also wait for every global load in flight).
+// Rows are a multiple of 16 bytes apart: a 16-byte LDS read at an 8-byte offset
+// costs as much as some eight aligned ones, and with the 24-byte rows of I = 6
+// in FP32 these reads took half of the gradient kernels' LDS time (LDS active
+// 8 cycles an instruction, against 4 elsewhere).
+template <int I, typename V>
+constexpr int kCoefPitch = sizeof(V) == 4 ? (I + 3) / 4 * 4 : I;
+
 template <int I, typename V>
 __device__ __forceinline__ void coef_row(const V* tab, int off, V* c) {
   asm volatile("" : "+v"(off));
@@ -247,10 +254,10 @@ __device__ __forceinline__ void particle_sums(const unsigned char* smem, const f
   // the gradient kernels read their coefficient rows from LDS here (their
   // registers are needed for the sums); the value kernels pass register rows
   V cvl[GRAD ? I : 1];
-  if constexpr (GRAD) coef_row<I>(ctab, jj * I, cvl);
+  if constexpr (GRAD) coef_row<I>(ctab, jj * kCoefPitch<I, V>, cvl);
   const V* cv = GRAD ? cvl : cvreg;
   Weights<I, GRAD, V> wt;
-  lane_weights(cv, [&](V* cd) { coef_row<I>(ctab, I * I + jj * I, cd); }, j, h, t1, t2, t3, wt);
+  lane_weights(cv, [&](V* cd) { coef_row<I>(ctab, (I + jj) * kCoefPitch<I, V>, cd); }, j, h, t1, t2, t3, wt);
   // contraction: x2 over all rows per plane, x3 over this lane's planes
   const int noff = l2 * RP + (l1 + jj) * NB;
   const int s0 = (z3 + h) % R;
@@ -403,20 +410,20 @@ __global__ __launch_bounds__(StoreT<ST>::THREADS, ST == ST_F64 ? 2 : 4) void k_i
   const int h = l16 >> 3;             // plane half
   const int jj = j < I ? j : I - 1;
   const int grp = tid / GL;
-  // the kernel's coefficient rows (in powers of t - 1/2) in LDS: [2][I][I]
+  // the kernel's coefficient rows (in powers of t - 1/2) in LDS: [2][I] rows
   // values then derivatives; written here, read after the first barrier
-  __shared__ __attribute__((aligned(16))) V ctab[2 * I * I];
+  __shared__ __attribute__((aligned(16))) V ctab[2 * I * kCoefPitch<I, V>];
   {
     const KernelTables* tab = (const KernelTables*)a.coef;
     for (int e = tid; e < 2 * I * I; e += Gm::THREADS) {
       const int d = e / (I * I), rr = (e / I) % I, p = e % I;
       if constexpr (sizeof(V) == 8)
-        ctab[e] = d ? tab->cder64[rr][p] : tab->cval64[rr][p];
+        ctab[(d * I + rr) * kCoefPitch<I, V> + p] = d ? tab->cder64[rr][p] : tab->cval64[rr][p];
       else
-        ctab[e] = d ? tab->cder32[rr][p] : tab->cval32[rr][p];
+        ctab[(d * I + rr) * kCoefPitch<I, V> + p] = d ? tab->cder32[rr][p] : tab->cval32[rr][p];
     }
   }
-  const V* cvrow = ctab + jj * I;
+  const V* cvrow = ctab + jj * kCoefPitch<I, V>;
   // value kernels hold their row in registers for the whole launch (a read
   // per round would sit at the head of every round's dependency chain); the
   // gradient kernels, which need their registers for the sums, read both
@@ -461,14 +468,18 @@ __global__ __launch_bounds__(StoreT<ST>::THREADS, ST == ST_F64 ? 2 : 4) void k_i
   constexpr int DEPTH = (GRAD || ST == ST_BF16 || ST == ST_F16) ? 1 : 2;
   uint4 pre[DEPTH][Gm::PRE][3];
   bool pok[DEPTH][Gm::PRE];
-  // window w+1: its particle range, this thread's coordinate and destination
+  // the next item (a chunk of a window): its window's range from its first
+  // particle on, this thread's coordinate and destination
   double pos_x = 0.0;
   uint32_t pos_q = 0u, pos_s = 0u, pos_e = 0u;
   int pos_n = 0;
-  // window w+2: its particle range, this thread's row of X and destination
+  // the item after it: range, this thread's row of X and destination
   uint32_t idx_i = 0u, idx_q = 0u, idx_s = 0u, idx_e = 0u;
   int idx_n = 0;
-  // the end of window w+3's range, read a window before it is needed
+  // the index registers' window (counted from w_begin; n_w windows), and the
+  // end of the window after it, read an item before it is needed
+  const int n_w = (int)(w_end - w_begin);
+  int idx_w = 0;
   uint32_t end3 = 0u;
 
   // (the unit index of a thread is recomputed per window from a laundered
@@ -547,17 +558,6 @@ __global__ __launch_bounds__(StoreT<ST>::THREADS, ST == ST_F64 ? 2 : 4) void k_i
       }
     }
   };
-  // position coordinate + destination index of particle c0 + tid/3 (clamped, unconditional)
-  auto issue_pos = [&](uint32_t c0, int n, double& xv, uint32_t& qv) {
-    const int pi = min(tid / 3, max(n - 1, 0));
-    const int64_t p = min((int64_t)c0 + pi, (int64_t)a.np - 1);
-    const int64_t xi = a.xrow ? (int64_t)a.xrow[p] : p;
-    xv = a.X[3 * xi + tid % 3];
-    // axis-1 threads fetch the gradient destination, the others the value one
-    const uint32_t* src = (tid % 3 == 1 && a.grad_orig) ? a.grad_orig : a.orig;
-    qv = src ? src[p] : (uint32_t)p;
-  };
-  // steps 1-3 of Sec. 2.2 once per coordinate: one thread per (particle, axis)
   // steps 1-3 of Sec. 2.2 once per coordinate: one thread per (particle, axis)
   auto write_rec = [&](int64_t wr, int n, double xv, uint32_t qv) {
     settle(xv);
@@ -727,15 +727,20 @@ __global__ __launch_bounds__(StoreT<ST>::THREADS, ST == ST_F64 ? 2 : 4) void k_i
   };
   // the coordinate of that row (iv is always a row of X)
   auto issue_window_x = [&](uint32_t iv, double& xv) { xv = a.X[3 * (int64_t)iv + tid % 3]; };
-  // one window: records of w are in LDS, the ring holds w's planes, the
-  // position registers hold w's range; plane buffer B (w - w_begin mod DEPTH)
-  // receives the planes of w+DEPTH
-  auto window = [&](int64_t w, auto B_) {
-    constexpr int B = decltype(B_)::value;
-    constexpr int B1 = (B + 1) % DEPTH;
-    const uint32_t start = pos_s, end = pos_e;
-    // positions of w+1 from the rows found a window ago, then the rows of w+2
-    // (the rows' loads are waited for before any new load is issued)
+  // the item after the one whose rows are in the index registers: the next
+  // chunk of its window, or the first of the next window (an empty one past
+  // the segment's end)
+  auto next_idx = [&]() {
+    const bool more = idx_e - idx_s > (uint32_t)CH;
+    const uint32_t s = more ? idx_s + (uint32_t)CH : idx_e, e = more ? idx_e : end3;
+    if (!more) idx_w = min(idx_w + 1, n_w);
+    issue_window_idx(s, e, idx_i, idx_q, idx_n, idx_s, idx_e);
+    end3 = woff[min(idx_w + 2, n_w)];
+  };
+  // positions of the item whose rows were found an item ago, then the rows of
+  // the item after it (the rows' loads are waited for before any new load is
+  // issued)
+  auto next_pos = [&]() {
     settle(idx_i);
     settle(idx_q);
     pos_s = idx_s;
@@ -743,20 +748,27 @@ __global__ __launch_bounds__(StoreT<ST>::THREADS, ST == ST_F64 ? 2 : 4) void k_i
     pos_n = idx_n;
     pos_q = idx_q;
     issue_window_x(idx_i, pos_x);
-    issue_window_idx(idx_e, w + 2 < w_end ? end3 : idx_e, idx_i, idx_q, idx_n, idx_s, idx_e);
-    if (w + 3 < w_end) end3 = woff[w + 4 - w_begin];
+    next_idx();
+  };
+  // one window: records of its first chunk are in LDS, the ring holds its
+  // planes; plane buffer B (w - w_begin mod DEPTH) receives the planes of
+  // w+DEPTH
+  auto window = [&](int64_t w, auto B_) {
+    constexpr int B = decltype(B_)::value;
+    constexpr int B1 = (B + 1) % DEPTH;
+    uint32_t start = pos_s;
+    const uint32_t end = pos_e;
+    next_pos();
     issue_planes(w + DEPTH, pre[B], pok[B]);
     __syncthreads();  // records of w and the ring are complete
-    int n = (int)min((int64_t)CH, (int64_t)end - (int64_t)start);
-    compute_chunk(n);
-    // rare: more than CH particles in the window; later chunks are loaded in place
-    for (uint32_t c0 = start + CH; c0 < end; c0 += CH) {
-      const int m = (int)min((int64_t)CH, (int64_t)end - (int64_t)c0);
-      double xm;
-      uint32_t qm;
-      issue_pos(c0, m, xm, qm);
-      __syncthreads();
-      write_rec(w, m, xm, qm);
+    compute_chunk((int)min((int64_t)CH, (int64_t)end - (int64_t)start));
+    // further chunks of a crowded window: their positions were loaded during
+    // the chunk before
+    for (; end - start > (uint32_t)CH; start += (uint32_t)CH) {
+      const int m = pos_n;
+      __syncthreads();  // every read of the chunk's records is done
+      write_rec(w, m, pos_x, pos_q);
+      next_pos();
       __syncthreads();
       if constexpr (PAIR) {
         const int kr = rank_kappa(m);
@@ -801,8 +813,10 @@ __global__ __launch_bounds__(StoreT<ST>::THREADS, ST == ST_F64 ? 2 : 4) void k_i
       __syncthreads();
       place(nv, kr);
     }
-    issue_window_idx(pos_e, w_begin + 1 < w_end ? woff[2] : pos_e, idx_i, idx_q, idx_n, idx_s, idx_e);
-    if (w_begin + 2 < w_end) end3 = woff[3];
+    idx_s = pos_s;
+    idx_e = pos_e;
+    end3 = woff[min(2, n_w)];
+    next_idx();
   }
   static_for<1, DEPTH>([&](auto K) { issue_planes(w_begin + decltype(K)::value, pre[decltype(K)::value], pok[decltype(K)::value]); });
   // windows in pairs so that every plane buffer index is a constant (single
