@@ -198,12 +198,31 @@ int flag_error(ptk_ctx* c, int h) {
   return PTK_OK;
 }
 
+// The status words live in pinned host memory, cleared and read by the host
+// itself: as a device word they cost a small call a launch to clear and a copy
+// to read, two of the three commands of a direct call (1000 particles on 32^3:
+// 32 us a call so, now 20; a Heun step of 10^4 on 32^3 34 us, now 21).
+int* flag_words(const ptk_ctx* c) { return const_cast<int*>(c->flag); }
+
+int read_flag(const ptk_ctx* c, int slot) {
+  return (c->flag[2 * slot] ? kFlagDomain : 0) | (c->flag[2 * slot + 1] ? kFlagBinning : 0);
+}
+
+// Before a call's first launch.  (Without checks nothing reads the words; with
+// them every call ends in check_flag, unless it failed half-way.)
+void clear_flag(ptk_ctx* c) {
+  if (!c->check) return;
+  if (c->flag_busy) (void)hipDeviceSynchronize();
+  c->flag[0] = 0;
+  c->flag[1] = 0;
+  c->flag_busy = true;
+}
+
 int check_flag(ptk_ctx* c, hipStream_t s) {
   if (!c->check) return PTK_OK;
-  int h = 0;
-  PTK_HIP(c, hipMemcpyAsync(&h, c->flag.ptr, sizeof(int), hipMemcpyDeviceToHost, s), "flag read");
   PTK_HIP(c, hipStreamSynchronize(s), "stream synchronize");
-  return flag_error(c, h);
+  c->flag_busy = false;
+  return flag_error(c, read_flag(c, 0));
 }
 
 // scratch for binning Np particles over n_bins bins
@@ -298,7 +317,7 @@ InterpArgs base_args(const ptk_ctx* c, bool next_field = false) {
   a.nseg = (a.nw + a.wps - 1) / a.wps;
   a.offsets = (const uint32_t*)c->offsets.ptr;
   a.coef = c->coef.ptr;
-  a.flag = (int*)c->flag.ptr;
+  a.flag = flag_words(c);
   for (int q = 0; q < 3; ++q) a.scale[q] = next_field ? c->scale_next[q] : c->scale[q];
   return a;
 }
@@ -380,13 +399,13 @@ int interp_core(ptk_ctx* c, const InterpScratch& w, const double* X, int64_t Np,
     }
     return PTK_OK;
   }
-  PTK_HIP(c, launch_fill_i32((int*)c->flag.ptr, 1, 0, s), "flag clear");
+  clear_flag(c);
   const Route route = route_of(c, Np, grad != nullptr);
   uint32_t* perm = nullptr;
   if (route != Route::kDirect) {
     {
       Timed t(c, s, PTK_T_KEYS);
-      PTK_HIP(c, launch_keys(X, Np, (int)N, invd_of(N), bg, w.keys_a, (int*)c->flag.ptr, s), "keys");
+      PTK_HIP(c, launch_keys(X, Np, (int)N, invd_of(N), bg, w.keys_a, flag_words(c), s), "keys");
     }
     Timed t(c, s, PTK_T_SORT);
     uint32_t* sk = nullptr;
@@ -598,11 +617,14 @@ int ptk_create(ptk_ctx** out, int device) {
     delete c;
     return PTK_EHIP;
   }
-  int r = ensure(c, c->flag, 256);
-  if (r != PTK_OK) {
+  void* flag = nullptr;
+  if (hipHostMalloc(&flag, 4 * sizeof(int), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+    (void)hipGetLastError();
     delete c;
-    return r;
+    return PTK_ENOMEM;
   }
+  c->flag = (volatile int*)flag;
+  for (int q = 0; q < 4; ++q) c->flag[q] = 0;
   c->noalloc = noalloc_scratch(device);
   *out = c;
   return PTK_OK;
@@ -614,7 +636,7 @@ void ptk_destroy(ptk_ctx* c) {
     DeviceGuard g(c->device);
     (void)hipDeviceSynchronize();
     DevBuf* bufs[] = {&c->field, &c->field_next, &c->coef, &c->bin_keys, &c->keys_a, &c->keys_b, &c->vals_a, &c->vals_b, &c->offsets,
-                      &c->hist, &c->scan_tmp, &c->flag, &c->xs, &c->xn, &c->orig, &c->orig_b, &c->k1,
+                      &c->hist, &c->scan_tmp, &c->xs, &c->xn, &c->orig, &c->orig_b, &c->k1,
                       &c->k2, &c->abh[0], &c->abh[1], &c->abh[2], &c->abh[3], &c->abh_b[0], &c->abh_b[1],
                       &c->abh_b[2], &c->abh_b[3], &c->gint, &c->stage, &c->lparams,
                       &c->lm, &c->lv, &c->lw1b, &c->lw2b, &c->lw2bt, &c->lgpart, &c->llpart, &c->lwide,
@@ -625,6 +647,7 @@ void ptk_destroy(ptk_ctx* c) {
                       &c->ori_h[2], &c->ori_h[3], &c->ori_hb[0], &c->ori_hb[1], &c->ori_hb[2], &c->ori_hb[3],
                       &c->gint2, &c->io};
     for (DevBuf* b : bufs) release(*b);
+    if (c->flag) (void)hipHostFree(const_cast<int*>(c->flag));
     fft_release(c->fft);
     c->fft = nullptr;
     for (TimedPair& p : c->pending) {
@@ -853,8 +876,8 @@ int ptk_locate(ptk_ctx* c, const double* X, int64_t Np, int32_t* cell, double* t
   DeviceGuard g(c->device);
   if (g.err != hipSuccess) return hip_fail(c, g.err, "hipSetDevice");
   hipStream_t s = S(stream);
-  PTK_HIP(c, launch_fill_i32((int*)c->flag.ptr, 1, 0, s), "flag clear");
-  PTK_HIP(c, launch_locate(X, 3 * Np, (int)c->geom.N, invd_of(c->geom.N), cell, t, (int*)c->flag.ptr, s),
+  clear_flag(c);
+  PTK_HIP(c, launch_locate(X, 3 * Np, (int)c->geom.N, invd_of(c->geom.N), cell, t, flag_words(c), s),
           "locate");
   return check_flag(c, s);
 }
@@ -971,8 +994,8 @@ int adv_load(ptk_ctx* c, const double* X, int64_t Np, const void* rhs_hist, int 
   }
   c->bin_valid = false;  // the sort below reuses the interpolate calls' sort buffers
   uint32_t* keys = (uint32_t*)c->keys_a.ptr;
-  int* flag = (int*)c->flag.ptr;
-  PTK_HIP(c, launch_fill_i32(flag, 1, 0, s), "flag clear");
+  int* flag = flag_words(c);
+  clear_flag(c);
   const bool binned = route_of(c, Np, false) != Route::kDirect;
   if (Np > 0) {
     Timed t(c, s, PTK_T_KEYS);
@@ -1151,7 +1174,7 @@ int adv_steps(ptk_ctx* c, int scheme, double dt, int nsteps, void* grad_out, hip
   }
 
   uint32_t* keys = (uint32_t*)c->keys_a.ptr;
-  int* flag = (int*)c->flag.ptr;
+  int* flag = flag_words(c);
   void* k2 = c->k2.ptr;
   int hl = st.hl;
   auto gather_v = [&](const void* in, const uint32_t* pm, void* out) -> hipError_t {
@@ -1239,7 +1262,7 @@ int adv_steps(ptk_ctx* c, int scheme, double dt, int nsteps, void* grad_out, hip
     return PTK_OK;
   };
 
-  PTK_HIP(c, launch_fill_i32(flag, 1, 0, s), "flag clear");
+  if (!final_X) clear_flag(c);  // (the one-shot form: adv_load did, and its kernels may be running)
   const bool direct = route_of(c, Np, false) != Route::kSweep;
   if (!direct && !st.binned) {
     // the particles were stepped without bins (on another field): sort them
@@ -1472,7 +1495,7 @@ int ptk_advance_particles(ptk_ctx* c, double* X, int64_t Np, void* rhs_hist, int
     DirectSteps d = direct_steps(scheme, dt, K ? *hist_len : 0, a);
     d.X = X;
     for (int j = 0; j < K; ++j) d.hist[j] = (char*)rhs_hist + (size_t)j * Np * 3 * vel_bytes(c);
-    PTK_HIP(c, launch_fill_i32((int*)c->flag.ptr, 1, 0, s), "flag clear");
+    clear_flag(c);
     PTK_TRY(run_direct_steps(c, a, d, nsteps, s));
     PTK_TRY(check_flag(c, s));
     if (K) *hist_len = d.hl;
@@ -1890,9 +1913,9 @@ int ptk_learned_make_pairs(ptk_ctx* c, const double* X, int64_t Np, uint16_t* fe
     PTK_TRY(need(c, c->lwide, (size_t)Np * 12, "wide-kernel values"));
     PTK_TRY(interp_common(c, X, Np, c->lwide.ptr, nullptr, PTK_F32, stream));
   }
-  PTK_HIP(c, launch_fill_i32((int*)c->flag.ptr, 1, 0, s), "flag clear");
+  clear_flag(c);
   PTK_HIP(c,
-          launch_learned_pairs(lf, X, Np, (const float*)c->lwide.ptr, feat, target, (int*)c->flag.ptr, s),
+          launch_learned_pairs(lf, X, Np, (const float*)c->lwide.ptr, feat, target, flag_words(c), s),
           "training pairs");
   return check_flag(c, s);
 }
@@ -2051,11 +2074,12 @@ int ptk_interpolate_learned(ptk_ctx* c, const double* X, int64_t Np, float* out,
   const int64_t n_bins = n_bins_of(bg);
   c->bin_valid = false;
   PTK_TRY(ensure_binning(c, Np, n_bins));
-  PTK_HIP(c, launch_fill_i32((int*)c->flag.ptr, 1, 0, s), "flag clear");
+  int* flag = flag_words(c) + 2;  // (no earlier call on these words is unfinished: it waited)
+  c->flag[2] = 0;
+  c->flag[3] = 0;
   {
     Timed t(c, s, PTK_T_KEYS);
-    PTK_HIP(c, launch_keys(X, Np, (int)N, invd_of(N), bg, (uint32_t*)c->keys_a.ptr, (int*)c->flag.ptr, s),
-            "keys");
+    PTK_HIP(c, launch_keys(X, Np, (int)N, invd_of(N), bg, (uint32_t*)c->keys_a.ptr, flag, s), "keys");
   }
   uint32_t* perm = nullptr;
   {
@@ -2067,16 +2091,13 @@ int ptk_interpolate_learned(ptk_ctx* c, const double* X, int64_t Np, float* out,
     Timed t(c, s, PTK_T_LEARNED);
     PTK_HIP(c,
             launch_learned_infer(lf, X, Np, perm, (const float*)c->lparams.ptr,
-                                 (const uint16_t*)c->lw1b.ptr, (const uint16_t*)c->lw2b.ptr, out, (int*)c->flag.ptr,
-                                 s),
+                                 (const uint16_t*)c->lw1b.ptr, (const uint16_t*)c->lw2b.ptr, out, flag, s),
             "learned interpolation");
   }
   {
     // positions outside the domain are reported before the audit re-bins
-    int h = 0;
-    PTK_HIP(c, hipMemcpyAsync(&h, c->flag.ptr, sizeof(int), hipMemcpyDeviceToHost, s), "flag read");
     PTK_HIP(c, hipStreamSynchronize(s), "stream synchronize");
-    PTK_TRY(flag_error(c, h));
+    PTK_TRY(flag_error(c, read_flag(c, 1)));
   }
   // audit with the wide kernel at particles 0, k, 2k, ...
   int64_t k = (int64_t)std::llround(1.0 / audit_frac);

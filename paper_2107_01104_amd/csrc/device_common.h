@@ -12,6 +12,13 @@
 
 namespace ptk {
 
+// Raise one condition in the call's status words (pinned host memory the host
+// reads once the stream has completed): one word per condition, so that a
+// plain store will do.
+__device__ __forceinline__ void raise_flag(int* flag, int bit) {
+  *(volatile int*)(flag + (bit == kFlagDomain ? 0 : 1)) = 1;
+}
+
 // Positions accepted by the library: finite with |x| < 2^50.  Beyond that the
 // binary64 wrap below can no longer bring x into [0, 2*pi) (the rounding error
 // of L*q exceeds L), so such positions are reported as a domain error.

@@ -184,7 +184,7 @@ __global__ __launch_bounds__(kDirThreads) void k_direct(InterpArgs a, BinGeom g,
   share_value<ST, GRAD>(a, r, u);
   if (!active) return;
   if (l16 == 0) {
-    if (!ok) atomicOr(a.flag, kFlagDomain);
+    if (!ok) raise_flag(a.flag, kFlagDomain);
     if (keys) keys[p] = ok ? bin_key(c[0], c[1], c[2], g) : 0u;
   }
   const int64_t q = a.orig ? (int64_t)a.orig[p] : p;
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_steps(InterpArgs a, Dire
     }
   }
   if (!active) return;
-  if (l16 == 0 && !ok) atomicOr(a.flag, kFlagDomain);
+  if (l16 == 0 && !ok) raise_flag(a.flag, kFlagDomain);
   if (l16 < 3) {
     s.X[3 * row + l16] = l16 == 0 ? x[0] : l16 == 1 ? x[1] : x[2];
     if (s.kind == kAB) {

@@ -584,7 +584,7 @@ __global__ __launch_bounds__(StoreT<ST>::THREADS, ST == ST_F64 ? 2 : 4) void k_i
         inside = (int64_t)c >= W * wr && (int64_t)c < W * wr + W;
         lc = (int)min(max((int64_t)c, W * wr), W * wr + W - 1);
       }
-      if (!inside) atomicOr(a.flag, kFlagBinning);
+      if (!inside) raise_flag(a.flag, kFlagBinning);
       // the weights are polynomials in t - 1/2 (exact in binary64 for t >= 1/4
       // by Sterbenz's lemma and for every t that is a multiple of 2^-53;
       // below that it rounds by less than 2^-54)

@@ -8,7 +8,7 @@
 
 namespace ptk {
 
-// Bits of the device status word the kernels raise (atomicOr) and the host
+// Conditions the kernels raise (raise_flag, one status word each) and the host
 // reads at the end of a call.
 constexpr int kFlagDomain = 1;   // a position was NaN, infinite or |x| >= 2^50
 constexpr int kFlagBinning = 2;  // a particle's cell lies outside its bin's tile column or window
@@ -105,7 +105,7 @@ struct InterpArgs {
   int out_f64;
   const void* coef;         // device KernelTables
   float scale[3];
-  int* flag;                // device status word (kFlag* bits)
+  int* flag;                // status words (raise_flag)
 };
 hipError_t launch_interp(int storage, int I, const InterpArgs& a, hipStream_t s);
 

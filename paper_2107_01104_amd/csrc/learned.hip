@@ -163,7 +163,7 @@ __global__ __launch_bounds__(NT) void k_pairs(LearnedField f, const double* X, i
   int c[3];
   double td[3];
   const bool ok = locate_quad(X + 3 * p, k3, f.N, f.invd, c, td);
-  if (active && !ok) atomicOr(flag, kFlagDomain);
+  if (active && !ok) raise_flag(flag, kFlagDomain);
   uint32_t fe[24];
   float u[3];
   stencil_plane(f, c, td, k3, fe, u);
@@ -758,7 +758,7 @@ __global__ __launch_bounds__(NT, 2) void k_infer(LearnedField f, const double* X
     const uint32_t o_dst = xrow_of(ch * ROWS + orow);
     const uint32_t oi_nn = xrow(min(ch + 2, ch_end - 1));
     const bool active = ch * ROWS + pi < n;
-    if (active && !ok) atomicOr(flag, kFlagDomain);
+    if (active && !ok) raise_flag(flag, kFlagDomain);
     uint32_t fe[24];
     float u[3];
     stencil_sums(f, td, k3, q, fe, u);

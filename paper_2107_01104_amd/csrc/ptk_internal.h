@@ -105,7 +105,11 @@ struct ptk_ctx {
   bool bin_from_keys = false;
   ptk::DevBuf bin_keys;
   // scratch
-  ptk::DevBuf keys_a, keys_b, vals_a, vals_b, offsets, hist, scan_tmp, flag;
+  ptk::DevBuf keys_a, keys_b, vals_a, vals_b, offsets, hist, scan_tmp;
+  // status words in pinned host memory: two for the calls, two for the learned
+  // inference (which reads its own whether or not checks are on)
+  volatile int* flag = nullptr;
+  bool flag_busy = false;  // a call that uses them has not been waited for
   ptk::DevBuf xs, xn, orig, orig_b, k1, k2, gint, stage;
   ptk::DevBuf abh[4], abh_b[4];  // Adams-Bashforth history in bin order, and its permuted copy
   // incremental re-binning inside advance: sorted keys and offsets of the

@@ -99,7 +99,7 @@ __global__ __launch_bounds__(kUpdThreads) void k_update(int kind, const double* 
       (void)locate(xn, N, invd, &c[d], &t);
       sx[e] = xn;  // only this thread touches its three entries
     }
-    if (!ok) atomicOr(flag, kFlagDomain);
+    if (!ok) raise_flag(flag, kFlagDomain);
     keys[base + p] = bin_key(c[0], c[1], c[2], g);
   }
   __syncthreads();
