@@ -151,15 +151,16 @@ int ptk_get_field_scale(const ptk_ctx *ctx, float *scale3);
  * The grid field is the Fourier series u_a(x) = sum over all k of
  *    u^_a(k) exp(i k.x) at the nodes x = delta (j1, j2, j3) (the modes with
  *    k1 < 0 being the complex conjugates of the stored ones), computed by an
- *    inverse real FFT in the precision of in_dtype (rocFFT), then stored as by
+ *    inverse real FFT in the precision of in_dtype (the library's own for
+ *    N = 64, 128, 256, 512 and 1024, else rocFFT), then stored as by
  *    ptk_set_field (same storage types, scale and kernel rules).  The k1 = 0
  *    and k1 = N/2 planes must be Hermitian, as those of a real field are
  *    (u^(-k) = conj u^(k) within the plane); otherwise the result is
  *    undefined.
- * N: even, 8 <= N <= 2048.  The library keeps a transform buffer of
- *    3 N^2 (N/2+1) complex numbers of in_dtype, one of 3 N^3 real numbers for
- *    its result and the transform's work buffer (grown, never shrunk,
- *    released by ptk_destroy).
+ * N: even, 8 <= N <= 2048.  The library keeps a transform buffer of about
+ *    3 N^2 (N/2+1) complex numbers of in_dtype, and (with rocFFT, or for 16-bit
+ *    storage) one of 3 N^3 real numbers for its result and the transform's work
+ *    buffer (grown, never shrunk, released by ptk_destroy).
  * Errors: PTK_EINVAL (NULL pointer, odd or out-of-range N, bad kind or
  *    dtype), PTK_EUNSUPPORTED (kernel), PTK_ENOMEM, PTK_EHIP (transform set-up
  *    or launch); on an argument error the context is unchanged. */
@@ -422,8 +423,9 @@ int ptk_get_binning(ptk_ctx *ctx, uint32_t *perm, uint32_t *offsets, void *strea
  *   PTK_T_UPDATE       position update (+ keys of the new positions)
  *   PTK_T_PERMUTE      gathers/scatters of particle state between orders
  *   PTK_T_LEARNED      learned-form inference kernel (features, L4 sum, network)
- *   PTK_T_IFT          spectral set-up: spectrum reorder (and Biot-Savart) and
- *                      the inverse FFT (the field pack is not included)
+ *   PTK_T_IFT          spectral set-up: Biot-Savart and the inverse FFT (with
+ *                      rocFFT or 16-bit storage the field pack is not included;
+ *                      the library's own transform stores the field itself)
  * ptk_timing_enable(ctx, 1) starts (and clears) the accumulators, 0 stops.
  * ptk_timing_read waits for the recorded events, adds their durations to the
  * accumulators and copies them out: ms[PTK_T_COUNT] (milliseconds) and

@@ -642,7 +642,7 @@ void ptk_destroy(ptk_ctx* c) {
                       &c->lm, &c->lv, &c->lw1b, &c->lw2b, &c->lw2bt, &c->lgpart, &c->llpart, &c->lwide,
                       &c->laudit_x, &c->laudit_u, &c->laudit_sums, &c->skeys, &c->skeys2, &c->offsets2,
                       &c->mk_a, &c->mk_b, &c->mv_a, &c->mv_b, &c->mo, &c->rb_in, &c->rb_out, &c->rb_inc,
-                      &c->rb_block, &c->spec, &c->fft_out, &c->fft_work, &c->aoff, &c->aperm, &c->aperm_p,
+                      &c->rb_block, &c->spec, &c->fft_out, &c->fft_work, &c->twiddles, &c->aoff, &c->aperm, &c->aperm_p,
                       &c->ori_p, &c->ori_pn, &c->ori_r1, &c->ori_r2, &c->ori_ps, &c->ori_h[0], &c->ori_h[1],
                       &c->ori_h[2], &c->ori_h[3], &c->ori_hb[0], &c->ori_hb[1], &c->ori_hb[2], &c->ori_hb[3],
                       &c->gint2, &c->io};
@@ -681,10 +681,18 @@ int check_field_args(ptk_ctx* c, int64_t N, int in_dtype, int storage_dtype, con
   return PTK_OK;
 }
 
-// Stores the grid field u (layout l, FP64 or FP32) as the context's field:
-// the per-component scale for 16-bit storage, the coefficient tables, the pack.
+// A half spectrum that the library's own transform writes into the field.
+struct SpecSource {
+  const void* spec;
+  int f64, vorticity;
+};
+
+// Stores the grid field u (layout l, FP64 or FP32), or with `spec` the field of
+// that spectrum (FP64 or FP32 storage), as the context's field: the
+// per-component scale for 16-bit storage, the coefficient tables, the pack.
 int store_field(ptk_ctx* c, const void* u, int in_f64, const SrcLayout& l, int64_t N, int storage_dtype,
-                const ptk_kernel* k, int m, const KernelTables& tab, hipStream_t s, bool next_field = false) {
+                const ptk_kernel* k, int m, const KernelTables& tab, hipStream_t s, bool next_field = false,
+                const SpecSource* spec = nullptr) {
   FieldGeom geo;
   geo.N = N;
   geo.P = N + k->I - 1;
@@ -723,15 +731,21 @@ int store_field(ptk_ctx* c, const void* u, int in_f64, const SrcLayout& l, int64
     }
     delete[] part;
   }
+  auto fill = [&](void* field) -> hipError_t {
+    if (!spec)
+      return launch_pack(u, in_f64, l, N, storage_dtype, k->I, field, geo.row_pitch, geo.plane_pitch, inv, s);
+    Timed t(c, s, PTK_T_IFT);
+    const SpecTransform p{spec->spec,    c->spec.ptr,     c->twiddles.ptr, spec_transform_row(N, spec->f64),
+                          field,         geo.row_pitch,   geo.plane_pitch, (int)geo.P,
+                          geo.halo_lo,   storage_dtype == PTK_F64};
+    return launch_spec_transform(p, N, spec->f64, spec->vorticity, s);
+  };
   if (next_field) {
     // the next time's field: same kernel, tables and storage as the current
     c->has_next = false;
     PTK_TRY(ensure(c, c->field_next, field_bytes));
     PTK_TRY(need(c, c->field_next, field_bytes, "stored next field"));
-    PTK_HIP(c,
-            launch_pack(u, in_f64, l, N, storage_dtype, k->I, c->field_next.ptr, geo.row_pitch, geo.plane_pitch, inv,
-                        s),
-            "field pack");
+    PTK_HIP(c, fill(c->field_next.ptr), "field pack");
     c->geom_next = geo;
     for (int q = 0; q < 3; ++q) c->scale_next[q] = scl[q];
     c->has_next = true;
@@ -750,8 +764,7 @@ int store_field(ptk_ctx* c, const void* u, int in_f64, const SrcLayout& l, int64
   c->tables = tab;
   PTK_HIP(c, hipMemcpyAsync(c->coef.ptr, &c->tables, sizeof(KernelTables), hipMemcpyHostToDevice, s),
           "coefficient upload");
-  PTK_HIP(c, launch_pack(u, in_f64, l, N, storage_dtype, k->I, c->field.ptr, geo.row_pitch, geo.plane_pitch, inv, s),
-          "field pack");
+  PTK_HIP(c, fill(c->field.ptr), "field pack");
   c->geom = geo;
   c->family = k->family;
   c->I = k->I;
@@ -788,6 +801,60 @@ int spectrum_to_grid(ptk_ctx* c, const void* spec, int64_t N, int f64, int kind,
   return PTK_OK;
 }
 
+// Buffers and twiddles of the library's own transform of (N, precision).
+int ensure_transform(ptk_ctx* c, int64_t N, int f64, hipStream_t s) {
+  const size_t cb = f64 ? 16 : 8;
+  const size_t mid = (size_t)N * (size_t)N * (size_t)spec_transform_row(N, f64) * cb;
+  PTK_TRY(ensure(c, c->spec, mid));
+  PTK_TRY(need(c, c->spec, mid, "transform buffer"));
+  if (c->tw_N != N || c->tw_f64 != f64) {
+    c->tw_N = 0;
+    PTK_TRY(ensure(c, c->twiddles, (size_t)N * cb));
+    PTK_TRY(need(c, c->twiddles, (size_t)N * cb, "twiddles"));
+    try {
+      c->tw_host.resize((size_t)N * 2);
+    } catch (const std::bad_alloc&) {
+      return fail(c, PTK_ENOMEM, "host allocation failed");
+    }
+    spec_twiddles(N, f64, c->tw_host.data());
+    PTK_HIP(c, hipMemcpyAsync(c->twiddles.ptr, c->tw_host.data(), (size_t)N * cb, hipMemcpyHostToDevice, s),
+            "twiddle upload");
+    c->tw_N = N;
+    c->tw_f64 = f64;
+  }
+  return PTK_OK;
+}
+
+// Stores the field of a half spectrum.  Grids the library's own transform is
+// built for take its three passes, straight into the stored rows (16-bit
+// storage, whose scale is the whole field's rms, by way of the plain grid);
+// others go through rocFFT's planes.  Measured with FP64 vorticity
+// into FP32 storage: 64^3 172 us by rocFFT, 157 so; 128^3 185 and 166; 256^3
+// 1041 and 570; 512^3 7.68 ms and 4.33; 1024^3 81.5 and 33.9; into BF16 512^3
+// 8.17 and 5.71.
+int store_spectrum(ptk_ctx* c, const void* spec, int64_t N, int f64, int kind, int storage, const ptk_kernel* k, int m,
+                   const KernelTables& tab, hipStream_t s, bool next_field) {
+  if (!spec_transform_built(N)) {
+    PTK_TRY(spectrum_to_grid(c, spec, N, f64, kind, s));
+    return store_field(c, c->fft_out.ptr, f64, transform_layout(N), N, storage, k, m, tab, s, next_field);
+  }
+  PTK_TRY(ensure_transform(c, N, f64, s));
+  const SpecSource src{spec, f64, kind == PTK_SPEC_VORTICITY};
+  if (storage == PTK_F64 || storage == PTK_F32)
+    return store_field(c, nullptr, f64, interleaved_layout(N), N, storage, k, m, tab, s, next_field, &src);
+  const size_t rb = f64 ? 8 : 4, grid = 3 * (size_t)N * (size_t)N * (size_t)N * rb;
+  PTK_TRY(ensure(c, c->fft_out, grid));
+  PTK_TRY(need(c, c->fft_out, grid, "transform output"));
+  {
+    Timed t(c, s, PTK_T_IFT);
+    const int64_t row = N * 3 * (int64_t)rb;
+    const SpecTransform p{spec, c->spec.ptr, c->twiddles.ptr, spec_transform_row(N, f64), c->fft_out.ptr, row,
+                          row * N, (int)N, 0, f64};
+    PTK_HIP(c, launch_spec_transform(p, N, f64, src.vorticity, s), "transform");
+  }
+  return store_field(c, c->fft_out.ptr, f64, interleaved_layout(N), N, storage, k, m, tab, s, next_field);
+}
+
 }  // namespace
 
 int ptk_set_field(ptk_ctx* c, const void* u, int64_t N, int in_dtype, int storage_dtype, const ptk_kernel* k,
@@ -818,8 +885,7 @@ int ptk_set_field_spectral(ptk_ctx* c, const void* spec, int64_t N, int in_dtype
   if (g.err != hipSuccess) return hip_fail(c, g.err, "hipSetDevice");
   hipStream_t s = S(stream);
   const int f64 = in_dtype == PTK_F64;
-  PTK_TRY(spectrum_to_grid(c, spec, N, f64, kind, s));
-  return store_field(c, c->fft_out.ptr, f64, transform_layout(N), N, storage_dtype, k, m, tab, s);
+  return store_spectrum(c, spec, N, f64, kind, storage_dtype, k, m, tab, s, false);
 }
 
 int ptk_set_field_next(ptk_ctx* c, const void* src, int64_t N, int in_dtype, int form, void* stream) {
@@ -840,8 +906,7 @@ int ptk_set_field_next(ptk_ctx* c, const void* src, int64_t N, int in_dtype, int
   const int f64 = in_dtype == PTK_F64;
   if (form == PTK_GRID)
     return store_field(c, src, f64, interleaved_layout(N), N, c->storage, &k, c->m, c->tables, s, true);
-  PTK_TRY(spectrum_to_grid(c, src, N, f64, form, s));
-  return store_field(c, c->fft_out.ptr, f64, transform_layout(N), N, c->storage, &k, c->m, c->tables, s, true);
+  return store_spectrum(c, src, N, f64, form, c->storage, &k, c->m, c->tables, s, true);
 }
 
 int ptk_get_field(ptk_ctx* c, void* u, int out_dtype, void* stream) {

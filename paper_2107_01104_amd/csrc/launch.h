@@ -86,6 +86,22 @@ int fft_prepare(FftState** st, int64_t N, int f64, size_t* work_bytes, const cha
 int fft_run(FftState* st, void* buf, void* out, void* work, size_t work_bytes, hipStream_t s, const char** err);
 void fft_release(FftState* st);
 
+// fft.hip: the same transform in three passes of this library's own, spectrum
+// in, stored rows out, for the grid sizes spec_transform_built names
+struct SpecTransform {
+  const void* spec;         // the caller's half spectrum
+  void* mid;                // [N][N][spec_transform_row] complex
+  const void* twiddles;     // exp(2 pi i j / N), j < N (spec_twiddles)
+  int64_t mid_row;
+  void* out;                // rows of P nodes of 3 doubles or floats, lo of them below the grid
+  int64_t row_pitch, plane_pitch;  // bytes
+  int P, lo, out_f64;
+};
+bool spec_transform_built(int64_t N);
+int64_t spec_transform_row(int64_t N, int f64);
+void spec_twiddles(int64_t N, int f64, void* host);
+hipError_t launch_spec_transform(const SpecTransform& p, int64_t N, int f64, int vorticity, hipStream_t s);
+
 // interp.hip
 struct InterpArgs {
   const void* field;

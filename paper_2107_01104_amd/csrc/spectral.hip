@@ -9,6 +9,7 @@
 // the vorticity w^(k), from which the Biot-Savart law of Sec. 2.1 gives
 // u^(k) = i k x w^(k) / |k|^2.
 //
+// This file serves the grid sizes that fft.hip is not built for.
 // k_spec_prep writes the three components as [a][k3][k2][k1] (one thread per
 // mode: coalesced writes, and each thread reads its mode's three components
 // from one 48-byte (FP64) or 24-byte (FP32) span); the inverse real transform
