@@ -70,6 +70,15 @@ __device__ __forceinline__ float quad_sum(float v) {
   return v;
 }
 
+// sums over a lane's group of 8 (DPP, every lane gets them) and of 16; shuffles
+// through LDS would put an LDS round trip in every step of a phase's tail
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float sum8(float v) { return dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(v))); }
+__device__ __forceinline__ float sum16(float v) { return dpp_add<0x140>(sum8(v)); }
+
 typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));
 
 // Steps 1-3 of Sec. 2.2 for the particle of this lane's group of 4: lane k
@@ -193,37 +202,42 @@ __global__ __launch_bounds__(NT) void k_pairs(LearnedField f, const double* X, i
 // (and its transpose in sH1t if given), the pre-activations' derivatives
 // (training) in ds1.  Ends with the barrier after which h1 is complete and sX
 // is dead.
-template <bool TRAIN>
+// A wave takes RT of the two 32-row tiles from tile rt0 on (inference: both;
+// training's eight waves: one each).
+template <bool TRAIN, int RT>
 __device__ __forceinline__ void hidden_layer1(const uint16_t* sX, uint16_t* sH1, uint16_t* sH1t,
-                                              const bf16x8 (&bw1)[13], float bias1, f32x16 (&ds1)[2]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+                                              const bf16x8 (&bw1)[13], float bias1, f32x16 (&ds1)[RT], int rt0 = 0) {
+  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3;
   const int r32 = lane & 31, hi = lane >> 5;
   const int J = 32 * wave + r32;
-  f32x16 acc[2];
+  sX += 32 * rt0 * PX;
+  f32x16 acc[RT];
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
+  for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[rt][v] = 0.f;
   // the A fragments of step s + 1 are read while step s's products run; in
   // inference an empty asm with a memory clobber ends every step, so the
   // compiler reads no further ahead (holding all 26 fragments would take 104
   // registers that inference spends on the next chunk's stencil loads)
-  bf16x8 an[2];
+  bf16x8 an[RT];
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt) an[rt] = frag(sX, PX, 32 * rt + r32, 8 * hi);
+  for (int rt = 0; rt < RT; ++rt) an[rt] = frag(sX, PX, 32 * rt + r32, 8 * hi);
 #pragma unroll
   for (int s = 0; s < 13; ++s) {
-    const bf16x8 a0 = an[0], a1 = an[1];
+    bf16x8 a[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) a[rt] = an[rt];
     if (s + 1 < 13) {
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt) an[rt] = frag(sX, PX, 32 * rt + r32, 16 * (s + 1) + 8 * hi);
+      for (int rt = 0; rt < RT; ++rt) an[rt] = frag(sX, PX, 32 * rt + r32, 16 * (s + 1) + 8 * hi);
     }
-    acc[0] = mfma(a0, bw1[s], acc[0]);
-    acc[1] = mfma(a1, bw1[s], acc[1]);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) acc[rt] = mfma(a[rt], bw1[s], acc[rt]);
     if constexpr (!TRAIN) asm volatile("" ::: "memory");
   }
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
+  for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int v0 = 0; v0 < 16; v0 += 4) {
       float h[4];
@@ -234,7 +248,7 @@ __device__ __forceinline__ void hidden_layer1(const uint16_t* sX, uint16_t* sH1,
         if constexpr (TRAIN) ds1[rt][v0 + q] = dsilu(z);
       }
       const uint32_t p01 = pack_bf16(h[0], h[1]), p23 = pack_bf16(h[2], h[3]);
-      const int r0 = 32 * rt + acc_row(v0, hi);
+      const int r0 = 32 * (rt0 + rt) + acc_row(v0, hi);
       sH1[r0 * PH + J] = (uint16_t)p01;
       sH1[(r0 + 1) * PH + J] = (uint16_t)(p01 >> 16);
       sH1[(r0 + 2) * PH + J] = (uint16_t)p23;
@@ -245,41 +259,32 @@ __device__ __forceinline__ void hidden_layer1(const uint16_t* sX, uint16_t* sH1,
 }
 
 // Training's forward pass: layer 1 as above, then h2 (FP32) in sH2 and its
-// pre-activations' derivatives in ds2 (the backward pass reads h2 by rows).
-// sX and sH2 may alias.
+// pre-activations' derivatives in ds2 (the backward pass reads h2 by rows);
+// wave w takes hidden units 32 (w % 4) .. and rows 32 (w / 4) ..  sX and sH2 may
+// alias.
 __device__ __forceinline__ void forward_hidden(const uint16_t* sX, uint16_t* sH1, uint16_t* sH1t, float* sH2,
                                                const bf16x8 (&bw1)[13], const bf16x8 (&bw2)[8], float bias1,
-                                               float bias2, f32x16 (&ds1)[2], f32x16 (&ds2)[2]) {
-  hidden_layer1<true>(sX, sH1, sH1t, bw1, bias1, ds1);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+                                               float bias2, f32x16 (&ds1)[1], f32x16 (&ds2)[1]) {
+  const int lane = threadIdx.x & 63, ub = (threadIdx.x >> 6) & 3, rt = threadIdx.x >> 8;
+  hidden_layer1<true, 1>(sX, sH1, sH1t, bw1, bias1, ds1, rt);
   const int r32 = lane & 31, hi = lane >> 5;
-  const int J = 32 * wave + r32;
-  f32x16 acc[2];
+  const int J = 32 * ub + r32;
+  f32x16 acc;
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[rt][v] = 0.f;
-  bf16x8 an[2];
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt) an[rt] = frag(sH1, PH, 32 * rt + r32, 8 * hi);
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  bf16x8 an = frag(sH1, PH, 32 * rt + r32, 8 * hi);
 #pragma unroll
   for (int s = 0; s < 8; ++s) {
-    const bf16x8 a0 = an[0], a1 = an[1];
-    if (s + 1 < 8) {
-#pragma unroll
-      for (int rt = 0; rt < 2; ++rt) an[rt] = frag(sH1, PH, 32 * rt + r32, 16 * (s + 1) + 8 * hi);
-    }
-    acc[0] = mfma(a0, bw2[s], acc[0]);
-    acc[1] = mfma(a1, bw2[s], acc[1]);
+    const bf16x8 a = an;
+    if (s + 1 < 8) an = frag(sH1, PH, 32 * rt + r32, 16 * (s + 1) + 8 * hi);
+    acc = mfma(a, bw2[s], acc);
   }
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const float z = acc[rt][v] + bias2;
-      sH2[(32 * rt + acc_row(v, hi)) * PH2 + J] = silu(z);
-      ds2[rt][v] = dsilu(z);
-    }
+  for (int v = 0; v < 16; ++v) {
+    const float z = acc[v] + bias2;
+    sH2[(32 * rt + acc_row(v, hi)) * PH2 + J] = silu(z);
+    ds2[0][v] = dsilu(z);
+  }
   __syncthreads();  // h2 complete
 }
 
@@ -351,42 +356,31 @@ __device__ __forceinline__ void infer_layer2_out(const uint16_t* sH1, const bf16
   __syncthreads();  // every wave's sums are in sY
 }
 
-// y[r][a] = b3[a] + sum_c h2[r][c] W3[a][c] for thread t < 192 (r = t/3, a = t%3)
-__device__ __forceinline__ float output_layer(const float* sH2, const float* sW3, const float* b3, int t) {
-  const int r = t / 3, a = t - 3 * (t / 3);
-  const float4* h = (const float4*)(sH2 + r * PH2);
-  const float4* w = (const float4*)(sW3 + a * NH);
-  float y0 = 0.f, y1 = 0.f;
-#pragma unroll 8
-  for (int c = 0; c < NH / 4; c += 2) {
-    const float4 h0 = h[c], w0 = w[c], h1 = h[c + 1], w1 = w[c + 1];
-    y0 = fmaf(h0.x, w0.x, y0);
-    y0 = fmaf(h0.y, w0.y, y0);
-    y0 = fmaf(h0.z, w0.z, y0);
-    y0 = fmaf(h0.w, w0.w, y0);
-    y1 = fmaf(h1.x, w1.x, y1);
-    y1 = fmaf(h1.y, w1.y, y1);
-    y1 = fmaf(h1.z, w1.z, y1);
-    y1 = fmaf(h1.w, w1.w, y1);
-  }
-  return b3[a] + (y0 + y1);
+// The BF16 weight copies are kept in the order the fragments are loaded: element
+// (unit J, input k) of a layer with KS steps of 16 inputs.  A wave's fragment is
+// then 1 KB of consecutive bytes; from row-major copies each of its 64 lanes
+// read its own cache line, and the 29 fragments of a training workgroup took
+// 14 000 of its 35 000 cycles.
+template <int KS>
+__device__ __forceinline__ int frag_index(int J, int k) {
+  return (((J >> 5) * KS + (k >> 4)) * 64 + ((k >> 3) & 1) * 32 + (J & 31)) * 8 + (k & 7);
 }
-
-__device__ __forceinline__ void load_weight_frags(const uint16_t* w1b, const uint16_t* w2b, bf16x8 (&bw1)[13],
-                                                  bf16x8 (&bw2)[8]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int J = 32 * wave + (lane & 31), hi = lane >> 5;
+template <int KS>
+__device__ __forceinline__ void load_frags(const uint16_t* w, bf16x8 (&b)[KS]) {
+  const int lane = threadIdx.x & 63, ub = (threadIdx.x >> 6) & 3;
 #pragma unroll
-  for (int s = 0; s < 13; ++s) bw1[s] = frag(w1b, K1, J, 16 * s + 8 * hi);
-#pragma unroll
-  for (int s = 0; s < 8; ++s) bw2[s] = frag(w2b, NH, J, 16 * s + 8 * hi);
+  for (int s = 0; s < KS; ++s) b[s] = __builtin_bit_cast(bf16x8, ((const uint4*)w)[(ub * KS + s) * 64 + lane]);
 }
 
 // ---------------------------------------------------------------- training
-// One workgroup: 64 consecutive pairs starting at row0 = 64 * blockIdx.x.
+// One workgroup: 64 consecutive pairs starting at row0 = 64 * blockIdx.x, eight
+// waves (wave w: hidden units 32 (w % 4) .., rows 32 (w / 4) ..).  A workgroup is
+// a serial chain of short phases, so the time of a batch is that chain's; with
+// four waves, each on both row tiles, a batch of 16384 took TRAIN_MEASURED.
 // Writes its part of the gradient (parameter layout) to gpart[blockIdx.x] and
 // its sum of squared errors to lpart[blockIdx.x].
-__global__ __launch_bounds__(NT, 1) void k_forward_backward(const uint16_t* feat, const float* target, int64_t batch,
+constexpr int NTB = 512;
+__global__ __launch_bounds__(NTB, 2) void k_forward_backward(const uint16_t* feat, const float* target, int64_t batch,
                                                             const float* params, const uint16_t* w1b,
                                                             const uint16_t* w2b, const uint16_t* w2bt, float* gpart,
                                                             float* lpart, const uint16_t* feat_next) {
@@ -399,10 +393,11 @@ __global__ __launch_bounds__(NT, 1) void k_forward_backward(const uint16_t* feat
   constexpr int R3 = NH * PT * 2;
   static_assert(R3 >= ROWS * PH * 2, "R3 size");
   __shared__ __attribute__((aligned(16))) unsigned char lds[R0 + R1 + R2 + R3];
-  __shared__ float sW3[NO * NH];
-  __shared__ float sdy[ROWS * NO];
-  __shared__ float sdw3[2 * NO * NH];  // dW3 sums of the two halves of the rows
-  __shared__ float sred[NT / 64];
+  __shared__ __attribute__((aligned(16))) float sW3[NO * NH];
+  __shared__ __attribute__((aligned(16))) float sdy[ROWS * 4];  // [row][a], a quad a row
+  __shared__ float sdw3[4 * NO * NH];  // dW3 sums of the four quarters of the rows
+  __shared__ float sdb[2 * 2 * NH];    // db2 and db1 sums of the two row tiles
+  __shared__ __attribute__((aligned(16))) float sred[NTB / 16];
   uint16_t* sXt = (uint16_t*)lds;
   uint16_t* sH1t = (uint16_t*)(lds + R0);
   unsigned char* r2 = lds + R0 + R1;
@@ -414,22 +409,32 @@ __global__ __launch_bounds__(NT, 1) void k_forward_backward(const uint16_t* feat
   uint16_t* sdZ1t = sH1;
 
   const int t = threadIdx.x;
-  const int lane = t & 63, wave = t >> 6, r32 = lane & 31, hi = lane >> 5;
-  const int J = 32 * wave + r32;
+  const int lane = t & 63, wave = t >> 6, ub = wave & 3, rt = wave >> 2, r32 = lane & 31, hi = lane >> 5;
+  const int J = 32 * ub + r32;
   const int64_t row0 = (int64_t)blockIdx.x * ROWS;
   float* gp = gpart + (int64_t)blockIdx.x * kLearnedNParams;
 
   // features -> sX (row-major) and sXt (transposed); entries 195.. are zero.
   // This thread's 16-byte pieces are loaded together (unconditionally, from
   // a clamped address), then stored.
-  constexpr int FE = ROWS * (K1 / 8), FI = (FE + NT - 1) / NT;
+  constexpr int FE = ROWS * (K1 / 8), FI = (FE + NTB - 1) / NTB;
   uint4 fq[FI];
 #pragma unroll
   for (int i = 0; i < FI; ++i) {
-    const int e = min(t + i * NT, FE - 1);
+    const int e = min(t + i * NTB, FE - 1);
     const int r = e / (K1 / 8), k0 = (e % (K1 / 8)) * 8;
     fq[i] = *(const uint4*)(feat + (row0 + r) * FP + (k0 < FP ? k0 : 0));
   }
+  // the phases' other global operands, loaded ahead of them: this thread's
+  // target, W3 and layer 1's fragments behind the features, layer 2's behind
+  // the first barrier
+  bf16x8 bw1[13], bw2[8], bw2t[8];
+  const int orow = t >> 3, oa = min(t & 7, NO - 1);
+  const float bias1 = params[oB1 + J], bias2 = params[oB2 + J], bias3 = params[oB3 + oa];
+  const float tgt = target[(row0 + orow) * NO + oa];
+  static_assert(NO * NH <= NTB && ROWS * 8 == NTB, "an element of W3 and an eighth of a row per thread");
+  const float w3e = params[oW3 + min(t, NO * NH - 1)];
+  load_frags(w1b, bw1);
   // the same rows of the next step's batch, read now so that they are in
   // this XCD's L2 when that step's workgroup (same block index, same XCD)
   // starts; their registers are consumed only at the end of the kernel
@@ -437,14 +442,14 @@ __global__ __launch_bounds__(NT, 1) void k_forward_backward(const uint16_t* feat
   if (feat_next) {
 #pragma unroll
     for (int i = 0; i < FI; ++i) {
-      const int e = min(t + i * NT, FE - 1);
+      const int e = min(t + i * NTB, FE - 1);
       const int r = e / (K1 / 8), k0 = (e % (K1 / 8)) * 8;
       fnext[i] = *(const uint4*)(feat_next + (row0 + r) * FP + (k0 < FP ? k0 : 0));
     }
   }
 #pragma unroll
   for (int i = 0; i < FI; ++i) {
-    const int e = t + i * NT;
+    const int e = t + i * NTB;
     if (e >= FE) break;
     const int r = e / (K1 / 8), k0 = (e % (K1 / 8)) * 8;
     uint16_t v[8];
@@ -459,12 +464,15 @@ __global__ __launch_bounds__(NT, 1) void k_forward_backward(const uint16_t* feat
     *(uint4*)(sX + r * PX + k0) = make_uint4((uint32_t)v[0] | ((uint32_t)v[1] << 16), (uint32_t)v[2] | ((uint32_t)v[3] << 16),
                                              (uint32_t)v[4] | ((uint32_t)v[5] << 16), (uint32_t)v[6] | ((uint32_t)v[7] << 16));
   }
+  if (t < NO * NH) sW3[t] = w3e;
   __syncthreads();  // sX complete
+  load_frags(w2b, bw2);
+  load_frags(w2bt, bw2t);
   // sXt from sX: item (k, 8 rows from r0) per thread, consecutive threads on
   // consecutive k, so the 2-byte reads of a row are contiguous and the
   // 16-byte writes (row pitch 144 bytes) fall on distinct banks within each
   // quarter-wave; rows k >= K1 are zero
-  for (int i = t; i < 224 * (ROWS / 8); i += NT) {
+  for (int i = t; i < 224 * (ROWS / 8); i += NTB) {
     const int k = i % 224, r0 = (i / 224) * 8;
     uint16_t v[8];
 #pragma unroll
@@ -472,143 +480,171 @@ __global__ __launch_bounds__(NT, 1) void k_forward_backward(const uint16_t* feat
     *(uint4*)(sXt + k * PT + r0) = make_uint4((uint32_t)v[0] | ((uint32_t)v[1] << 16), (uint32_t)v[2] | ((uint32_t)v[3] << 16),
                                               (uint32_t)v[4] | ((uint32_t)v[5] << 16), (uint32_t)v[6] | ((uint32_t)v[7] << 16));
   }
-  for (int e = t; e < NO * NH; e += NT) sW3[e] = params[oW3 + e];
-  bf16x8 bw1[13], bw2[8];
-  load_weight_frags(w1b, w2b, bw1, bw2);
-  const float bias1 = params[oB1 + J], bias2 = params[oB2 + J];
-  __syncthreads();
+  // (layer 1 reads only sX: its barrier completes sXt too)
 
-  f32x16 ds1[2], ds2[2];
+  f32x16 ds1[1], ds2[1];
   forward_hidden(sX, sH1, sH1t, sH2, bw1, bw2, bias1, bias2, ds1, ds2);
 
-  // output layer, loss and dy = 2 (y - target) / (3 batch)
+  // output layer, loss and dy = 2 (y - target) / (3 batch): eight threads a row,
+  // every eighth quad of hidden units each
   float se = 0.f;
-  if (t < ROWS * NO) {
-    const float y = output_layer(sH2, sW3, params + oB3, t);
-    const float d = y - target[(row0 + t / 3) * NO + t % 3];
-    se = d * d;
-    sdy[t] = 2.0f * d / (float)(NO * batch);
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) se += __shfl_xor(se, o);
-  if (lane == 0) sred[wave] = se;
-  __syncthreads();
-  if (t == 0) lpart[blockIdx.x] = (sred[0] + sred[1]) + (sred[2] + sred[3]);
-  // dW3[a][c] = sum_r dy[r][a] h2[r][c]: thread (c, half) sums its half of
-  // the rows for the three a (the halves are added after the barrier);
-  // db3[a] = sum_r dy[r][a]
-  static_assert(NT == 2 * NH, "dW3 split");
   {
-    const int c = t & (NH - 1), r0 = (t / NH) * (ROWS / 2);
+    const int seg = t & 7;
+    const float4* h = (const float4*)(sH2 + orow * PH2);
+    const float4* w = (const float4*)sW3;
+    float y[NO] = {0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < NH / 4; c += 8) {
+      const float4 hc = h[c + seg];
+#pragma unroll
+      for (int a = 0; a < NO; ++a) {
+        const float4 wc = w[a * (NH / 4) + c + seg];
+        y[a] = fmaf(hc.x, wc.x, y[a]);
+        y[a] = fmaf(hc.y, wc.y, y[a]);
+        y[a] = fmaf(hc.z, wc.z, y[a]);
+        y[a] = fmaf(hc.w, wc.w, y[a]);
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < NO; ++a) y[a] = sum8(y[a]);
+    if (seg < NO) {
+      const float d = bias3 + (seg == 0 ? y[0] : seg == 1 ? y[1] : y[2]) - tgt;
+      se = d * d;
+      sdy[orow * 4 + seg] = 2.0f * d / (float)(NO * batch);
+    }
+  }
+  se = sum16(se);
+  if ((lane & 15) == 0) sred[t >> 4] = se;
+  __syncthreads();
+  if (t == 0) {
+    float l = 0.f;
+#pragma unroll
+    for (int w = 0; w < NTB / 16; ++w) l += sred[w];
+    lpart[blockIdx.x] = l;
+  }
+  // dW3[a][c] = sum_r dy[r][a] h2[r][c]: thread (c, quarter) sums its quarter of
+  // the rows for the three a (the quarters are added after the barrier);
+  // db3[a] = sum_r dy[r][a], wave 7 a lane per row
+  static_assert(NTB == 4 * NH, "dW3 split");
+  {
+    const int c = t & (NH - 1), r0 = (t / NH) * (ROWS / 4);
     float g[NO] = {0.f, 0.f, 0.f};
 #pragma unroll 8
-    for (int r = r0; r < r0 + ROWS / 2; ++r) {
+    for (int r = r0; r < r0 + ROWS / 4; ++r) {
       const float h = sH2[r * PH2 + c];
-#pragma unroll
-      for (int a = 0; a < NO; ++a) g[a] = fmaf(sdy[r * NO + a], h, g[a]);
+      const float4 dy = *(const float4*)(sdy + 4 * r);
+      g[0] = fmaf(dy.x, h, g[0]);
+      g[1] = fmaf(dy.y, h, g[1]);
+      g[2] = fmaf(dy.z, h, g[2]);
     }
 #pragma unroll
     for (int a = 0; a < NO; ++a) sdw3[(t / NH) * NO * NH + a * NH + c] = g[a];
   }
-  if (t < NO) {
-    float g = 0.f;
-    for (int r = 0; r < ROWS; ++r) g += sdy[r * NO + t];
-    gp[oB3 + t] = g;
+  if (wave == 7) {
+    static_assert(ROWS == 64, "a lane per row");
+#pragma unroll
+    for (int a = 0; a < NO; ++a) {
+      const int g = __builtin_bit_cast(int, sum16(sdy[lane * 4 + a]));
+      const float q0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(g, 0)),
+                  q1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(g, 16)),
+                  q2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(g, 32)),
+                  q3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(g, 48));
+      if (lane == 0) gp[oB3 + a] = (q0 + q1) + (q2 + q3);
+    }
   }
   __syncthreads();  // every read of h2 is done: R2 now takes dz2
-  for (int o = t; o < NO * NH; o += NT) gp[oW3 + o] = sdw3[o] + sdw3[NO * NH + o];
+  for (int o = t; o < NO * NH; o += NTB)
+    gp[oW3 + o] = (sdw3[o] + sdw3[NO * NH + o]) + (sdw3[2 * NO * NH + o] + sdw3[3 * NO * NH + o]);
 
   // dz2 = (dy W3) * silu'(z2), stored as BF16 row-major and transposed
   {
+    const float w30 = sW3[J], w31 = sW3[NH + J], w32 = sW3[2 * NH + J];
     float db = 0.f;
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
+    for (int v0 = 0; v0 < 16; v0 += 4) {
+      float dz[4];
 #pragma unroll
-      for (int v0 = 0; v0 < 16; v0 += 4) {
-        float dz[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int r = 32 * rt + acc_row(v0 + q, hi);
-          const float dh = sdy[r * NO] * sW3[J] + sdy[r * NO + 1] * sW3[NH + J] + sdy[r * NO + 2] * sW3[2 * NH + J];
-          dz[q] = dh * ds2[rt][v0 + q];
-          db += dz[q];
-        }
-        const uint32_t p01 = pack_bf16(dz[0], dz[1]), p23 = pack_bf16(dz[2], dz[3]);
-        const int r0 = 32 * rt + acc_row(v0, hi);
-        sdZ2[r0 * PH + J] = (uint16_t)p01;
-        sdZ2[(r0 + 1) * PH + J] = (uint16_t)(p01 >> 16);
-        sdZ2[(r0 + 2) * PH + J] = (uint16_t)p23;
-        sdZ2[(r0 + 3) * PH + J] = (uint16_t)(p23 >> 16);
-        *(uint2*)(sdZ2t + J * PT + r0) = make_uint2(p01, p23);
+      for (int q = 0; q < 4; ++q) {
+        const int r = 32 * rt + acc_row(v0 + q, hi);
+        const float4 dy = *(const float4*)(sdy + 4 * r);
+        const float dh = dy.x * w30 + dy.y * w31 + dy.z * w32;
+        dz[q] = dh * ds2[0][v0 + q];
+        db += dz[q];
       }
+      const uint32_t p01 = pack_bf16(dz[0], dz[1]), p23 = pack_bf16(dz[2], dz[3]);
+      const int r0 = 32 * rt + acc_row(v0, hi);
+      sdZ2[r0 * PH + J] = (uint16_t)p01;
+      sdZ2[(r0 + 1) * PH + J] = (uint16_t)(p01 >> 16);
+      sdZ2[(r0 + 2) * PH + J] = (uint16_t)p23;
+      sdZ2[(r0 + 3) * PH + J] = (uint16_t)(p23 >> 16);
+      *(uint2*)(sdZ2t + J * PT + r0) = make_uint2(p01, p23);
+    }
     db += __shfl_xor(db, 32);
-    if (hi == 0) gp[oB2 + J] = db;
+    if (hi == 0) sdb[rt * NH + J] = db;
   }
   __syncthreads();
 
   // dh1 = dz2 W2 (unit J of layer 1), dz1 = dh1 * silu'(z1) -> transposed BF16
   {
-    f32x16 acc[2];
+    f32x16 acc;
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[rt][v] = 0.f;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const bf16x8 b = frag(w2bt, NH, J, 16 * s + 8 * hi);
-#pragma unroll
-      for (int rt = 0; rt < 2; ++rt) acc[rt] = mfma(frag(sdZ2, PH, 32 * rt + r32, 16 * s + 8 * hi), b, acc[rt]);
-    }
+    for (int s = 0; s < 8; ++s)
+      acc = mfma(frag(sdZ2, PH, 32 * rt + r32, 16 * s + 8 * hi), bw2t[s], acc);
     float db = 0.f;
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
+    for (int v0 = 0; v0 < 16; v0 += 4) {
+      float dz[4];
 #pragma unroll
-      for (int v0 = 0; v0 < 16; v0 += 4) {
-        float dz[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          dz[q] = acc[rt][v0 + q] * ds1[rt][v0 + q];
-          db += dz[q];
-        }
-        *(uint2*)(sdZ1t + J * PT + 32 * rt + acc_row(v0, hi)) =
-            make_uint2(pack_bf16(dz[0], dz[1]), pack_bf16(dz[2], dz[3]));
+      for (int q = 0; q < 4; ++q) {
+        dz[q] = acc[v0 + q] * ds1[0][v0 + q];
+        db += dz[q];
       }
+      *(uint2*)(sdZ1t + J * PT + 32 * rt + acc_row(v0, hi)) =
+          make_uint2(pack_bf16(dz[0], dz[1]), pack_bf16(dz[2], dz[3]));
+    }
     db += __shfl_xor(db, 32);
-    if (hi == 0) gp[oB1 + J] = db;
+    if (hi == 0) sdb[(2 + rt) * NH + J] = db;
   }
-  // dW2[i][j] = sum_r dz2[r][i] h1[r][j]: rows i of tile `wave`, 4 column tiles
+  // dW2[i][j] = sum_r dz2[r][i] h1[r][j]: rows i of tile ub, column tiles 2 rt
+  // and 2 rt + 1
   {
-    f32x16 acc[4];
+    f32x16 acc[2];
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
+    for (int q = 0; q < 2; ++q)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[nt][v] = 0.f;
+      for (int v = 0; v < 16; ++v) acc[q][v] = 0.f;
 #pragma unroll
     for (int s = 0; s < ROWS / 16; ++s) {
-      const bf16x8 a = frag(sdZ2t, PT, 32 * wave + r32, 16 * s + 8 * hi);
+      const bf16x8 a = frag(sdZ2t, PT, 32 * ub + r32, 16 * s + 8 * hi);
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt) acc[nt] = mfma(a, frag(sH1t, PT, 32 * nt + r32, 16 * s + 8 * hi), acc[nt]);
+      for (int q = 0; q < 2; ++q) acc[q] = mfma(a, frag(sH1t, PT, 32 * (2 * rt + q) + r32, 16 * s + 8 * hi), acc[q]);
     }
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
+    for (int q = 0; q < 2; ++q)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) gp[oW2 + (32 * wave + acc_row(v, hi)) * NH + 32 * nt + r32] = acc[nt][v];
+      for (int v = 0; v < 16; ++v)
+        gp[oW2 + (32 * ub + acc_row(v, hi)) * NH + 32 * (2 * rt + q) + r32] = acc[q][v];
   }
-  __syncthreads();  // dz1 complete
-  // dW1[i][f] = sum_r dz1[r][i] x[r][f] for f < 195: 7 column tiles in two passes
-#pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
+  __syncthreads();  // dz1 and the bias sums complete
+  if (t < NH)
+    gp[oB2 + t] = sdb[t] + sdb[NH + t];
+  else if (t < 2 * NH)
+    gp[oB1 + t - NH] = sdb[NH + t] + sdb[2 * NH + t];
+  // dW1[i][f] = sum_r dz1[r][i] x[r][f] for f < 195: of the 7 column tiles, the
+  // first four (rt = 0) or the last three
+  {
     constexpr int NTP = 4;
     f32x16 acc[NTP];
 #pragma unroll
     for (int q = 0; q < NTP; ++q)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[q][v] = 0.f;
-    const int nt0 = pass * NTP;
-    const int ntn = pass == 0 ? NTP : 7 - NTP;
+    const int nt0 = rt * NTP, ntn = rt == 0 ? NTP : 7 - NTP;
 #pragma unroll
     for (int s = 0; s < ROWS / 16; ++s) {
-      const bf16x8 a = frag(sdZ1t, PT, 32 * wave + r32, 16 * s + 8 * hi);
+      const bf16x8 a = frag(sdZ1t, PT, 32 * ub + r32, 16 * s + 8 * hi);
 #pragma unroll
       for (int q = 0; q < NTP; ++q)
         if (q < ntn) acc[q] = mfma(a, frag(sXt, PT, 32 * (nt0 + q) + r32, 16 * s + 8 * hi), acc[q]);
@@ -618,7 +654,7 @@ __global__ __launch_bounds__(NT, 1) void k_forward_backward(const uint16_t* feat
       const int fcol = 32 * (nt0 + q) + r32;
       if (q < ntn && fcol < NF)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) gp[oW1 + (32 * wave + acc_row(v, hi)) * NF + fcol] = acc[q][v];
+        for (int v = 0; v < 16; ++v) gp[oW1 + (32 * ub + acc_row(v, hi)) * NF + fcol] = acc[q][v];
     }
   }
   if (feat_next) {
@@ -680,11 +716,11 @@ __global__ __launch_bounds__(NT) void k_update(float* params, float* m, float* v
   }
   const uint16_t b = to_bf16(p);
   if (e < oB1) {
-    w1b[(e / NF) * K1 + e % NF] = b;
+    w1b[frag_index<K1 / 16>(e / NF, e % NF)] = b;
   } else if (e >= oW2 && e < oB2) {
     const int j = (e - oW2) / NH, k = (e - oW2) % NH;
-    w2b[j * NH + k] = b;
-    w2bt[k * NH + j] = b;
+    w2b[frag_index<NH / 16>(j, k)] = b;
+    w2bt[frag_index<NH / 16>(k, j)] = b;
   }
 }
 
@@ -715,7 +751,8 @@ __global__ __launch_bounds__(NT, 2) void k_infer(LearnedField f, const double* X
   if (t < NH) sB2[t] = params[oB2 + t];
   if (t < NO) sB3[t] = params[oB3 + t];
   bf16x8 bw1[13], bw2[8];
-  load_weight_frags(w1b, w2b, bw1, bw2);
+  load_frags(w1b, bw1);
+  load_frags(w2b, bw2);
   const float bias1 = params[oB1 + J];
   f32x16 unused1[2];
   // each block walks a contiguous range of chunks (neighbouring bins, so its
@@ -790,7 +827,7 @@ __global__ __launch_bounds__(NT, 2) void k_infer(LearnedField f, const double* X
       x_n = X[3 * (int64_t)oi_nn + kx];
     }
     __syncthreads();
-    hidden_layer1<false>(sX, sH1, nullptr, bw1, bias1, unused1);
+    hidden_layer1<false, 2>(sX, sH1, nullptr, bw1, bias1, unused1);
     infer_layer2_out(sH1, bw2, sB2, sW3, sY);
     if (t < ROWS * NO) {
       const float* yw = sY + orow * NO + oa;
@@ -855,7 +892,7 @@ hipError_t launch_learned_forward_backward(const uint16_t* feat, const float* ta
                                            const uint16_t* w2bt, float* gpart, float* lpart, hipStream_t s,
                                            const uint16_t* feat_next) {
   if (batch <= 0 || batch % ROWS) return hipErrorInvalidValue;
-  k_forward_backward<<<(unsigned)(batch / ROWS), NT, 0, s>>>(feat, target, batch, params, w1b, w2b, w2bt, gpart,
+  k_forward_backward<<<(unsigned)(batch / ROWS), NTB, 0, s>>>(feat, target, batch, params, w1b, w2b, w2bt, gpart,
                                                              lpart, feat_next);
   return hipGetLastError();
 }
