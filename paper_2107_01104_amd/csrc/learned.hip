@@ -198,81 +198,48 @@ __global__ __launch_bounds__(NT) void k_pairs(LearnedField f, const double* X, i
 }
 
 // ---------------------------------------------------------------- forward
-// Hidden layer 1 for the 64 rows whose features are in sX: h1 (BF16) in sH1
-// (and its transpose in sH1t if given), the pre-activations' derivatives
-// (training) in ds1.  Ends with the barrier after which h1 is complete and sX
-// is dead.
-// A wave takes RT of the two 32-row tiles from tile rt0 on (inference: both;
-// training's eight waves: one each).
-template <bool TRAIN, int RT>
-__device__ __forceinline__ void hidden_layer1(const uint16_t* sX, uint16_t* sH1, uint16_t* sH1t,
-                                              const bf16x8 (&bw1)[13], float bias1, f32x16 (&ds1)[RT], int rt0 = 0) {
-  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3;
-  const int r32 = lane & 31, hi = lane >> 5;
-  const int J = 32 * wave + r32;
-  sX += 32 * rt0 * PX;
-  f32x16 acc[RT];
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[rt][v] = 0.f;
-  // the A fragments of step s + 1 are read while step s's products run; in
-  // inference an empty asm with a memory clobber ends every step, so the
-  // compiler reads no further ahead (holding all 26 fragments would take 104
-  // registers that inference spends on the next chunk's stencil loads)
-  bf16x8 an[RT];
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt) an[rt] = frag(sX, PX, 32 * rt + r32, 8 * hi);
-#pragma unroll
-  for (int s = 0; s < 13; ++s) {
-    bf16x8 a[RT];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) a[rt] = an[rt];
-    if (s + 1 < 13) {
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) an[rt] = frag(sX, PX, 32 * rt + r32, 16 * (s + 1) + 8 * hi);
-    }
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) acc[rt] = mfma(a[rt], bw1[s], acc[rt]);
-    if constexpr (!TRAIN) asm volatile("" ::: "memory");
-  }
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-    for (int v0 = 0; v0 < 16; v0 += 4) {
-      float h[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float z = acc[rt][v0 + q] + bias1;
-        h[q] = silu(z);
-        if constexpr (TRAIN) ds1[rt][v0 + q] = dsilu(z);
-      }
-      const uint32_t p01 = pack_bf16(h[0], h[1]), p23 = pack_bf16(h[2], h[3]);
-      const int r0 = 32 * (rt0 + rt) + acc_row(v0, hi);
-      sH1[r0 * PH + J] = (uint16_t)p01;
-      sH1[(r0 + 1) * PH + J] = (uint16_t)(p01 >> 16);
-      sH1[(r0 + 2) * PH + J] = (uint16_t)p23;
-      sH1[(r0 + 3) * PH + J] = (uint16_t)(p23 >> 16);
-      if (sH1t) *(uint2*)(sH1t + J * PT + r0) = make_uint2(p01, p23);
-    }
-  __syncthreads();  // h1 complete; sX is dead from here on
-}
-
-// Training's forward pass: layer 1 as above, then h2 (FP32) in sH2 and its
-// pre-activations' derivatives in ds2 (the backward pass reads h2 by rows);
-// wave w takes hidden units 32 (w % 4) .. and rows 32 (w / 4) ..  sX and sH2 may
-// alias.
+// Training's forward pass for the 64 rows whose features are in sX; wave w takes
+// hidden units 32 (w % 4) .. and rows 32 (w / 4) ..: h1 (BF16) in sH1 and its
+// transpose in sH1t, h2 (FP32) in sH2 (the backward pass reads it by rows), the
+// pre-activations' derivatives in ds1 and ds2.  sX and sH2 may alias.
 __device__ __forceinline__ void forward_hidden(const uint16_t* sX, uint16_t* sH1, uint16_t* sH1t, float* sH2,
                                                const bf16x8 (&bw1)[13], const bf16x8 (&bw2)[8], float bias1,
-                                               float bias2, f32x16 (&ds1)[1], f32x16 (&ds2)[1]) {
+                                               float bias2, f32x16& ds1, f32x16& ds2) {
   const int lane = threadIdx.x & 63, ub = (threadIdx.x >> 6) & 3, rt = threadIdx.x >> 8;
-  hidden_layer1<true, 1>(sX, sH1, sH1t, bw1, bias1, ds1, rt);
   const int r32 = lane & 31, hi = lane >> 5;
   const int J = 32 * ub + r32;
   f32x16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-  bf16x8 an = frag(sH1, PH, 32 * rt + r32, 8 * hi);
+  // (the A fragment of step s + 1 is read while step s's product runs)
+  bf16x8 an = frag(sX, PX, 32 * rt + r32, 8 * hi);
+#pragma unroll
+  for (int s = 0; s < 13; ++s) {
+    const bf16x8 a = an;
+    if (s + 1 < 13) an = frag(sX, PX, 32 * rt + r32, 16 * (s + 1) + 8 * hi);
+    acc = mfma(a, bw1[s], acc);
+  }
+#pragma unroll
+  for (int v0 = 0; v0 < 16; v0 += 4) {
+    float h[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float z = acc[v0 + q] + bias1;
+      h[q] = silu(z);
+      ds1[v0 + q] = dsilu(z);
+    }
+    const uint32_t p01 = pack_bf16(h[0], h[1]), p23 = pack_bf16(h[2], h[3]);
+    const int r0 = 32 * rt + acc_row(v0, hi);
+    sH1[r0 * PH + J] = (uint16_t)p01;
+    sH1[(r0 + 1) * PH + J] = (uint16_t)(p01 >> 16);
+    sH1[(r0 + 2) * PH + J] = (uint16_t)p23;
+    sH1[(r0 + 3) * PH + J] = (uint16_t)(p23 >> 16);
+    *(uint2*)(sH1t + J * PT + r0) = make_uint2(p01, p23);
+  }
+  __syncthreads();  // h1 complete; sX is dead from here on
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  an = frag(sH1, PH, 32 * rt + r32, 8 * hi);
 #pragma unroll
   for (int s = 0; s < 8; ++s) {
     const bf16x8 a = an;
@@ -283,77 +250,9 @@ __device__ __forceinline__ void forward_hidden(const uint16_t* sX, uint16_t* sH1
   for (int v = 0; v < 16; ++v) {
     const float z = acc[v] + bias2;
     sH2[(32 * rt + acc_row(v, hi)) * PH2 + J] = silu(z);
-    ds2[0][v] = dsilu(z);
+    ds2[v] = dsilu(z);
   }
   __syncthreads();  // h2 complete
-}
-
-// Inference: hidden layer 2 with the operands swapped (W2 rows as the A tile,
-// h1 rows as the B tile), so that lane l holds particle 32 rt + l % 32 and,
-// in register v, the wave's hidden unit 32 wave + acc_row(v, l / 32); then
-// the output layer straight from those registers.  Each lane adds its 16
-// units' h2 W3 products, the wave's two lane halves add theirs (lane l ^ 32
-// holds the other 16 units of the same particles), and lanes l < 32 leave the
-// wave's sums in sY[wave][row][a].  Ends with the barrier after which sY is
-// complete.  Training keeps the FP32 h2 tile (forward_hidden): its backward
-// pass reads h2 by rows.
-__device__ __forceinline__ void infer_layer2_out(const uint16_t* sH1, const bf16x8 (&bw2)[8], const float* sB2,
-                                                 const float* sW3, float* sY) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r32 = lane & 31, hi = lane >> 5;
-  f32x16 acc[2];
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[rt][v] = 0.f;
-  bf16x8 bn[2];
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt) bn[rt] = frag(sH1, PH, 32 * rt + r32, 8 * hi);
-#pragma unroll
-  for (int s = 0; s < 8; ++s) {
-    const bf16x8 b0 = bn[0], b1 = bn[1];
-    if (s + 1 < 8) {
-#pragma unroll
-      for (int rt = 0; rt < 2; ++rt) bn[rt] = frag(sH1, PH, 32 * rt + r32, 16 * (s + 1) + 8 * hi);
-    }
-    acc[0] = mfma(bw2[s], b0, acc[0]);
-    acc[1] = mfma(bw2[s], b1, acc[1]);
-    asm volatile("" ::: "memory");
-  }
-  float y[2][NO];
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-    for (int a = 0; a < NO; ++a) y[rt][a] = 0.f;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    // registers 4k .. 4k+3 hold units u0 .. u0+3
-    const int u0 = 32 * wave + 8 * k + 4 * hi;
-    const float4 b = *(const float4*)(sB2 + u0);
-    const float4 w0 = *(const float4*)(sW3 + u0), w1 = *(const float4*)(sW3 + NH + u0),
-                 w2 = *(const float4*)(sW3 + 2 * NH + u0);
-    const float bb[4] = {b.x, b.y, b.z, b.w};
-    const float ww[NO][4] = {{w0.x, w0.y, w0.z, w0.w}, {w1.x, w1.y, w1.z, w1.w}, {w2.x, w2.y, w2.z, w2.w}};
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float h = silu(acc[rt][4 * k + q] + bb[q]);
-#pragma unroll
-        for (int a = 0; a < NO; ++a) y[rt][a] = fmaf(h, ww[a][q], y[rt][a]);
-      }
-  }
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-    for (int a = 0; a < NO; ++a) y[rt][a] += __shfl_xor(y[rt][a], 32);
-  if (hi == 0) {
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-      for (int a = 0; a < NO; ++a) sY[(wave * ROWS + 32 * rt + r32) * NO + a] = y[rt][a];
-  }
-  __syncthreads();  // every wave's sums are in sY
 }
 
 // The BF16 weight copies are kept in the order the fragments are loaded: element
@@ -485,7 +384,7 @@ __global__ __launch_bounds__(NTB, 2) void k_forward_backward(const uint16_t* fea
   }
   // (layer 1 reads only sX: its barrier completes sXt too)
 
-  f32x16 ds1[1], ds2[1];
+  f32x16 ds1, ds2;
   forward_hidden(sX, sH1, sH1t, sH2, bw1, bw2, bias1, bias2, ds1, ds2);
 
   // output layer, loss and dy = 2 (y - target) / (3 batch): eight threads a row,
@@ -571,7 +470,7 @@ __global__ __launch_bounds__(NTB, 2) void k_forward_backward(const uint16_t* fea
         const int r = 32 * rt + acc_row(v0 + q, hi);
         const float4 dy = *(const float4*)(sdy + 4 * r);
         const float dh = dy.x * w30 + dy.y * w31 + dy.z * w32;
-        dz[q] = dh * ds2[0][v0 + q];
+        dz[q] = dh * ds2[v0 + q];
         db += dz[q];
       }
       const uint32_t p01 = pack_bf16(dz[0], dz[1]), p23 = pack_bf16(dz[2], dz[3]);
@@ -601,7 +500,7 @@ __global__ __launch_bounds__(NTB, 2) void k_forward_backward(const uint16_t* fea
       float dz[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        dz[q] = acc[v0 + q] * ds1[0][v0 + q];
+        dz[q] = acc[v0 + q] * ds1[v0 + q];
         db += dz[q];
       }
       *(uint2*)(sdZ1t + J * PT + 32 * rt + acc_row(v0, hi)) =
@@ -728,116 +627,252 @@ __global__ __launch_bounds__(NT) void k_update(float* params, float* m, float* v
 }
 
 // ---------------------------------------------------------------- inference
-// Particles in bin order (the k-th is the caller's orig[k]; orig is required),
-// 64 per chunk;
-// every workgroup keeps its layer weights in registers and walks a range of
-// chunks.  The loads run a chunk ahead of their use along the chain row
-// index -> coordinate -> stencil: while chunk ch's two layers run, chunk
-// ch + 1's stencil rows, chunk ch + 2's coordinates and chunk ch + 3's row
-// indices are in flight.
-__global__ __launch_bounds__(NT, 2) void k_infer(LearnedField f, const double* X, int64_t n, const uint32_t* orig,
-                                                 const float* params, const uint16_t* w1b, const uint16_t* w2b,
-                                                 float* out, int* flag) {
-  constexpr int RX = ROWS * PX * 2;  // features
-  __shared__ __attribute__((aligned(16))) unsigned char lds[RX + ROWS * PH * 2];
-  __shared__ __attribute__((aligned(16))) float sW3[NO * NH];
-  __shared__ __attribute__((aligned(16))) float sB2[NH];
-  __shared__ float sY[4 * ROWS * NO];  // the 4 waves' output-layer sums
-  __shared__ float sU[ROWS * NO];
-  __shared__ float sB3[NO];
-  uint16_t* sX = (uint16_t*)lds;
-  uint16_t* sH1 = (uint16_t*)(lds + RX);
-  const int t = threadIdx.x;
-  const int lane = t & 63, wave = t >> 6;
-  const int J = 32 * wave + (lane & 31);
-  for (int e = t; e < NO * NH; e += NT) sW3[e] = params[oW3 + e];
-  if (t < NH) sB2[t] = params[oB2 + t];
-  if (t < NO) sB3[t] = params[oB3 + t];
-  bf16x8 bw1[13], bw2[8];
-  load_frags(w1b, bw1);
-  load_frags(w2b, bw2);
-  const float bias1 = params[oB1 + J];
-  f32x16 unused1[2];
-  // each block walks a contiguous range of chunks (neighbouring bins, so its
-  // stencil reads stay in L2 and in the translation caches); consecutive
-  // blocks go round-robin to the 8 XCDs, so XCD x is given a contiguous range
-  const int64_t nchunks = (n + ROWS - 1) / ROWS;
+// Particles in bin order (the k-th is the caller's orig[k]; orig is required).
+// A wave takes 32 particles through the whole network by itself: two lanes per
+// particle, lane l = particle l % 32 with the rows 2 (l / 32) and 2 (l / 32) + 1
+// of its stencil's planes.  With the weights as the matrix instructions' A
+// tile and the particles as B, a lane's 96 stencil values are its B fragments
+// of layer 1 as they come from memory, and the hidden units that the result
+// leaves in a lane are its B fragments of layer 2: the inputs of both layers
+// are summed in the order that this distribution gives (layer1_piece,
+// layer2_piece), and no value of a particle leaves its two lanes but the final
+// sums.  So the waves need no barriers and share only the weights, in LDS.
+// The stencil rows come in coalesced 16-byte pieces and change lanes through the
+// wave's own LDS.  12.5e6 particles on 512^3 in the caller's order: 2.79 ms with
+// two lanes reading their own rows (a cache access per lane: the address units
+// busy 66%), 2.48 so; four waves staging 64 particles through LDS, the weights
+// in registers, 2.75.  Without its gather it takes 1.7 ms; the SiLUs (two
+// transcendentals each) and the matrix instructions are not what bounds it, and
+// neither more waves (12: 2.60) nor the next chunk's stencil in flight (256
+// registers, 2.61) help: the vector, address and LDS pipes are each about half
+// busy.
+constexpr int INF_WAVES = 8, INF_PART = 32;
+
+// 16-byte piece (unit tile ub, step s, lane) of a layer's A fragments <- pieces
+// of the fragment-order copies (frag_index).  Layer 1: input 16 s + 8 hi + e
+// stands for feature 48 (s / 3) + 24 hi + 8 (s % 3) + e (s < 12), step 12 for
+// features 192 + 8 hi + e.
+__device__ __forceinline__ uint4 layer1_piece(const uint4* w1b, int ub, int s, int lane) {
+  const int f = s < 12 ? 48 * (s / 3) + 24 * (lane >> 5) + 8 * (s % 3) : 192 + 8 * (lane >> 5);
+  return w1b[(ub * (K1 / 16) + (f >> 4)) * 64 + ((f >> 3) & 1) * 32 + (lane & 31)];
+}
+// Layer 2: the step's inputs e of half hi are the units in registers
+// 8 (s % 2) + e of layer 1's tile s / 2: 16 s + 8 (e / 4) + 4 hi + e % 4.
+__device__ __forceinline__ uint4 layer2_piece(const uint2* w2b, int ub, int s, int lane) {
+  const int hi = lane >> 5, r = lane & 31, base = (ub * (NH / 16) + s) * 64;
+  const uint2 a = w2b[2 * (base + r) + hi], b = w2b[2 * (base + 32 + r) + hi];
+  return make_uint4(a.x, a.y, b.x, b.y);
+}
+
+__global__ __launch_bounds__(64 * INF_WAVES, INF_WAVES / 4) void k_infer(LearnedField f, const double* X, int64_t n,
+                                                                         const uint32_t* orig, const float* params,
+                                                                         const uint16_t* w1b, const uint16_t* w2b,
+                                                                         float* out, int* flag) {
+  constexpr int S1 = K1 / 16, S2 = NH / 16;
+  __shared__ uint4 sW1[4 * S1 * 64], sW2[4 * S2 * 64];
+  __shared__ __attribute__((aligned(16))) float sB1[NH], sB2[NH], sW3[NO * NH];
+  __shared__ float4 sQ[INF_WAVES][4 * 3 * INF_PART];  // a wave's stencil plane: [row][particle][16-byte piece]
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, hi = lane >> 5;
+  for (int e = t; e < 4 * S1 * 64; e += 64 * INF_WAVES)
+    sW1[e] = layer1_piece((const uint4*)w1b, e / (S1 * 64), e / 64 % S1, e & 63);
+  for (int e = t; e < 4 * S2 * 64; e += 64 * INF_WAVES)
+    sW2[e] = layer2_piece((const uint2*)w2b, e / (S2 * 64), e / 64 % S2, e & 63);
+  if (t < NH) {
+    sB1[t] = params[oB1 + t];
+    sB2[t] = params[oB2 + t];
+  }
+  if (t < NO * NH) sW3[t] = params[oW3 + t];
+  const float b3[NO] = {params[oB3], params[oB3 + 1], params[oB3 + 2]};
+  __syncthreads();
+
+  // each workgroup walks a contiguous range of chunks (neighbouring bins, so its
+  // stencil reads stay in L2 and in the translation caches), a chunk per wave in
+  // turn; consecutive workgroups go round-robin to the 8 XCDs, so XCD x is given
+  // a contiguous range
+  const int64_t nchunks = (n + INF_PART - 1) / INF_PART;
   const int64_t per_xcd = gridDim.x / 8;
   const int64_t bid = (int64_t)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   const int64_t per_block = (nchunks + gridDim.x - 1) / gridDim.x;
   const int64_t ch_end = min(nchunks, (bid + 1) * per_block);
-  const int64_t ch0 = bid * per_block;
-  const int kx = (t & 3) < 3 ? (t & 3) : 2;  // the coordinate this thread loads
-  // row of X of this thread's particle in chunk ch
-  // caller row of bin-ordered particle p (clamped to the last particle;
-  // unconditional, so no branch merge waits for the load)
-  auto xrow_of = [&](int64_t p) -> uint32_t { return orig[min(p, n - 1)]; };
-  auto xrow = [&](int64_t ch) -> uint32_t { return xrow_of(ch * ROWS + (t >> 2)); };
-  // At the top of chunk ch: its stencil rows q (with their offsets td and
-  // domain check ok), loaded during chunk ch - 1, and chunk ch + 1's
-  // coordinate x_n.  Each load's result is consumed before the register is
-  // loaded again, and every wait finds the loads it needs issued before the
-  // ones still in flight (the counter retires loads in order).
-  const int pi = t >> 2, k3 = t & 3;
-  float4 q[4][3];
-  double td[3];
-  bool ok = true;
-  double x_n = 0.0;
-  if (ch0 < ch_end) {
-    const double x_c = X[3 * (int64_t)xrow(ch0) + kx];
-    const uint32_t oi = xrow(min(ch0 + 1, ch_end - 1));
+  // row indices two chunks ahead, coordinates one chunk ahead (clamped to the
+  // last particle; unconditional, so no branch merge waits for them)
+  auto row_of = [&](int64_t ch) -> uint32_t { return orig[min(ch * INF_PART + (lane & 31), n - 1)]; };
+  int64_t ch = bid * per_block + wave;
+  if (ch >= ch_end) return;
+  uint32_t row = row_of(ch), row_n = row_of(ch + INF_WAVES);
+  double x[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) x[d] = X[3 * (int64_t)row + d];
+  for (; ch < ch_end; ch += INF_WAVES) {
+    const int64_t p = ch * INF_PART + (lane & 31);
+    const uint32_t dst = row;
     int c[3];
-    ok = locate_quad_x(x_c, k3, f.N, f.invd, c, td);
-    stencil_issue(f, c, k3, q);
-    x_n = X[3 * (int64_t)oi + kx];
-  }
-  // output thread t < 192 writes component t % 3 of the chunk's particle t / 3
-  const int orow = min(t / 3, ROWS - 1), oa = t % 3;
-  for (int64_t ch = ch0; ch < ch_end; ++ch) {
-    // the caller's row of this thread's output, and chunk ch + 2's rows of X
-    const uint32_t o_dst = xrow_of(ch * ROWS + orow);
-    const uint32_t oi_nn = xrow(min(ch + 2, ch_end - 1));
-    const bool active = ch * ROWS + pi < n;
-    if (active && !ok) raise_flag(flag, kFlagDomain);
-    uint32_t fe[24];
-    float u[3];
-    stencil_sums(f, td, k3, q, fe, u);
+    float td[3];
+    const bool ok = in_domain3(x[0], x[1], x[2]);
 #pragma unroll
-    for (int a = 0; a < 3; ++a) u[a] = quad_sum(u[a]);
-    uint16_t* row = sX + pi * PX;
-#pragma unroll
-    for (int e = 0; e < 12; ++e) *(uint2*)(row + 48 * k3 + 4 * e) = make_uint2(fe[2 * e], fe[2 * e + 1]);
-    if (k3 == 0) {
-      *(uint32_t*)(row + 192) = pack_bf16((float)td[0], (float)td[1]);
-      row[194] = to_bf16((float)td[2]);
-      sU[pi * NO] = u[0];
-      sU[pi * NO + 1] = u[1];
-      sU[pi * NO + 2] = u[2];
-    } else if (k3 == 1) {
-#pragma unroll
-      for (int k = NF; k < PX; ++k) row[k] = 0;
+    for (int d = 0; d < 3; ++d) {
+      double tt;
+      locate(x[d], f.N, f.invd, &c[d], &tt);
+      td[d] = (float)tt;
     }
-    // the next chunk: locate its particles and put its stencil loads in
-    // flight (clamped to the last chunk: the loads are unconditional, so no
-    // path waits for them early); then the coordinates of the chunk after it.
-    // The empty asm keeps these loads below the use of this chunk's rows, so
-    // the two sets of rows are never held at once.
-    asm volatile("" ::: "memory");
+    if (!ok && p < n) raise_flag(flag, kFlagDomain);
+    // the chunk's stencil rows, 48 bytes each, in 16-byte pieces: consecutive
+    // lanes take consecutive pieces (row pair by row pair, particle by particle),
+    // so a row is one or two cache lines to the memory pipeline and not three
+    // lanes' accesses each on its own
+    const int64_t own = (int64_t)(c[2] - 1 + f.halo_lo) * f.plane_pitch + (int64_t)(c[1] - 1 + f.halo_lo) * f.row_pitch +
+                        12 * (c[0] - 1 + f.halo_lo);
+    float4 q[4][2][3];
     {
-      int c[3];
-      ok = locate_quad_x(x_n, k3, f.N, f.invd, c, td);
-      stencil_issue(f, c, k3, q);
-      x_n = X[3 * (int64_t)oi_nn + kx];
+      const unsigned char* at[3];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const int j = 64 * i + lane, pj = j % 96 / 3;
+        const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)own, pj), up = (uint32_t)__shfl((int)(own >> 32), pj);
+        at[i] = (const unsigned char*)f.field + (((int64_t)up << 32) | lo) + j / 96 * f.row_pitch + 16 * (j % 3);
+      }
+#pragma unroll
+      for (int k3 = 0; k3 < 4; ++k3)
+#pragma unroll
+        for (int pr = 0; pr < 2; ++pr)
+#pragma unroll
+          for (int i = 0; i < 3; ++i) {
+            const f32x4a v = *(const f32x4a*)(at[i] + k3 * f.plane_pitch + 2 * pr * f.row_pitch);
+            q[k3][pr][i] = make_float4(v.x, v.y, v.z, v.w);
+          }
     }
-    __syncthreads();
-    hidden_layer1<false, 2>(sX, sH1, nullptr, bw1, bias1, unused1);
-    infer_layer2_out(sH1, bw2, sB2, sW3, sY);
-    if (t < ROWS * NO) {
-      const float* yw = sY + orow * NO + oa;
-      const float y = sB3[oa] + ((yw[0] + yw[ROWS * NO]) + (yw[2 * ROWS * NO] + yw[3 * ROWS * NO]));
-      if (ch * ROWS + orow < n) out[3 * (int64_t)o_dst + oa] = sU[orow * NO + oa] + y;
+    // the next chunk's coordinates and the rows after them
+    row = row_n;
+    row_n = row_of(ch + 2 * INF_WAVES);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) x[d] = X[3 * (int64_t)row + d];
+    // the I = 4 Lagrange sum over this lane's planes
+    float w[3][4];
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float acc = f.l4[j][3];
+#pragma unroll
+        for (int e = 2; e >= 0; --e) acc = fmaf(acc, td[d], f.l4[j][e]);
+        w[d][j] = acc;
+      }
+    float u[3] = {0.f, 0.f, 0.f};
+    bf16x8 b[S1];
+    {
+      uint32_t fe[48];
+#pragma unroll
+      for (int k3 = 0; k3 < 4; ++k3) {
+        // the plane through the wave's LDS (its own instructions are in order):
+        // this lane's rows are 2 hi and 2 hi + 1 of its particle.  Rows are 48
+        // bytes from particle to particle: 16 lanes read 16 different slots.
+        float4* sq = sQ[wave];
+#pragma unroll
+        for (int pr = 0; pr < 2; ++pr)
+#pragma unroll
+          for (int i = 0; i < 3; ++i) sq[192 * pr + 64 * i + lane] = q[k3][pr][i];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        float4 g[2][3];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int e = 0; e < 3; ++e) g[i][e] = sq[96 * (2 * hi + i) + 3 * (lane & 31) + e];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const float4 q0 = g[i][0], q1 = g[i][1], q2 = g[i][2];
+          const float v[12] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w, q2.x, q2.y, q2.z, q2.w};
+          const float w23 = w[2][k3] * (hi ? w[1][2 + i] : w[1][i]);
+#pragma unroll
+          for (int k1 = 0; k1 < 4; ++k1) {
+            const float ww = w23 * w[0][k1];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) u[a] = fmaf(ww, v[3 * k1 + a], u[a]);
+          }
+#pragma unroll
+          for (int e = 0; e < 6; ++e) fe[12 * k3 + 6 * i + e] = pack_bf16(v[2 * e], v[2 * e + 1]);
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < 12; ++s)
+        b[s] = __builtin_bit_cast(bf16x8, make_uint4(fe[4 * s], fe[4 * s + 1], fe[4 * s + 2], fe[4 * s + 3]));
+      const uint32_t t01 = pack_bf16(td[0], td[1]), t2 = (uint32_t)to_bf16(td[2]);
+      b[12] = __builtin_bit_cast(bf16x8, make_uint4(hi ? 0u : t01, hi ? 0u : t2, 0u, 0u));
     }
-    __syncthreads();  // sY and sU are read before the next chunk overwrites them
+    // layer 1, two unit tiles at a time; registers v of the result are units
+    // 8 (v / 4) + 4 hi + v % 4 of their tile
+    bf16x8 h1[S2];
+#pragma unroll
+    for (int ub = 0; ub < 4; ub += 2) {
+      f32x16 acc[2];
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[r][v] = 0.f;
+#pragma unroll
+      for (int s = 0; s < S1; ++s)
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+          acc[r] = mfma(__builtin_bit_cast(bf16x8, sW1[((ub + r) * S1 + s) * 64 + lane]), b[s], acc[r]);
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        uint32_t h[8];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float4 bb = *(const float4*)(sB1 + 32 * (ub + r) + 8 * k + 4 * hi);
+          h[2 * k] = pack_bf16(silu(acc[r][4 * k] + bb.x), silu(acc[r][4 * k + 1] + bb.y));
+          h[2 * k + 1] = pack_bf16(silu(acc[r][4 * k + 2] + bb.z), silu(acc[r][4 * k + 3] + bb.w));
+        }
+        h1[2 * (ub + r)] = __builtin_bit_cast(bf16x8, make_uint4(h[0], h[1], h[2], h[3]));
+        h1[2 * (ub + r) + 1] = __builtin_bit_cast(bf16x8, make_uint4(h[4], h[5], h[6], h[7]));
+      }
+    }
+    // layer 2 and the output layer's sums over this lane's units
+    float y[NO] = {0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ub = 0; ub < 4; ub += 2) {
+      f32x16 acc[2];
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[r][v] = 0.f;
+#pragma unroll
+      for (int s = 0; s < S2; ++s)
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+          acc[r] = mfma(__builtin_bit_cast(bf16x8, sW2[((ub + r) * S2 + s) * 64 + lane]), h1[s], acc[r]);
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int u0 = 32 * (ub + r) + 8 * k + 4 * hi;
+          const float4 bb = *(const float4*)(sB2 + u0);
+          const float hh[4] = {silu(acc[r][4 * k] + bb.x), silu(acc[r][4 * k + 1] + bb.y),
+                               silu(acc[r][4 * k + 2] + bb.z), silu(acc[r][4 * k + 3] + bb.w)};
+#pragma unroll
+          for (int a = 0; a < NO; ++a) {
+            const float4 ww = *(const float4*)(sW3 + a * NH + u0);
+            y[a] = fmaf(hh[0], ww.x, y[a]);
+            y[a] = fmaf(hh[1], ww.y, y[a]);
+            y[a] = fmaf(hh[2], ww.z, y[a]);
+            y[a] = fmaf(hh[3], ww.w, y[a]);
+          }
+        }
+    }
+    float r[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const float uu = u[a] + __shfl_xor(u[a], 32), yy = y[a] + __shfl_xor(y[a], 32);
+      r[a] = uu + (b3[a] + yy);
+    }
+    if (hi == 0 && p < n) {
+      float* o = out + 3 * (int64_t)dst;
+      o[0] = r[0];
+      o[1] = r[1];
+      o[2] = r[2];
+    }
   }
 }
 
@@ -913,9 +948,11 @@ hipError_t launch_learned_infer(const LearnedField& f, const double* X, int64_t 
                                 int* flag, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   if (!orig) return hipErrorInvalidValue;  // the kernel reads every particle's row through it
-  const int64_t nchunks = (n + ROWS - 1) / ROWS;
-  const int64_t grid = min((nchunks + 7) / 8 * 8, (int64_t)256 * 2 * 4);  // a multiple of the 8 XCDs
-  k_infer<<<(unsigned)grid, NT, 0, s>>>(f, X, n, orig, params, w1b, w2b, out, flag);
+  const int64_t nchunks = (n + INF_PART - 1) / INF_PART;
+  // one workgroup a CU (the weights fill more than half of its LDS), a multiple
+  // of the 8 XCDs
+  const int64_t grid = min((nchunks + 7) / 8 * 8, (int64_t)256);
+  k_infer<<<(unsigned)grid, 64 * INF_WAVES, 0, s>>>(f, X, n, orig, params, w1b, w2b, out, flag);
   return hipGetLastError();
 }
 
