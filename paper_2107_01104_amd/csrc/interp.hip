@@ -291,9 +291,13 @@ __device__ __forceinline__ void particle_sums(const unsigned char* smem, const f
       s[1] = um.y - uc.y;
       s[2] = um.z - uc.z;
     }
-    // rows read together before use: four for values, two for gradients
-    // (four would pass the 128-VGPR budget of two workgroups per CU and spill)
-    constexpr int G = GRAD ? 2 : (I % 4 == 0 ? 4 : 2);
+    // rows read together before use.  FP32 and 16-bit: four for values, two
+    // for gradients (four would pass the 128-VGPR budget of two workgroups per
+    // CU and spill).  FP64 has 256 VGPRs and only two waves per SIMD to hide a
+    // read's latency with, so all rows of a plane: 512^3, 1.25e7 particles,
+    // I = 8: gradients 5.30 ms (two rows: 5.59), values 4.01 (four: 4.11);
+    // 256^3, 1e7 particles: 3.33 (3.59), 2.29 (2.37); I = 6 values 3.20 (3.36)
+    constexpr int G = ST == ST_F64 ? I : GRAD ? 2 : (I % 4 == 0 ? 4 : 2);
 #pragma unroll
     for (int g = 0; g < I; g += G) {
       V v[G][3];
