@@ -220,8 +220,7 @@ int ptk_interpolate_gradient(ptk_ctx *ctx, const double *X, int64_t Np, void *u_
 /* Interpolation for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid allocation):
  * the same computation, kernels and results as ptk_interpolate, with every
- * scratch buffer (sort keys and values, histograms, scan partials, bin
- * offsets) carved out of a fixed 32 MiB array in the library's own code object
+ * scratch buffer (sort keys and values, histograms, bin offsets) carved out of a fixed 32 MiB array in the library's own code object
  * instead of the context's growable scratch.  The call allocates and frees
  * nothing; the caller passes X and out as for ptk_interpolate (the field must
  * have been set before).  Limit: the scratch of Np particles on the field's

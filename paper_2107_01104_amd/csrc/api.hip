@@ -234,8 +234,6 @@ int ensure_binning(ptk_ctx* c, int64_t Np, int64_t n_bins) {
   PTK_TRY(ensure(c, c->vals_b, n4));
   const size_t hw = sort_hist_words(Np);
   PTK_TRY(ensure(c, c->hist, hw * 4));
-  const int64_t scan_max = (int64_t)hw > n_bins + 1 ? (int64_t)hw : n_bins + 1;
-  PTK_TRY(ensure(c, c->scan_tmp, scan_tmp_words(scan_max) * 4));
   PTK_TRY(ensure(c, c->offsets, (size_t)(n_bins + 1) * 4));
   return PTK_OK;
 }
@@ -263,8 +261,6 @@ int check_binning_caps(ptk_ctx* c, int64_t Np, int64_t n_bins) {
   PTK_TRY(need(c, c->vals_b, n4, "sort values"));
   const size_t hw = sort_hist_words(Np);
   PTK_TRY(need(c, c->hist, hw * 4, "sort histograms"));
-  const int64_t scan_max = (int64_t)hw > n_bins + 1 ? (int64_t)hw : n_bins + 1;
-  PTK_TRY(need(c, c->scan_tmp, scan_tmp_words(scan_max) * 4, "scan partials"));
   PTK_TRY(need(c, c->offsets, (size_t)(n_bins + 1) * 4, "bin offsets"));
   return PTK_OK;
 }
@@ -280,15 +276,16 @@ int check_rebin_caps(ptk_ctx* c, int64_t Np, int64_t n_bins) {
   return PTK_OK;
 }
 
-// keys -> stable sort -> offsets.  keys of the particles must be in keys_a.
+// keys -> stable sort -> offsets.  keys of the particles must be in keys_a,
+// with have_hist also their first digit's histogram in hist.
 // *skeys (optional) receives the sorted keys' location.
-int bin_sorted(ptk_ctx* c, int64_t Np, int64_t n_bins, uint32_t** perm, hipStream_t s,
+int bin_sorted(ptk_ctx* c, int64_t Np, int64_t n_bins, bool have_hist, uint32_t** perm, hipStream_t s,
                uint32_t** skeys = nullptr, uint32_t* off_out = nullptr) {
   uint32_t* sk = nullptr;
   PTK_HIP(c,
           radix_sort_keys((uint32_t*)c->keys_a.ptr, (uint32_t*)c->keys_b.ptr, (uint32_t*)c->vals_a.ptr,
                           (uint32_t*)c->vals_b.ptr, Np, nullptr, false, bits_for(n_bins), (uint32_t*)c->hist.ptr,
-                          (uint32_t*)c->scan_tmp.ptr, &sk, perm, s),
+                          have_hist, &sk, perm, s),
           "radix sort");
   PTK_HIP(c, launch_offsets(sk, Np, n_bins, off_out ? off_out : (uint32_t*)c->offsets.ptr, s), "bin offsets");
   if (skeys) *skeys = sk;
@@ -365,9 +362,9 @@ Route route_of(const ptk_ctx* c, int64_t Np, bool grad) {
 }
 
 // Device scratch of one interpolate call: sort keys and values (double
-// buffered), radix histograms, scan partials, bin offsets.
+// buffered), radix histograms, bin offsets.
 struct InterpScratch {
-  uint32_t *keys_a, *keys_b, *vals_a, *vals_b, *hist, *scan_tmp, *offsets;
+  uint32_t *keys_a, *keys_b, *vals_a, *vals_b, *hist, *offsets;
 };
 
 int check_interp_args(ptk_ctx* c, const double* X, int64_t Np, void* u_out, void* grad, int out_dtype) {
@@ -405,13 +402,14 @@ int interp_core(ptk_ctx* c, const InterpScratch& w, const double* X, int64_t Np,
   if (route != Route::kDirect) {
     {
       Timed t(c, s, PTK_T_KEYS);
-      PTK_HIP(c, launch_keys(X, Np, (int)N, invd_of(N), bg, w.keys_a, flag_words(c), s), "keys");
+      PTK_HIP(c, launch_keys_hist(X, Np, (int)N, invd_of(N), bg, bits_for(n_bins), w.keys_a, w.hist, flag_words(c), s),
+              "keys");
     }
     Timed t(c, s, PTK_T_SORT);
     uint32_t* sk = nullptr;
     PTK_HIP(c,
             radix_sort_keys(w.keys_a, w.keys_b, w.vals_a, w.vals_b, Np, nullptr, false, bits_for(n_bins), w.hist,
-                            w.scan_tmp, &sk, &perm, s),
+                            true, &sk, &perm, s),
             "radix sort");
     PTK_HIP(c, launch_offsets(sk, Np, n_bins, w.offsets, s), "bin offsets");
   }
@@ -467,7 +465,7 @@ int interp_common(ptk_ctx* c, const double* X, int64_t Np, void* u_out, void* gr
   }
   PTK_TRY(need(c, c->offsets, (size_t)(n_bins + 1) * 4, "bin offsets"));
   InterpScratch w{(uint32_t*)c->keys_a.ptr, (uint32_t*)c->keys_b.ptr, (uint32_t*)c->vals_a.ptr,
-                  (uint32_t*)c->vals_b.ptr,  (uint32_t*)c->hist.ptr,   (uint32_t*)c->scan_tmp.ptr,
+                  (uint32_t*)c->vals_b.ptr,  (uint32_t*)c->hist.ptr,
                   (uint32_t*)c->offsets.ptr};
   return interp_core(c, w, X, Np, u_out, grad, out_dtype, S(stream), true);
 }
@@ -518,7 +516,7 @@ bool carve_noalloc(unsigned char* base, int64_t Np, int64_t n_bins, InterpScratc
   const size_t hw = sort_hist_words(Np);
   w->hist = take(hw * 4);
   const int64_t scan_max = (int64_t)hw > n_bins + 1 ? (int64_t)hw : n_bins + 1;
-  w->scan_tmp = take(scan_tmp_words(scan_max) * 4);
+  (void)take((size_t)((scan_max + 1023) / 1024 + 1) * 4);  // unused: the calls that fit stay the same ones
   w->offsets = take((size_t)(n_bins + 1) * 4);
   *need_bytes = off;
   return off <= kNoAllocBytes;
@@ -636,7 +634,7 @@ void ptk_destroy(ptk_ctx* c) {
     DeviceGuard g(c->device);
     (void)hipDeviceSynchronize();
     DevBuf* bufs[] = {&c->field, &c->field_next, &c->coef, &c->bin_keys, &c->keys_a, &c->keys_b, &c->vals_a, &c->vals_b, &c->offsets,
-                      &c->hist, &c->scan_tmp, &c->xs, &c->xn, &c->orig, &c->orig_b, &c->k1,
+                      &c->hist, &c->xs, &c->xn, &c->orig, &c->orig_b, &c->k1,
                       &c->k2, &c->abh[0], &c->abh[1], &c->abh[2], &c->abh[3], &c->abh_b[0], &c->abh_b[1],
                       &c->abh_b[2], &c->abh_b[3], &c->gint, &c->stage, &c->lparams,
                       &c->lm, &c->lv, &c->lw1b, &c->lw2b, &c->lw2bt, &c->lgpart, &c->llpart, &c->lwide,
@@ -1000,7 +998,7 @@ int ptk_get_binning(ptk_ctx* c, uint32_t* perm, uint32_t* offsets, void* stream)
     PTK_HIP(c,
             hipMemcpyAsync(c->keys_a.ptr, c->bin_keys.ptr, (size_t)c->bin_np * 4, hipMemcpyDeviceToDevice, s),
             "copy keys");
-    PTK_TRY(bin_sorted(c, c->bin_np, c->bin_nbins, &c->bin_perm, s));
+    PTK_TRY(bin_sorted(c, c->bin_np, c->bin_nbins, false, &c->bin_perm, s));
   }
   if (c->bin_np > 0)
     PTK_HIP(c, hipMemcpyAsync(perm, c->bin_perm, (size_t)c->bin_np * 4, hipMemcpyDeviceToDevice, s), "copy perm");
@@ -1064,7 +1062,12 @@ int adv_load(ptk_ctx* c, const double* X, int64_t Np, const void* rhs_hist, int 
   const bool binned = route_of(c, Np, false) != Route::kDirect;
   if (Np > 0) {
     Timed t(c, s, PTK_T_KEYS);
-    PTK_HIP(c, launch_keys(X, Np, (int)N, invd_of(N), bg, keys, flag, s), "keys");  // (and the domain check)
+    // (and the domain check)
+    if (binned)
+      PTK_HIP(c, launch_keys_hist(X, Np, (int)N, invd_of(N), bg, bits_for(n_bins), keys, (uint32_t*)c->hist.ptr, flag, s),
+              "keys");
+    else
+      PTK_HIP(c, launch_keys(X, Np, (int)N, invd_of(N), bg, keys, flag, s), "keys");
   }
   if (Np > 0 && !binned) {
     // the caller's order
@@ -1079,7 +1082,7 @@ int adv_load(ptk_ctx* c, const double* X, int64_t Np, const void* rhs_hist, int 
     {
       Timed t(c, s, PTK_T_SORT);
       uint32_t* sk = nullptr;
-      PTK_TRY(bin_sorted(c, Np, n_bins, &perm, s, &sk, (uint32_t*)c->aoff.ptr));
+      PTK_TRY(bin_sorted(c, Np, n_bins, true, &perm, s, &sk, (uint32_t*)c->aoff.ptr));
       PTK_HIP(c, hipMemcpyAsync(c->skeys.ptr, sk, (size_t)Np * 4, hipMemcpyDeviceToDevice, s), "sorted keys");
     }
     Timed t(c, s, PTK_T_PERMUTE);
@@ -1290,7 +1293,6 @@ int adv_steps(ptk_ctx* c, int scheme, double dt, int nsteps, void* grad_out, hip
     w.mv_b = (uint32_t*)c->mv_b.ptr;
     w.mo = (uint32_t*)c->mo.ptr;
     w.hist = (uint32_t*)c->hist.ptr;
-    w.scan_tmp = (uint32_t*)c->scan_tmp.ptr;
     PTK_HIP(c,
             rebin_incremental((const uint32_t*)c->skeys.ptr, (const uint32_t*)c->aoff.ptr, keys, Np, n_bins,
                               bits_for(n_bins), w, out, (uint32_t*)c->skeys2.ptr, (uint32_t*)c->offsets2.ptr, s),
@@ -1340,11 +1342,13 @@ int adv_steps(ptk_ctx* c, int scheme, double dt, int nsteps, void* grad_out, hip
     uint32_t *perm = nullptr, *sk = nullptr;
     {
       Timed t(c, s, PTK_T_SORT);
-      PTK_HIP(c, launch_keys(st.xcur, Np, (int)N, invd, bg, (uint32_t*)c->mk_a.ptr, flag, s), "keys");
+      PTK_HIP(c, launch_keys_hist(st.xcur, Np, (int)N, invd, bg, bits_for(n_bins), (uint32_t*)c->mk_a.ptr,
+                                  (uint32_t*)c->hist.ptr, flag, s),
+              "keys");
       PTK_HIP(c,
               radix_sort_keys((uint32_t*)c->mk_a.ptr, (uint32_t*)c->mk_b.ptr, (uint32_t*)c->mv_a.ptr,
                               (uint32_t*)c->mv_b.ptr, Np, nullptr, false, bits_for(n_bins), (uint32_t*)c->hist.ptr,
-                              (uint32_t*)c->scan_tmp.ptr, &sk, &perm, s),
+                              true, &sk, &perm, s),
               "radix sort");
       PTK_HIP(c, launch_offsets(sk, Np, n_bins, (uint32_t*)c->aoff.ptr, s), "bin offsets");
       PTK_HIP(c, hipMemcpyAsync(c->skeys.ptr, sk, (size_t)Np * 4, hipMemcpyDeviceToDevice, s), "sorted keys");
@@ -2144,12 +2148,14 @@ int ptk_interpolate_learned(ptk_ctx* c, const double* X, int64_t Np, float* out,
   c->flag[3] = 0;
   {
     Timed t(c, s, PTK_T_KEYS);
-    PTK_HIP(c, launch_keys(X, Np, (int)N, invd_of(N), bg, (uint32_t*)c->keys_a.ptr, flag, s), "keys");
+    PTK_HIP(c, launch_keys_hist(X, Np, (int)N, invd_of(N), bg, bits_for(n_bins), (uint32_t*)c->keys_a.ptr,
+                                (uint32_t*)c->hist.ptr, flag, s),
+            "keys");
   }
   uint32_t* perm = nullptr;
   {
     Timed t(c, s, PTK_T_SORT);
-    PTK_TRY(bin_sorted(c, Np, n_bins, &perm, s));
+    PTK_TRY(bin_sorted(c, Np, n_bins, true, &perm, s));
   }
   {
     // the kernel reads the caller's positions through the permutation
@@ -2219,7 +2225,7 @@ int ptk_selftest(void) {
   expect(flag_error(&c, kFlagBinning) == PTK_EINTERNAL);
   expect(flag_error(&c, kFlagDomain | kFlagBinning) == PTK_EDOMAIN);
   // binning and advance buffer checks on a context whose buffers are short
-  DevBuf* bufs[] = {&c.keys_a, &c.keys_b, &c.vals_a, &c.vals_b, &c.hist, &c.scan_tmp, &c.offsets};
+  DevBuf* bufs[] = {&c.keys_a, &c.keys_b, &c.vals_a, &c.vals_b, &c.hist, &c.offsets};
   for (DevBuf* d : bufs) {
     d->ptr = placeholder;
     d->cap = (size_t)1 << 30;

@@ -17,23 +17,26 @@ namespace ptk {
 // ---------------------------------------------------------------------------
 // keys and locate
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_keys(const double* __restrict__ X, int64_t n, int N,
-                                              double invd, BinGeom g, uint32_t* __restrict__ keys,
-                                              int* __restrict__ flag) {
-  int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
+__device__ __forceinline__ uint32_t key_of(const double* __restrict__ X, int64_t i, int N, double invd,
+                                           const BinGeom& g, int* __restrict__ flag) {
   double x1 = X[3 * i], x2 = X[3 * i + 1], x3 = X[3 * i + 2];
   if (!in_domain3(x1, x2, x3)) {
     raise_flag(flag, kFlagDomain);
-    keys[i] = 0;
-    return;
+    return 0;
   }
   int c1, c2, c3;
   double t;
   locate(x1, N, invd, &c1, &t);
   locate(x2, N, invd, &c2, &t);
   locate(x3, N, invd, &c3, &t);
-  keys[i] = bin_key(c1, c2, c3, g);
+  return bin_key(c1, c2, c3, g);
+}
+
+__global__ __launch_bounds__(256) void k_keys(const double* __restrict__ X, int64_t n, int N,
+                                              double invd, BinGeom g, uint32_t* __restrict__ keys,
+                                              int* __restrict__ flag) {
+  int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) keys[i] = key_of(X, i, N, invd, g, flag);
 }
 
 __global__ __launch_bounds__(256) void k_locate(const double* __restrict__ X, int64_t n3, int N,
@@ -92,6 +95,27 @@ __device__ __forceinline__ int64_t sort_tiles(int64_t n, const uint32_t* n_dev) 
   return (n + kTile - 1) / kTile;
 }
 
+// keys and, of the same tiles, the histogram of the sort's first digit
+__global__ __launch_bounds__(256) void k_keys_hist(const double* __restrict__ X, int64_t n, int N, double invd,
+                                                   BinGeom g, uint32_t mask, uint32_t* __restrict__ keys,
+                                                   uint32_t* __restrict__ hist, int64_t n_tiles,
+                                                   int* __restrict__ flag) {
+  __shared__ uint32_t h[256];
+  h[threadIdx.x] = 0;
+  __syncthreads();
+  const int64_t base = (int64_t)blockIdx.x * kTile;
+  for (int k = 0; k < kSortItems; ++k) {
+    const int64_t i = base + k * kSortThreads + threadIdx.x;
+    if (i < n) {
+      const uint32_t key = key_of(X, i, N, invd, g, flag);
+      keys[i] = key;
+      atomicAdd(&h[key & mask], 1u);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x <= mask) hist[(int64_t)threadIdx.x * n_tiles + blockIdx.x] = h[threadIdx.x];
+}
+
 __global__ __launch_bounds__(256) void k_radix_hist(const uint32_t* __restrict__ keys, int64_t n,
                                                     const uint32_t* __restrict__ n_dev, int shift, uint32_t mask,
                                                     uint32_t* __restrict__ hist, int64_t n_tiles) {
@@ -109,12 +133,15 @@ __global__ __launch_bounds__(256) void k_radix_hist(const uint32_t* __restrict__
     if (i < n) atomicAdd(&h[(keys[i] >> shift) & mask], 1u);
   }
   __syncthreads();
-  hist[(int64_t)threadIdx.x * n_tiles + blockIdx.x] = h[threadIdx.x];
+  if (threadIdx.x <= mask) hist[(int64_t)threadIdx.x * n_tiles + blockIdx.x] = h[threadIdx.x];
 }
 
+// incl: the histogram rows after k_scan_rows, so a row's last entry is its
+// digit's count; the digits' starts are those counts' scan, done here by every
+// block
 __global__ __launch_bounds__(256) void k_radix_scatter(
     const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in, int64_t n,
-    const uint32_t* __restrict__ n_dev, int shift, uint32_t mask, int bits, const uint32_t* __restrict__ prefix,
+    const uint32_t* __restrict__ n_dev, int shift, uint32_t mask, int bits, const uint32_t* __restrict__ incl,
     int64_t n_tiles, uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out) {
   if (n_dev) {
     n_tiles = sort_tiles(n, n_dev);
@@ -122,12 +149,18 @@ __global__ __launch_bounds__(256) void k_radix_scatter(
   }
   if ((int64_t)blockIdx.x * kTile >= n) return;
   __shared__ uint32_t wcount[4][256];
-  __shared__ uint32_t dstart[256];
+  __shared__ uint32_t dstart[256], dpos[256];
   __shared__ uint32_t scan_sh[4];
   __shared__ uint32_t skey[kTile], sval[kTile];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   for (int d = threadIdx.x; d < 4 * 256; d += 256) (&wcount[0][0])[d] = 0;
+  uint32_t dcount = 0, dbefore = 0;  // of digit threadIdx.x: its count, and that of the tiles before this one
+  if (threadIdx.x <= mask) {
+    const uint32_t* row = incl + (int64_t)threadIdx.x * n_tiles;
+    dcount = row[n_tiles - 1];
+    dbefore = blockIdx.x ? row[(int64_t)blockIdx.x - 1] : 0u;
+  }
   __syncthreads();
   const int64_t wbase = (int64_t)blockIdx.x * kTile + wave * (64 * kSortItems);
   const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -167,7 +200,9 @@ __global__ __launch_bounds__(256) void k_radix_scatter(
   }
   uint32_t ntile;
   const uint32_t my_start = block_excl_scan_256(tile_count, scan_sh, &ntile);
+  uint32_t all;
   dstart[threadIdx.x] = my_start;
+  dpos[threadIdx.x] = block_excl_scan_256(dcount, scan_sh, &all) + dbefore - my_start;
   __syncthreads();
   // the tile in digit order in LDS, then written out run by run: consecutive
   // threads write consecutive addresses of a digit's run
@@ -181,70 +216,51 @@ __global__ __launch_bounds__(256) void k_radix_scatter(
   __syncthreads();
   for (uint32_t j = threadIdx.x; j < ntile; j += kSortThreads) {
     const uint32_t k = skey[j];
-    const uint32_t d = (k >> shift) & mask;
-    const uint64_t pos = (uint64_t)prefix[(int64_t)d * n_tiles + blockIdx.x] + (j - dstart[d]);
+    const uint32_t pos = dpos[(k >> shift) & mask] + j;
     keys_out[pos] = k;
     vals_out[pos] = sval[j];
   }
 }
 
-// exclusive scan of n uint32 (in place): block sums, scan of sums, apply
-constexpr int kScanBlock = 1024;  // elements per block (256 threads x 4)
+// In-place inclusive scan of every row of a [rows][len] array, a block a row:
+// the histogram rows of a sort pass, or the movers per tile.  One launch where
+// a scan of the whole array takes three (block sums, their scan, the sums
+// added), and no work for digits that do not occur: what these launches cost
+// is their latency.  (Re-binning is 12 launches with two digits, 23 before; a
+// Heun step of 10^6 particles with axes at 256^3 and a store 975 us, now 904;
+// the sort of a call with 1.25e7 at 512^3, whose first histogram is now taken
+// with the keys, about 50 us less: learned inference 2903 us, now 2852.)
+constexpr int kScanThreads = 1024;
 
-
-// length of a scan over sort histograms whose tile count lives on the device
-// (cnt != NULL: 256 digits x sort_tiles(cap, cnt)), else n
-__device__ __forceinline__ int64_t scan_len(int64_t n, const uint32_t* cnt, int64_t cap) {
-  return cnt ? 256 * sort_tiles(cap, cnt) : n;
-}
-
-__global__ __launch_bounds__(256) void k_scan_reduce(const uint32_t* __restrict__ a, int64_t n,
-                                                     uint32_t* __restrict__ sums, const uint32_t* __restrict__ cnt,
-                                                     int64_t cap) {
-  n = scan_len(n, cnt, cap);
-  if ((int64_t)blockIdx.x * kScanBlock >= n) return;
-  __shared__ uint32_t sh[4];
-  int64_t base = (int64_t)blockIdx.x * kScanBlock + threadIdx.x * 4;
-  uint32_t s = 0;
-  for (int k = 0; k < 4; ++k)
-    if (base + k < n) s += a[base + k];
-  uint32_t tot;
-  block_excl_scan_256(s, sh, &tot);
-  if (threadIdx.x == 0) sums[blockIdx.x] = tot;
-}
-
-__global__ __launch_bounds__(256) void k_scan_top(uint32_t* __restrict__ sums, int64_t nb,
-                                                  const uint32_t* __restrict__ cnt, int64_t cap) {
-  if (cnt) nb = (scan_len(0, cnt, cap) + kScanBlock - 1) / kScanBlock;
-  __shared__ uint32_t sh[4];
+__global__ __launch_bounds__(1024) void k_scan_rows(uint32_t* __restrict__ a, int64_t len, int64_t n,
+                                                    const uint32_t* __restrict__ n_dev) {
+  if (n_dev) len = sort_tiles(n, n_dev);
+  constexpr int W = kScanThreads / 64;
+  __shared__ uint32_t sh[2][W];
+  uint32_t* row = a + (int64_t)blockIdx.x * len;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint32_t carry = 0;
-  for (int64_t base = 0; base < nb; base += 256) {
-    int64_t i = base + threadIdx.x;
-    uint32_t v = i < nb ? sums[i] : 0u;
-    uint32_t tot;
-    uint32_t ex = block_excl_scan_256(v, sh, &tot);
-    if (i < nb) sums[i] = carry + ex;
-    carry += tot;
-  }
-}
-
-__global__ __launch_bounds__(256) void k_scan_apply(uint32_t* __restrict__ a, int64_t n,
-                                                    const uint32_t* __restrict__ sums,
-                                                    const uint32_t* __restrict__ cnt, int64_t cap) {
-  n = scan_len(n, cnt, cap);
-  if ((int64_t)blockIdx.x * kScanBlock >= n) return;
-  __shared__ uint32_t sh[4];
-  int64_t base = (int64_t)blockIdx.x * kScanBlock + threadIdx.x * 4;
-  uint32_t v[4], s = 0;
-  for (int k = 0; k < 4; ++k) {
-    v[k] = (base + k < n) ? a[base + k] : 0u;
-    s += v[k];
-  }
-  uint32_t tot;
-  uint32_t ex = block_excl_scan_256(s, sh, &tot) + sums[blockIdx.x];
-  for (int k = 0; k < 4; ++k) {
-    if (base + k < n) a[base + k] = ex;
-    ex += v[k];
+  int buf = 0;
+  for (int64_t base = 0; base < len; base += 4 * kScanThreads, buf ^= 1) {
+    const int64_t i = base + 4 * (int64_t)threadIdx.x;
+    uint32_t v[4];
+    for (int k = 0; k < 4; ++k) v[k] = i + k < len ? row[i + k] : 0u;
+    for (int k = 1; k < 4; ++k) v[k] += v[k - 1];
+    uint32_t x = v[3];
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(x, o, 64);
+      if (lane >= o) x += y;
+    }
+    if (lane == 63) sh[buf][wave] = x;
+    __syncthreads();  // (the buffer is written again two rounds on, past the next barrier)
+    uint32_t before = carry + x - v[3];
+    for (int w = 0; w < W; ++w) {
+      const uint32_t t = sh[buf][w];
+      if (w < wave) before += t;
+      carry += t;
+    }
+    for (int k = 0; k < 4; ++k)
+      if (i + k < len) row[i + k] = before + v[k];
   }
 }
 
@@ -386,7 +402,7 @@ __global__ __launch_bounds__(256) void k_rebin_compact(const uint32_t* __restric
                                                        uint32_t* __restrict__ mo) {
   TileMovers t;
   tile_movers(okeys, nkeys, n, t);
-  const uint32_t base = tile_off[blockIdx.x];
+  const uint32_t base = blockIdx.x ? tile_off[blockIdx.x - 1] : 0u;
   for (int r = 0; r < kSortItems; ++r)
     if (t.mover[r]) {
       mk[base + t.before[r]] = t.nk[r];
@@ -395,34 +411,39 @@ __global__ __launch_bounds__(256) void k_rebin_compact(const uint32_t* __restric
     }
 }
 
-// first[b] = first index i < m with keys[i] >= b (m if none), for sorted keys
-// and b = 0..n_bins, by binary search (one thread per bin, so the cost does
-// not depend on how the keys are spread); m is read on the device
-__global__ __launch_bounds__(256) void k_first_ge(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ m_dev,
-                                                  int64_t n_bins, uint32_t* __restrict__ first) {
-  const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (b > n_bins) return;
-  uint32_t lo = 0, hi = *m_dev;
+// first index i < m with keys[i] >= b (m if none), for sorted keys
+__device__ __forceinline__ uint32_t first_ge(const uint32_t* __restrict__ keys, uint32_t m, uint32_t b) {
+  uint32_t lo = 0, hi = m;
   while (lo < hi) {
     const uint32_t mid = lo + (hi - lo) / 2;
-    if (keys[mid] < (uint32_t)b)
+    if (keys[mid] < b)
       lo = mid + 1;
     else
       hi = mid;
   }
-  first[b] = lo;
+  return lo;
 }
 
-// new offsets: elements with new key < b = (old key < b) - (movers whose old
-// key < b) + (movers whose new key < b); also clears the per-bin count of
-// movers that come from earlier bins
-__global__ __launch_bounds__(256) void k_rebin_offsets(const uint32_t* __restrict__ ooff,
-                                                       const uint32_t* __restrict__ out_before,
-                                                       const uint32_t* __restrict__ in_start, int64_t n_bins,
-                                                       uint32_t* __restrict__ noff, uint32_t* __restrict__ inc_before) {
+// Per bin b = 0..n_bins: the movers whose old key < b (mo: their old keys, in
+// current order, so sorted) and those whose new key < b (sk: sorted), by binary
+// search (one thread per bin, so the cost does not depend on how the keys are
+// spread; m is read on the device); the new offset: elements with new key < b
+// = (old key < b) - (movers whose old key < b) + (movers whose new key < b);
+// and the cleared count of movers that come from earlier bins.
+__global__ __launch_bounds__(256) void k_rebin_offsets(const uint32_t* __restrict__ mo,
+                                                       const uint32_t* __restrict__ sk,
+                                                       const uint32_t* __restrict__ m_dev,
+                                                       const uint32_t* __restrict__ ooff, int64_t n_bins,
+                                                       uint32_t* __restrict__ out_before,
+                                                       uint32_t* __restrict__ in_start, uint32_t* __restrict__ noff,
+                                                       uint32_t* __restrict__ inc_before) {
   const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (b > n_bins) return;
-  noff[b] = ooff[b] - out_before[b] + in_start[b];
+  const uint32_t m = *m_dev;
+  const uint32_t out = first_ge(mo, m, (uint32_t)b), in = first_ge(sk, m, (uint32_t)b);
+  out_before[b] = out;
+  in_start[b] = in;
+  noff[b] = ooff[b] - out + in;
   inc_before[b] = 0u;
 }
 
@@ -461,7 +482,7 @@ __global__ __launch_bounds__(256) void k_rebin_stayers(const uint32_t* __restric
                                                        uint32_t* __restrict__ perm, uint32_t* __restrict__ skeys) {
   TileMovers t;
   tile_movers(okeys, nkeys, n, t);
-  const uint32_t base = tile_off[blockIdx.x];
+  const uint32_t base = blockIdx.x ? tile_off[blockIdx.x - 1] : 0u;
   for (int r = 0; r < kSortItems; ++r) {
     if (!t.valid[r] || t.mover[r]) continue;
     const uint32_t b = t.nk[r];
@@ -479,10 +500,26 @@ __global__ __launch_bounds__(256) void k_rebin_stayers(const uint32_t* __restric
 // ---------------------------------------------------------------------------
 static inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
+// passes of a sort of keys below 2^key_bits, and the bits of a digit
+static inline int sort_passes(int key_bits) { return key_bits <= 0 ? 1 : (key_bits + 7) / 8; }
+static inline int digit_bits(int key_bits) {
+  const int passes = sort_passes(key_bits);
+  return key_bits <= 0 ? 1 : (key_bits + passes - 1) / passes;
+}
+
 hipError_t launch_keys(const double* X, int64_t n, int N, double invd, const BinGeom& g, uint32_t* keys,
                        int* flag, hipStream_t s) {
   if (n == 0) return hipSuccess;
   k_keys<<<blocks_for(n, 256), 256, 0, s>>>(X, n, N, invd, g, keys, flag);
+  return hipGetLastError();
+}
+
+hipError_t launch_keys_hist(const double* X, int64_t n, int N, double invd, const BinGeom& g, int key_bits,
+                            uint32_t* keys, uint32_t* hist, int* flag, hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  const unsigned n_tiles = blocks_for(n, kTile);
+  k_keys_hist<<<n_tiles, 256, 0, s>>>(X, n, N, invd, g, (1u << digit_bits(key_bits)) - 1u, keys, hist,
+                                      (int64_t)n_tiles, flag);
   return hipGetLastError();
 }
 
@@ -498,38 +535,21 @@ size_t sort_hist_words(int64_t n) {
   return (size_t)256 * (size_t)(n_tiles > 0 ? n_tiles : 1);
 }
 
-size_t scan_tmp_words(int64_t m) { return (size_t)((m + kScanBlock - 1) / kScanBlock + 1); }
-
-// exclusive scan of a[0, m); with cnt != NULL the length is the histogram
-// size of a sort of min(cap, *cnt) elements (m is then its upper bound)
-static hipError_t scan_u32(uint32_t* a, int64_t m, uint32_t* tmp, const uint32_t* cnt, int64_t cap,
-                           hipStream_t s) {
-  if (m == 0) return hipSuccess;
-  int64_t nb = (m + kScanBlock - 1) / kScanBlock;
-  k_scan_reduce<<<(unsigned)nb, 256, 0, s>>>(a, m, tmp, cnt, cap);
-  k_scan_top<<<1, 256, 0, s>>>(tmp, nb, cnt, cap);
-  k_scan_apply<<<(unsigned)nb, 256, 0, s>>>(a, m, tmp, cnt, cap);
-  return hipGetLastError();
-}
-
-hipError_t exclusive_scan_u32(uint32_t* a, int64_t m, uint32_t* tmp, hipStream_t s) {
-  return scan_u32(a, m, tmp, nullptr, 0, s);
-}
-
 // Stable sort of keys.  Values: those in va if vals_in_va, else the input
 // positions.  n_dev (optional) holds the element count on the device, n an
-// upper bound.  On return *keys_sorted and *perm point into {ka, kb} / {va, vb}.
+// upper bound.  have_hist: hist holds the first digit's histogram already
+// (launch_keys_hist).  On return *keys_sorted and *perm point into {ka, kb} / {va, vb}.
 hipError_t radix_sort_keys(uint32_t* ka, uint32_t* kb, uint32_t* va, uint32_t* vb, int64_t n,
-                           const uint32_t* n_dev, bool vals_in_va, int key_bits, uint32_t* hist,
-                           uint32_t* tmp, uint32_t** keys_sorted, uint32_t** perm, hipStream_t s) {
+                           const uint32_t* n_dev, bool vals_in_va, int key_bits, uint32_t* hist, bool have_hist,
+                           uint32_t** keys_sorted, uint32_t** perm, hipStream_t s) {
   if (n == 0) {
     *keys_sorted = ka;
     *perm = va;
     return hipSuccess;
   }
   const int64_t n_tiles = (n + kTile - 1) / kTile;
-  const int passes = key_bits <= 0 ? 1 : (key_bits + 7) / 8;
-  const int bits = key_bits <= 0 ? 1 : (key_bits + passes - 1) / passes;
+  const int passes = sort_passes(key_bits);
+  const int bits = digit_bits(key_bits);
   const uint32_t mask = (1u << bits) - 1u;
   // pass p reads (kin, vin) and writes (kout, vout); the first pass takes the
   // input positions as values
@@ -537,13 +557,13 @@ hipError_t radix_sort_keys(uint32_t* ka, uint32_t* kb, uint32_t* va, uint32_t* v
            *vspare = vb;
   for (int p = 0; p < passes; ++p) {
     const int shift = p * bits;
-    k_radix_hist<<<(unsigned)n_tiles, 256, 0, s>>>(kin, n, n_dev, shift, mask, hist, n_tiles);
+    if (p > 0 || !have_hist)
+      k_radix_hist<<<(unsigned)n_tiles, 256, 0, s>>>(kin, n, n_dev, shift, mask, hist, n_tiles);
     // with the count on the device, every kernel sizes the histogram from it
-    hipError_t e = scan_u32(hist, 256 * n_tiles, tmp, n_dev, n, s);
-    if (e != hipSuccess) return e;
+    k_scan_rows<<<mask + 1u, kScanThreads, 0, s>>>(hist, n_tiles, n, n_dev);
     k_radix_scatter<<<(unsigned)n_tiles, 256, 0, s>>>(kin, vin, n, n_dev, shift, mask, bits, hist, n_tiles,
                                                       kout, vout);
-    e = hipGetLastError();
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     uint32_t* t = kin;
     kin = kout;
@@ -565,41 +585,24 @@ hipError_t rebin_incremental(const uint32_t* okeys, const uint32_t* ooff, const 
   if (n == 0) return hipSuccess;
   const int64_t n_tiles = (n + kTile - 1) / kTile;
   hipError_t e;
-  // movers per tile, exclusive scan: the last entry becomes the mover count m
-  if ((e = launch_fill_i32((int*)(w.blockoff + n_tiles), 1, 0, s)) != hipSuccess) return e;
+  // movers per tile, inclusive scan: the last entry becomes the mover count m
   k_rebin_count<<<(unsigned)n_tiles, 256, 0, s>>>(okeys, nkeys, n, w.blockoff);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = exclusive_scan_u32(w.blockoff, n_tiles + 1, w.scan_tmp, s)) != hipSuccess) return e;
-  const uint32_t* m_dev = w.blockoff + n_tiles;
+  k_scan_rows<<<1, kScanThreads, 0, s>>>(w.blockoff, n_tiles, 0, nullptr);
+  const uint32_t* m_dev = w.blockoff + (n_tiles - 1);
   // movers in current order (their old keys are then sorted), then sorted by new key
   k_rebin_compact<<<(unsigned)n_tiles, 256, 0, s>>>(okeys, nkeys, n, w.blockoff, w.mk_a, w.mv_a, w.mo);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_first_ge<<<blocks_for(n_bins + 1, 256), 256, 0, s>>>(w.mo, m_dev, n_bins, w.out_before);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   uint32_t *sk = nullptr, *sv = nullptr;
-  if ((e = radix_sort_keys(w.mk_a, w.mk_b, w.mv_a, w.mv_b, n, m_dev, true, key_bits, w.hist, w.scan_tmp, &sk, &sv,
-                           s)) != hipSuccess)
+  if ((e = radix_sort_keys(w.mk_a, w.mk_b, w.mv_a, w.mv_b, n, m_dev, true, key_bits, w.hist, false, &sk, &sv, s)) !=
+      hipSuccess)
     return e;
-  k_first_ge<<<blocks_for(n_bins + 1, 256), 256, 0, s>>>(sk, m_dev, n_bins, w.in_start);
-  k_rebin_offsets<<<blocks_for(n_bins + 1, 256), 256, 0, s>>>(ooff, w.out_before, w.in_start, n_bins, noff,
-                                                             w.inc_before);
+  k_rebin_offsets<<<blocks_for(n_bins + 1, 256), 256, 0, s>>>(w.mo, sk, m_dev, ooff, n_bins, w.out_before, w.in_start,
+                                                             noff, w.inc_before);
   const int64_t mgrid = min((int64_t)4096, (n + 255) / 256);
   k_rebin_movers<<<(unsigned)mgrid, 256, 0, s>>>(sk, sv, m_dev, ooff, noff, w.in_start, w.out_before, w.inc_before,
                                                  perm, skeys);
   k_rebin_stayers<<<(unsigned)n_tiles, 256, 0, s>>>(okeys, nkeys, n, w.blockoff, ooff, noff, w.out_before,
                                                     w.inc_before, perm, skeys);
-  return hipGetLastError();
-}
-
-// a fill of n ints (a kernel, so that a captured graph records no memset node)
-__global__ __launch_bounds__(256) void k_fill_i32(int* __restrict__ p, int64_t n, int value) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = value;
-}
-
-hipError_t launch_fill_i32(int* p, int64_t n, int value, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  k_fill_i32<<<blocks_for(n, 256), 256, 0, s>>>(p, n, value);
   return hipGetLastError();
 }
 

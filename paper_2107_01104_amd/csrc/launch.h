@@ -22,14 +22,16 @@ struct BinGeom {
 // binning.hip
 hipError_t launch_keys(const double* X, int64_t n, int N, double invd, const BinGeom& g, uint32_t* keys,
                        int* flag, hipStream_t s);
+// the same, and the histogram of the first digit of a sort of keys below
+// 2^key_bits (sort_hist_words(n) words) for radix_sort_keys
+hipError_t launch_keys_hist(const double* X, int64_t n, int N, double invd, const BinGeom& g, int key_bits,
+                            uint32_t* keys, uint32_t* hist, int* flag, hipStream_t s);
 hipError_t launch_locate(const double* X, int64_t n3, int N, double invd, int32_t* cell, double* off,
                          int* flag, hipStream_t s);
 size_t sort_hist_words(int64_t n);
-size_t scan_tmp_words(int64_t m);
-hipError_t exclusive_scan_u32(uint32_t* a, int64_t m, uint32_t* tmp, hipStream_t s);
 hipError_t radix_sort_keys(uint32_t* ka, uint32_t* kb, uint32_t* va, uint32_t* vb, int64_t n,
-                           const uint32_t* n_dev, bool vals_in_va, int key_bits, uint32_t* hist,
-                           uint32_t* tmp, uint32_t** keys_sorted, uint32_t** perm, hipStream_t s);
+                           const uint32_t* n_dev, bool vals_in_va, int key_bits, uint32_t* hist, bool have_hist,
+                           uint32_t** keys_sorted, uint32_t** perm, hipStream_t s);
 // Stable re-sort after small moves.  okeys: the current keys, sorted, with
 // CSR offsets ooff[n_bins+1]; nkeys: new keys in the same order.  Produces
 // perm (new position -> current index), skeys (new sorted keys) and noff
@@ -39,13 +41,12 @@ struct RebinScratch {
   uint32_t *in_start, *out_before, *inc_before;  // [n_bins + 1] each
   uint32_t* blockoff;                            // [n/2048 + 2]
   uint32_t *mk_a, *mk_b, *mv_a, *mv_b, *mo;      // [n] each
-  uint32_t *hist, *scan_tmp;                     // as for radix_sort_keys on n elements
+  uint32_t* hist;                                // as for radix_sort_keys on n elements
 };
 size_t rebin_block_words(int64_t n);
 hipError_t rebin_incremental(const uint32_t* okeys, const uint32_t* ooff, const uint32_t* nkeys, int64_t n,
                              int64_t n_bins, int key_bits, const RebinScratch& w, uint32_t* perm, uint32_t* skeys,
                              uint32_t* noff, hipStream_t s);
-hipError_t launch_fill_i32(int* p, int64_t n, int value, hipStream_t s);
 hipError_t launch_iota(uint32_t* p, int64_t n, hipStream_t s);  // p[i] = i
 hipError_t launch_offsets(const uint32_t* skeys, int64_t n, int64_t n_bins, uint32_t* offsets,
                           hipStream_t s);

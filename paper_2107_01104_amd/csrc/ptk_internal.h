@@ -109,7 +109,7 @@ struct ptk_ctx {
   bool bin_from_keys = false;
   ptk::DevBuf bin_keys;
   // scratch
-  ptk::DevBuf keys_a, keys_b, vals_a, vals_b, offsets, hist, scan_tmp;
+  ptk::DevBuf keys_a, keys_b, vals_a, vals_b, offsets, hist;
   // status words in pinned host memory: two for the calls, two for the learned
   // inference (which reads its own whether or not checks are on)
   volatile int* flag = nullptr;
