@@ -6,9 +6,8 @@
 // Matrix-core tiles: v_mfma_f32_32x32x16_bf16.  Lane l holds, of a 32 x 16 A
 // tile, row l%32 and the 8 consecutive k starting at 8*(l/32); of a 16 x 32 B
 // tile, column l%32 and the same k; of the 32 x 32 FP32 result, column l%32
-// and rows 8*(v/4) + 4*(l/32) + v%4 in register v.  A workgroup of 4 waves
-// takes 64 rows (particles or training pairs); wave w owns hidden units
-// [32w, 32w+32) in the forward products.
+// and rows 8*(v/4) + 4*(l/32) + v%4 in register v.  In training a workgroup of
+// 8 waves takes 64 pairs; in inference a wave takes 32 particles by itself.
 #include "device_common.h"
 #include "launch.h"
 #include "ptk_internal.h"
