@@ -639,8 +639,8 @@ __global__ __launch_bounds__(NT) void k_update(float* params, float* m, float* v
 // The stencil rows come in coalesced 16-byte pieces and change lanes through the
 // wave's own LDS.  12.5e6 particles on 512^3 in the caller's order: 2.79 ms with
 // two lanes reading their own rows (a cache access per lane: the address units
-// busy 66%), 2.48 so; four waves staging 64 particles through LDS, the weights
-// in registers, 2.75.  Without its gather it takes 1.7 ms; the SiLUs (two
+// busy 66%), 2.48 so (2.21 with the order of the chunks below); four waves staging 64 particles through LDS, the weights
+// in registers, 2.75.  Without its gather it took 1.7 ms; the SiLUs (two
 // transcendentals each) and the matrix instructions are not what bounds it, and
 // neither more waves (12: 2.60) nor the next chunk's stencil in flight (256
 // registers, 2.61) help: the vector, address and LDS pipes are each about half
@@ -684,25 +684,26 @@ __global__ __launch_bounds__(64 * INF_WAVES, INF_WAVES / 4) void k_infer(Learned
   const float b3[NO] = {params[oB3], params[oB3 + 1], params[oB3 + 2]};
   __syncthreads();
 
-  // each workgroup walks a contiguous range of chunks (neighbouring bins, so its
-  // stencil reads stay in L2 and in the translation caches), a chunk per wave in
-  // turn; consecutive workgroups go round-robin to the 8 XCDs, so XCD x is given
-  // a contiguous range
+  // consecutive workgroups go round-robin to the 8 XCDs: XCD x takes a contiguous
+  // range of the chunks and its waves go through it side by side, so that the
+  // chunks in flight are neighbouring bins, which share their stencils' lines in
+  // the XCD's L2 (a range per workgroup: 512^3 with 1.25e7 particles 2.43 ms,
+  // now 2.21; 1024^3 with 1e8 23.6, now 22.4).  The workgroup varies faster
+  // than the wave: what is left for the last round is spread over the CUs.
   const int64_t nchunks = (n + INF_PART - 1) / INF_PART;
   const int64_t per_xcd = gridDim.x / 8;
-  const int64_t bid = (int64_t)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  const int64_t per_block = (nchunks + gridDim.x - 1) / gridDim.x;
-  const int64_t ch_end = min(nchunks, (bid + 1) * per_block);
+  const int64_t per = (nchunks + 7) / 8, step = per_xcd * INF_WAVES;
+  const int64_t ch_end = min(nchunks, ((int64_t)(blockIdx.x & 7) + 1) * per);
   // row indices two chunks ahead, coordinates one chunk ahead (clamped to the
   // last particle; unconditional, so no branch merge waits for them)
   auto row_of = [&](int64_t ch) -> uint32_t { return orig[min(ch * INF_PART + (lane & 31), n - 1)]; };
-  int64_t ch = bid * per_block + wave;
+  int64_t ch = (int64_t)(blockIdx.x & 7) * per + wave * per_xcd + (int64_t)(blockIdx.x >> 3);
   if (ch >= ch_end) return;
-  uint32_t row = row_of(ch), row_n = row_of(ch + INF_WAVES);
+  uint32_t row = row_of(ch), row_n = row_of(ch + step);
   double x[3];
 #pragma unroll
   for (int d = 0; d < 3; ++d) x[d] = X[3 * (int64_t)row + d];
-  for (; ch < ch_end; ch += INF_WAVES) {
+  for (; ch < ch_end; ch += step) {
     const int64_t p = ch * INF_PART + (lane & 31);
     const uint32_t dst = row;
     int c[3];
@@ -742,7 +743,7 @@ __global__ __launch_bounds__(64 * INF_WAVES, INF_WAVES / 4) void k_infer(Learned
     }
     // the next chunk's coordinates and the rows after them
     row = row_n;
-    row_n = row_of(ch + 2 * INF_WAVES);
+    row_n = row_of(ch + 2 * step);
 #pragma unroll
     for (int d = 0; d < 3; ++d) x[d] = X[3 * (int64_t)row + d];
     // the I = 4 Lagrange sum over this lane's planes
