@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <new>
 #include <mutex>
 #include <string>
@@ -343,6 +344,7 @@ enum class Route {
 // 1197 / 1180; 1024^3 with 3.2e6: 7348 / 4288 / 6995; 64^3 with 78643: 71 / 138 /
 // 119, 262144: 163 / 204 / 149.
 Route route_of(const ptk_ctx* c, int64_t Np, bool grad) {
+  if (c->test_route >= 0) return (Route)c->test_route;
   const BinGeom g = bin_geom(c);
   const bool f64 = c->storage == PTK_F64, f32 = c->storage == PTK_F32;
   const double n = 1e-6 * (double)Np, nodes = 1e-6 * (double)c->geom.N * (double)c->geom.N * (double)c->geom.N;
@@ -609,6 +611,11 @@ int ptk_create(ptk_ctx** out, int device) {
   if (!c) return PTK_ENOMEM;
   c->device = device;
   if (const char* cap = std::getenv("PTK_TEST_MAX_BYTES")) c->byte_cap = (size_t)std::strtoull(cap, nullptr, 10);
+  if (const char* r = std::getenv("PTK_TEST_ROUTE"))
+    c->test_route = (int)(!std::strcmp(r, "sweep")    ? Route::kSweep
+                          : !std::strcmp(r, "direct") ? Route::kDirect
+                          : !std::strcmp(r, "sorted") ? Route::kDirectSorted
+                                                      : (Route)-1);
   if (const char* nc = std::getenv("PTK_NO_CHECK")) c->check = !(nc[0] == '1');
   DeviceGuard g(device);
   if (g.err != hipSuccess) {
@@ -2237,6 +2244,23 @@ int ptk_selftest(void) {
   c.keys_b.cap = 3999;
   expect(check_binning_caps(&c, 1000, 5000) == PTK_EINTERNAL);
   for (DevBuf* d : bufs) *d = DevBuf();  // nothing for the destructor-free context to release
+  // launches of the direct kernels: below 2^32 work-items each, whole blocks but
+  // for the last, every particle once
+  for (int64_t np : {(int64_t)1, (int64_t)16, (int64_t)17, ((int64_t)1 << 28) - 16, (int64_t)1 << 28,
+                     ((int64_t)1 << 28) + 1, ((int64_t)1 << 32) - 1}) {
+    int64_t first = 0;
+    while (first < np) {
+      unsigned blocks = 0;
+      int threads = 0;
+      const int64_t n = direct_slice(np, first, &blocks, &threads), per = threads / 16;
+      const bool ok = n > 0 && per > 0 && (uint64_t)blocks * (uint64_t)threads < (uint64_t)1 << 32 &&
+                      blocks * per >= n && (blocks - 1) * per < n && (n % per == 0 || first + n == np);
+      expect(ok);
+      if (!ok) break;
+      first += n;
+    }
+    expect(first == np);
+  }
   return bad == 0 ? PTK_OK : PTK_EINTERNAL;
 }
 

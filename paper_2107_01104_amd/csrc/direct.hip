@@ -162,12 +162,25 @@ __device__ __forceinline__ void table_row(const void* coef, int d, int jj, V* c)
 constexpr int kDirThreads = 256;
 constexpr int kDirGroups = kDirThreads / 16;  // particles per block
 
+// A launch may not reach 2^32 work-items, and a particle takes 16: calls of 2^28
+// particles and more (small grids, or I = 4 on the largest) go in slices of
+// half that, this launch's from particle first on.
+constexpr int64_t kDirSlice = (int64_t)1 << 27;
+static_assert(kDirSlice % kDirGroups == 0 && kDirSlice * 16 < (int64_t)1 << 32, "whole blocks, below 2^32 work-items");
+
+int64_t direct_slice(int64_t np, int64_t first, unsigned* blocks, int* threads) {
+  const int64_t n = np - first < kDirSlice ? np - first : kDirSlice;
+  *blocks = (unsigned)((n + kDirGroups - 1) / kDirGroups);
+  *threads = kDirThreads;
+  return n;
+}
+
 template <int ST, int I, bool GRAD>
-__global__ __launch_bounds__(kDirThreads) void k_direct(InterpArgs a, BinGeom g, uint32_t* keys) {
+__global__ __launch_bounds__(kDirThreads) void k_direct(InterpArgs a, BinGeom g, uint32_t* keys, int64_t first) {
   using V = typename StoreT<ST>::acc;
   const int l16 = threadIdx.x & 15, j = l16 & 7, h = l16 >> 3;
   const int jj = j < I ? j : I - 1;
-  const int64_t p0 = (int64_t)blockIdx.x * kDirGroups + (threadIdx.x >> 4);
+  const int64_t p0 = first + (int64_t)blockIdx.x * kDirGroups + (threadIdx.x >> 4);
   const bool active = p0 < a.np;  // (idle groups of the last block repeat its last particle: the row's DPP moves need every lane)
   const int64_t p = active ? p0 : a.np - 1;
   const int64_t row = a.xrow ? (int64_t)a.xrow[p] : p;
@@ -204,11 +217,11 @@ __global__ __launch_bounds__(kDirThreads) void k_direct(InterpArgs a, BinGeom g,
 // rounded binary64 one.  GRAD: the last step evaluates the gradient at its
 // start position.
 template <int ST, int I, bool GRAD>
-__global__ __launch_bounds__(kDirThreads) void k_direct_steps(InterpArgs a, DirectSteps s) {
+__global__ __launch_bounds__(kDirThreads) void k_direct_steps(InterpArgs a, DirectSteps s, int64_t first) {
   using V = typename StoreT<ST>::acc;
   const int l16 = threadIdx.x & 15, j = l16 & 7, h = l16 >> 3;
   const int jj = j < I ? j : I - 1;
-  const int64_t p0 = (int64_t)blockIdx.x * kDirGroups + (threadIdx.x >> 4);
+  const int64_t p0 = first + (int64_t)blockIdx.x * kDirGroups + (threadIdx.x >> 4);
   const bool active = p0 < a.np;
   const int64_t p = active ? p0 : a.np - 1;
   const int64_t row = a.xrow ? (int64_t)a.xrow[p] : p;
@@ -305,18 +318,24 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_steps(InterpArgs a, Dire
 template <int ST, int I>
 static hipError_t direct_one(const InterpArgs& a, const BinGeom& g, uint32_t* keys, const DirectSteps* st,
                              hipStream_t s) {
-  const unsigned grid = (unsigned)((a.np + kDirGroups - 1) / kDirGroups);
-  if (st) {
-    if (a.grad)
-      k_direct_steps<ST, I, true><<<grid, kDirThreads, 0, s>>>(a, *st);
-    else
-      k_direct_steps<ST, I, false><<<grid, kDirThreads, 0, s>>>(a, *st);
-  } else if (a.grad) {
-    k_direct<ST, I, true><<<grid, kDirThreads, 0, s>>>(a, g, keys);
-  } else {
-    k_direct<ST, I, false><<<grid, kDirThreads, 0, s>>>(a, g, keys);
+  for (int64_t first = 0, n; first < a.np; first += n) {
+    unsigned grid;
+    int threads;
+    n = direct_slice(a.np, first, &grid, &threads);
+    if (st) {
+      if (a.grad)
+        k_direct_steps<ST, I, true><<<grid, threads, 0, s>>>(a, *st, first);
+      else
+        k_direct_steps<ST, I, false><<<grid, threads, 0, s>>>(a, *st, first);
+    } else if (a.grad) {
+      k_direct<ST, I, true><<<grid, threads, 0, s>>>(a, g, keys, first);
+    } else {
+      k_direct<ST, I, false><<<grid, threads, 0, s>>>(a, g, keys, first);
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 template <int ST>

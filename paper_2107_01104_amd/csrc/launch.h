@@ -144,6 +144,9 @@ struct DirectSteps {
   double b[4][4];         // weights by order - 1
 };
 hipError_t launch_direct_steps(int storage, int I, const InterpArgs& a, const DirectSteps& st, hipStream_t s);
+// The launch that starts at particle `first` of np: its particles, blocks and
+// threads a block (host arithmetic only).
+int64_t direct_slice(int64_t np, int64_t first, unsigned* blocks, int* threads);
 
 // step.hip
 enum UpdateKind { kEulerOrPredict = 0, kHeunCorrect = 1, kAB = 2 };

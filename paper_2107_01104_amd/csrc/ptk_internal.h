@@ -174,6 +174,7 @@ struct ptk_ctx {
   void* noalloc = nullptr;   // device address of the no-allocation scratch array on this device
   size_t bytes_in_use = 0;
   size_t byte_cap = 0;      // 0 = unlimited (test hook PTK_TEST_MAX_BYTES)
+  int test_route = -1;      // test hook PTK_TEST_ROUTE: every launch's Route (api.hip), or -1 for the rule's
   bool check = true;        // PTK_NO_CHECK clears it
   // timing
   bool timing = false;
