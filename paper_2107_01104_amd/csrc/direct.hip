@@ -180,9 +180,8 @@ __global__ __launch_bounds__(kDirThreads) void k_direct(InterpArgs a, BinGeom g,
   using V = typename StoreT<ST>::acc;
   const int l16 = threadIdx.x & 15, j = l16 & 7, h = l16 >> 3;
   const int jj = j < I ? j : I - 1;
-  const int64_t p0 = first + (int64_t)blockIdx.x * kDirGroups + (threadIdx.x >> 4);
-  const bool active = p0 < a.np;  // (idle groups of the last block repeat its last particle: the row's DPP moves need every lane)
-  const int64_t p = active ? p0 : a.np - 1;
+  const int64_t p = first + (int64_t)blockIdx.x * kDirGroups + (threadIdx.x >> 4);
+  if (p >= a.np) return;  // (whole DPP rows: a particle's 16 lanes stay or leave together)
   const int64_t row = a.xrow ? (int64_t)a.xrow[p] : p;
   double x[3];
 #pragma unroll
@@ -195,7 +194,6 @@ __global__ __launch_bounds__(kDirThreads) void k_direct(InterpArgs a, BinGeom g,
   V r[3], u[3];
   direct_sums<ST, I, GRAD>(a, cv, cd, j, jj, h, x, r, c);
   share_value<ST, GRAD>(a, r, u);
-  if (!active) return;
   if (l16 == 0) {
     if (!ok) raise_flag(a.flag, kFlagDomain);
     if (keys) keys[p] = ok ? bin_key(c[0], c[1], c[2], g) : 0u;
@@ -221,9 +219,8 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_steps(InterpArgs a, Dire
   using V = typename StoreT<ST>::acc;
   const int l16 = threadIdx.x & 15, j = l16 & 7, h = l16 >> 3;
   const int jj = j < I ? j : I - 1;
-  const int64_t p0 = first + (int64_t)blockIdx.x * kDirGroups + (threadIdx.x >> 4);
-  const bool active = p0 < a.np;
-  const int64_t p = active ? p0 : a.np - 1;
+  const int64_t p = first + (int64_t)blockIdx.x * kDirGroups + (threadIdx.x >> 4);
+  if (p >= a.np) return;  // (before any read: positions and history are written in place)
   const int64_t row = a.xrow ? (int64_t)a.xrow[p] : p;
   double x[3];
 #pragma unroll
@@ -257,7 +254,7 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_steps(InterpArgs a, Dire
         table_row<I>(a.coef, 1, jj, cd);
         direct_sums<ST, I, true>(a, cv, cd, j, jj, h, x, r, c);
         share_value<ST, true>(a, r, k1);
-        if (active) write_grad<ST>(a, l16, r, a.grad_orig ? (int64_t)a.grad_orig[p] : p);
+        write_grad<ST>(a, l16, r, a.grad_orig ? (int64_t)a.grad_orig[p] : p);
         done = true;
       }
     }
@@ -303,7 +300,6 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_steps(InterpArgs a, Dire
       hl = min(hl + 1, s.depth);
     }
   }
-  if (!active) return;
   if (l16 == 0 && !ok) raise_flag(a.flag, kFlagDomain);
   if (l16 < 3) {
     s.X[3 * row + l16] = l16 == 0 ? x[0] : l16 == 1 ? x[1] : x[2];

@@ -54,3 +54,26 @@ def test_direct_calls_of_more_particles_than_a_launch_takes(ptk, monkeypatch):
     ctx.close()
     del X
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 31, 33])
+def test_direct_steps_at_the_edges_of_a_block(ptk, monkeypatch, n):
+    """70 AB3 steps (two launches) in place, history with them, against the same
+    particles among 64: a block takes 16 particles, and what its last lanes have
+    no particle for may not touch the others'."""
+    print(f"[routes] {n} particles, 70 steps", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(n)
+    u = torch.randn((16, 16, 16, 3), generator=g, device=DEV)
+    X0 = torch.rand((64, 3), generator=g, device=DEV, dtype=torch.float64) * L
+    ctx = context(ptk, monkeypatch, "direct")
+    ctx.set_field(u, ptk.SPLINE, 6, 1, storage=ptk.F32)
+
+    def run(X):
+        h = torch.zeros((3, X.shape[0], 3), device=DEV)
+        gr = torch.zeros((X.shape[0], 3, 3), device=DEV)
+        assert ctx.advance(X, ptk.AB3, 1e-3, 70, hist=h, grad_out=gr) == 3
+        return X, h, gr
+
+    a, b = run(X0.clone()), run(X0[:n].clone())
+    assert torch.equal(a[0][:n], b[0]) and torch.equal(a[1][:, :n], b[1]) and torch.equal(a[2][:n], b[2])
+    ctx.close()
