@@ -77,3 +77,57 @@ def test_direct_steps_at_the_edges_of_a_block(ptk, monkeypatch, n):
     a, b = run(X0.clone()), run(X0[:n].clone())
     assert torch.equal(a[0][:n], b[0]) and torch.equal(a[1][:, :n], b[1]) and torch.equal(a[2][:n], b[2])
     ctx.close()
+
+
+@pytest.mark.parametrize("kind,one_shot", [("tracers", False), ("tracers", True), ("axes", False), ("inertia", False)])
+@pytest.mark.parametrize("scheme", ["EULER", "HEUN", "AB3"])
+def test_steps_in_bin_order_keep_it(ptk, monkeypatch, kind, scheme, one_shot):
+    """Steps evaluated in bin order re-bin after each of them (but a one-shot
+    call's last), with the sweep's results bit for bit; a state that was not
+    sorted when it was loaded is sorted first."""
+    print(f"[routes] bin order kept: {kind} {scheme} one_shot={one_shot}", flush=True)
+    N, n, steps = 24, 9001, 7
+    g = torch.Generator(device=DEV).manual_seed(3)
+    u = torch.randn((N, N, N, 3), generator=g, device=DEV)
+    X0 = (torch.rand((n, 3), generator=g, device=DEV, dtype=torch.float64) * 3 - 1) * L
+    p0 = torch.nn.functional.normalize(torch.randn((n, 3), generator=g, device=DEV, dtype=torch.float64))
+    sch = getattr(ptk, scheme)
+    depth = ptk.AB_ORDER.get(sch, 0)
+
+    def run(route):
+        ctx = context(ptk, monkeypatch, route)
+        ctx.set_field(u, ptk.SPLINE, 8, 2, storage=ptk.F32)
+        X, p = X0.clone(), p0.clone()
+        h = torch.zeros((depth, n, 3), device=DEV) if depth else None
+        ph, vh = (torch.zeros((depth, n, 3), device=DEV, dtype=torch.float64) for _ in range(2))
+        gr = torch.zeros((n, 3, 3), device=DEV)
+        ctx.timing(True)
+        if one_shot:
+            ctx.advance(X, sch, 2e-2, steps, hist=h, grad_out=gr)
+        else:
+            ctx.particles_load(X, hist_depth=depth)
+            if kind == "axes":
+                ctx.particles_set_orientation(p, 0.7)
+            elif kind == "inertia":
+                ctx.particles_set_inertia(p, 0.2)
+            ctx.particles_advance(sch, 2e-2, 2)
+            ctx.particles_advance(sch, 2e-2, steps - 2, grad_out=gr)
+            ctx.particles_store(X, hist=h)
+            if kind == "axes":
+                ctx.particles_get_orientation(p, hist=ph)
+            elif kind == "inertia":
+                ctx.particles_get_inertia(p, v_hist=vh, r_hist=ph)
+        sorts = ctx.timing_read()["sort"][1]
+        ctx.close()
+        return sorts, [X, p, gr, ph, vh] + ([h] if depth else [])
+
+    sorts, a = run("sorted")
+    assert sorts == 1 + steps - (1 if one_shot else 0)
+    swept, b = run("sweep")
+    assert swept == sorts + (steps if scheme == "HEUN" else 0)  # (the predictor's bins too)
+    for x, y in zip(a, b):
+        assert torch.equal(x, y)
+    none, d = run("direct")
+    assert none == 0
+    for x, y in zip(a, d):
+        assert torch.equal(x, y)
