@@ -1,20 +1,59 @@
 """The ways a call's particles are evaluated (straight from the field, the same
 in bin order, the binned sweep), where a call's size or shape changes them.
-PTK_TEST_ROUTE, read when a context is made, takes the choice from the rule."""
+PTK_TEST_ROUTE, read when a context is made, takes the choice from the rule.
+
+The kernels add in the same order, so the routes agree bit for bit; the oracle
+tests' calls are small and mostly read directly, and through this equality they
+hold for the sweep too.  (Every case forces its routes: what the rule would
+choose plays no part.)"""
 import numpy as np
 import pytest
 import torch
 
-from oracle import geometry
+from oracle import geometry, kernels as K
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 L = geometry.L
 
 
+ROUTES = ("direct", "sorted", "sweep")
+KERNELS = [(K.LAGRANGE, 4, 0), (K.SPLINE, 6, 1), (K.SPLINE, 8, 2)]
+
+
 @pytest.fixture(scope="module")
 def ptk(lib):
     return lib
+
+
+def field(N, seed, storage):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    return torch.randn((N, N, N, 3), generator=g, device=DEV,
+                       dtype=torch.float64 if storage == "f64" else torch.float32) + 0.5
+
+
+def positions(N, n, seed):
+    """Uniform over three periods, the first ones on nodes, faces and just below them."""
+    rng = np.random.default_rng(seed)
+    X = rng.uniform(-L, 2 * L, (n, 3))
+    e = np.array([0.0, -0.0, L, -L, np.nextafter(L, 0), np.nextafter(0, -1), 12 * L / N, np.nextafter(12 * L / N, 0),
+                  (N - 1) * L / N, 5 * L / N, np.pi])
+    X[:200] = rng.choice(e, (min(n, 200), 3))
+    return torch.from_numpy(X).to(DEV)
+
+
+def same(a, b):
+    """Bit for bit, NaN for NaN."""
+    return torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(torch.nan_to_num(a), torch.nan_to_num(b))
+
+
+def evaluations(ctx, X, out_dtypes=(torch.float32, torch.float64)):
+    res = []
+    for out in out_dtypes:
+        res += [ctx.interpolate(X, out_dtype=out), *ctx.interpolate_gradient(X, out_dtype=out),
+                ctx.interpolate_gradient(X, out_dtype=out, with_value=False)[1]]
+        res.append(ctx.interpolate_noalloc(X, torch.full_like(res[-4], float("nan"))))
+    return res
 
 
 def context(ptk, monkeypatch, route):
@@ -131,3 +170,146 @@ def test_steps_in_bin_order_keep_it(ptk, monkeypatch, kind, scheme, one_shot):
     assert none == 0
     for x, y in zip(a, d):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "bf16", "f16"])
+@pytest.mark.parametrize("fam,I,m", KERNELS)
+@pytest.mark.parametrize("N", [8, 9, 12, 13, 67])
+def test_routes_agree(ptk, monkeypatch, storage, fam, I, m, N):
+    """Grids below, at and beyond a tile's edge; a particle, a ragged count and
+    (swept, with several chunks in every window) a crowd."""
+    print(f"[routes] {storage} I={I} N={N}", flush=True)
+    u = field(N, N + I, storage)
+    for n in (1, 3001, 40_000):
+        X = positions(N, n, n + I)
+        ref = None
+        for route in ROUTES:
+            ctx = context(ptk, monkeypatch, route)
+            ctx.set_field(u, fam, I, m, storage=getattr(ptk, storage.upper()))
+            got = evaluations(ctx, X)
+            ctx.close()
+            ref = ref or got
+            for a, b in zip(got, ref):
+                assert torch.equal(a, b), (n, route)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+@pytest.mark.parametrize("fam,I,m", KERNELS)
+def test_routes_agree_on_infinities_and_nan(ptk, monkeypatch, storage, fam, I, m):
+    print(f"[routes] non-finite nodes, {storage} I={I}", flush=True)
+    N, n = 29, 20_000
+    u = field(N, I, storage)
+    rng = np.random.default_rng(I)
+    for bad in (float("inf"), float("-inf"), float("nan")):
+        i = torch.from_numpy(rng.integers(0, N, (4, 3))).to(DEV)
+        u[i[:, 0], i[:, 1], i[:, 2], int(rng.integers(0, 3))] = bad
+    X = positions(N, n, I)
+    ref = None
+    for route in ROUTES:
+        ctx = context(ptk, monkeypatch, route)
+        ctx.set_field(u, fam, I, m, storage=getattr(ptk, storage.upper()))
+        got = evaluations(ctx, X, (torch.float64,))
+        ctx.close()
+        ref = ref or got
+        for a, b in zip(got, ref):
+            assert same(a, b), route
+    assert bool(torch.isnan(ref[0]).any()) and bool(torch.isfinite(ref[0]).any())
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("fam,I,m", KERNELS)
+def test_crowded_windows_beside_empty_ones(ptk, monkeypatch, storage, fam, I, m):
+    """130^3: segments of three windows of five layers (the last of two), 160
+    particles a chunk.  Windows with nothing, one particle, and counts at the
+    edges of one, two and many chunks, first, in the middle and last in their
+    segment."""
+    print(f"[routes] crowded windows, {storage} I={I}", flush=True)
+    N = 130
+    u = field(N, I, storage)
+    rng = np.random.default_rng(I)
+    counts = [0, 0, 1000, 161, 0, 0, 0, 320, 0, 159, 160, 161, 0, 0, 0, 1, 0, 321, 2000, 2000, 1, 0, 1, 0, 481, 1999]
+    assert len(counts) == -(-N // 5)
+    rows = []
+    for column in ((0, 0), (0, 10), (7, 3), (10, 10)):  # the last columns are ten cells wide
+        for w, c in enumerate(counts if column != (7, 3) else counts[::-1]):
+            lo = np.array([12 * column[0], 12 * column[1], 5 * w])
+            hi = np.minimum(lo + [12, 12, 5], N)
+            rows.append(rng.uniform(lo, hi, (c, 3)))
+    X = np.concatenate(rows)
+    X = torch.from_numpy(rng.permutation(X) * (L / N)).to(DEV)
+    ref = None
+    for route in ROUTES:
+        ctx = context(ptk, monkeypatch, route)
+        ctx.set_field(u, fam, I, m, storage=getattr(ptk, storage.upper()))
+        got = evaluations(ctx, X, (torch.float32,))
+        ctx.close()
+        ref = ref or got
+        for a, b in zip(got, ref):
+            assert torch.equal(a, b), route
+
+
+@pytest.mark.parametrize("route", ROUTES)
+@pytest.mark.parametrize("N,n", [(8, 0), (16, 1), (16, 2047), (16, 2048), (16, 2049), (24, 70_001), (60, 500_001)])
+def test_permutation_on_every_route(ptk, monkeypatch, route, N, n):
+    """The recorded binning is the stable order of the keys, however often it is
+    asked for and whatever a resident state does in between; single tiles,
+    their edges, one and two digit passes."""
+    print(f"[routes] binning, {route} N={N} n={n}", flush=True)
+    ctx = context(ptk, monkeypatch, route)
+    ctx.set_field(field(N, 1, "f32"), ptk.LAGRANGE, 4, 0, storage=ptk.F32)
+    rng = np.random.default_rng(n)
+    cells = rng.integers(0, N, (n, 3))
+    X = torch.from_numpy((cells + 0.5) * (L / N)).to(DEV)
+    ctx.particles_load(positions(N, 500, 2), hist_depth=2)
+    ctx.interpolate(X)
+    for _ in range(2):
+        perm, off, T, W = ctx.binning()
+        nt, nw = -(-N // T), -(-N // W)
+        key = ((cells[:, 1] // T) * nt + cells[:, 0] // T) * nw + cells[:, 2] // W
+        np.testing.assert_array_equal(perm.cpu().numpy(), np.argsort(key, kind="stable"))
+        np.testing.assert_array_equal(off.cpu().numpy()[1:], np.cumsum(np.bincount(key, minlength=nt * nt * nw)))
+        ctx.particles_advance(ptk.AB2, 1e-2, 2)
+    ctx.close()
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+@pytest.mark.parametrize("scheme", ["EULER", "HEUN", "AB2", "AB4"])
+def test_many_movers_on_every_route(ptk, monkeypatch, storage, scheme):
+    """Steps of about a cell: most particles change bins at each, the history
+    with them.  One-shot calls, resident ones, and a field of two times."""
+    print(f"[routes] many movers, {storage} {scheme}", flush=True)
+    N, n, dt = 26, 30_011, L / 26
+    u, u2 = field(N, 4, storage), field(N, 5, storage)
+    X0 = positions(N, n, 7)
+    sch = getattr(ptk, scheme)
+    depth = ptk.AB_ORDER.get(sch, 0)
+
+    def run(route):
+        ctx = context(ptk, monkeypatch, route)
+        ctx.set_field(u, K.SPLINE, 6, 1, storage=getattr(ptk, storage.upper()))
+        v = ctx.vel_dtype()
+        res = []
+        for resident in (False, True):
+            X, g = X0.clone(), torch.zeros((n, 3, 3), dtype=v, device=DEV)
+            h = torch.zeros((depth, n, 3), dtype=v, device=DEV) if depth else None
+            if resident:
+                ctx.particles_load(X, hist_depth=depth)
+                ctx.particles_advance(sch, dt, 5, grad_out=g)
+                assert ctx.particles_store(X, hist=h) == depth
+            else:
+                assert ctx.advance(X, sch, dt, 5, hist=h, grad_out=g) == depth
+            res += [X, g] + ([h] if depth else [])
+        g = torch.zeros((n, 3, 3), dtype=v, device=DEV)
+        X = torch.empty_like(X0)
+        for f in (u2, u, u2):
+            ctx.set_field_next(f)
+            ctx.particles_step_next_field(dt, grad_out=g)
+            ctx.particles_store(X, hist=h)
+            res += [X.clone(), g.clone()]
+        ctx.close()
+        return res
+
+    ref = run("direct")
+    for route in ("sorted", "sweep"):
+        for i, (a, b) in enumerate(zip(run(route), ref)):
+            assert torch.equal(a, b), (route, i)
