@@ -40,6 +40,16 @@ template <typename R>
 struct alignas(2 * sizeof(R)) Cx {
   R x, y;
 };
+// A number of a buffer that is aligned as its real and imaginary parts are, which
+// is all the caller's spectrum has to be (one load either way).
+template <typename R>
+__device__ __forceinline__ Cx<R> load(const Cx<R>* p) {
+  struct Parts {
+    R x, y;
+  };
+  const Parts v = *(const Parts*)p;
+  return {v.x, v.y};
+}
 template <typename R>
 __device__ __forceinline__ Cx<R> operator+(Cx<R> a, Cx<R> b) {
   return {a.x + b.x, a.y + b.y};
@@ -263,8 +273,8 @@ __global__ __launch_bounds__((kCols<N, R> * (N / kColE<N, R>))) void k_fft_cols(
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const Cx<R>* s = src + in_index<N, P::r1>(t + e / P::r1 * T, e % P::r1) * in_row;
-      wb[e] = s[b - a];
-      wd[e] = s[d - a];
+      wb[e] = load(s + (b - a));
+      wd[e] = load(s + (d - a));
     }
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -283,7 +293,7 @@ __global__ __launch_bounds__((kCols<N, R> * (N / kColE<N, R>))) void k_fft_cols(
     }
   } else {
 #pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = src[in_index<N, P::r1>(t + e / P::r1 * T, e % P::r1) * in_row];
+    for (int e = 0; e < E; ++e) v[e] = load(src + in_index<N, P::r1>(t + e / P::r1 * T, e % P::r1) * in_row);
   }
   transform<N, E, N, NC>(v, lds + c, t, tw);
   if (!active) return;
