@@ -433,7 +433,7 @@ int interp_core(ptk_ctx* c, const InterpScratch& w, const double* X, int64_t Np,
     else
       PTK_HIP(c,
               launch_direct(c->storage, c->I, a, bg,
-                            record && route == Route::kDirect ? (uint32_t*)c->bin_keys.ptr : nullptr, s),
+                            record && route == Route::kDirect ? w.keys_b : nullptr, s),
               "interpolate");
   }
   if (record) {
@@ -460,10 +460,6 @@ int interp_common(ptk_ctx* c, const double* X, int64_t Np, void* u_out, void* gr
   } else {
     PTK_TRY(ensure_binning(c, Np, n_bins));
     PTK_TRY(check_binning_caps(c, Np, n_bins));
-    if (route_of(c, Np, grad != nullptr) == Route::kDirect) {
-      PTK_TRY(ensure(c, c->bin_keys, (size_t)Np * 4));
-      PTK_TRY(need(c, c->bin_keys, (size_t)Np * 4, "bin keys"));
-    }
   }
   PTK_TRY(need(c, c->offsets, (size_t)(n_bins + 1) * 4, "bin offsets"));
   InterpScratch w{(uint32_t*)c->keys_a.ptr, (uint32_t*)c->keys_b.ptr, (uint32_t*)c->vals_a.ptr,
@@ -640,7 +636,7 @@ void ptk_destroy(ptk_ctx* c) {
   {
     DeviceGuard g(c->device);
     (void)hipDeviceSynchronize();
-    DevBuf* bufs[] = {&c->field, &c->field_next, &c->coef, &c->bin_keys, &c->keys_a, &c->keys_b, &c->vals_a, &c->vals_b, &c->offsets,
+    DevBuf* bufs[] = {&c->field, &c->field_next, &c->coef, &c->keys_a, &c->keys_b, &c->vals_a, &c->vals_b, &c->offsets,
                       &c->hist, &c->xs, &c->xn, &c->orig, &c->orig_b, &c->k1,
                       &c->k2, &c->abh[0], &c->abh[1], &c->abh[2], &c->abh[3], &c->abh_b[0], &c->abh_b[1],
                       &c->abh_b[2], &c->abh_b[3], &c->gint, &c->stage, &c->lparams,
@@ -1000,12 +996,19 @@ int ptk_get_binning(ptk_ctx* c, uint32_t* perm, uint32_t* offsets, void* stream)
   DeviceGuard g(c->device);
   hipStream_t s = S(stream);
   if (c->bin_from_keys) {
-    // (sorted from a copy, so that a further call finds the keys)
     PTK_TRY(check_binning_caps(c, c->bin_np, c->bin_nbins));
+    uint32_t *ka = (uint32_t*)c->keys_a.ptr, *kb = (uint32_t*)c->keys_b.ptr, *sk = nullptr;
     PTK_HIP(c,
-            hipMemcpyAsync(c->keys_a.ptr, c->bin_keys.ptr, (size_t)c->bin_np * 4, hipMemcpyDeviceToDevice, s),
-            "copy keys");
-    PTK_TRY(bin_sorted(c, c->bin_np, c->bin_nbins, false, &c->bin_perm, s));
+            radix_sort_keys(kb, ka, (uint32_t*)c->vals_a.ptr, (uint32_t*)c->vals_b.ptr, c->bin_np, nullptr, false,
+                            bits_for(c->bin_nbins), (uint32_t*)c->hist.ptr, false, &sk, &c->bin_perm, s),
+            "radix sort");
+    PTK_HIP(c, launch_offsets(sk, c->bin_np, c->bin_nbins, (uint32_t*)c->offsets.ptr, s), "bin offsets");
+    // the keys back to the caller's order, where a further call (or the replay of
+    // a captured one) finds them
+    uint32_t* back = sk == kb ? ka : kb;
+    PTK_HIP(c, scatter_u32(sk, c->bin_perm, c->bin_np, back, s), "keep keys");
+    if (back != kb)
+      PTK_HIP(c, hipMemcpyAsync(kb, back, (size_t)c->bin_np * 4, hipMemcpyDeviceToDevice, s), "keep keys");
   }
   if (c->bin_np > 0)
     PTK_HIP(c, hipMemcpyAsync(perm, c->bin_perm, (size_t)c->bin_np * 4, hipMemcpyDeviceToDevice, s), "copy perm");

@@ -340,6 +340,13 @@ __global__ __launch_bounds__(256) void k_gather_u32(const uint32_t* __restrict__
   out[k] = in[perm[k]];
 }
 
+__global__ __launch_bounds__(256) void k_scatter_u32(const uint32_t* __restrict__ in,
+                                                     const uint32_t* __restrict__ perm, int64_t n,
+                                                     uint32_t* __restrict__ out) {
+  int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (k >= n) return;
+  out[perm[k]] = in[k];
+}
 
 // ---------------------------------------------------------------------------
 // incremental re-binning (particles move less than a cell per step, so few
@@ -638,6 +645,12 @@ hipError_t gather3_f32(const float* in, const uint32_t* perm, int64_t n, float* 
 hipError_t gather_u32(const uint32_t* in, const uint32_t* perm, int64_t n, uint32_t* out, hipStream_t s) {
   if (n == 0) return hipSuccess;
   k_gather_u32<<<blocks_for(n, 256), 256, 0, s>>>(in, perm, n, out);
+  return hipGetLastError();
+}
+
+hipError_t scatter_u32(const uint32_t* in, const uint32_t* perm, int64_t n, uint32_t* out, hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  k_scatter_u32<<<blocks_for(n, 256), 256, 0, s>>>(in, perm, n, out);
   return hipGetLastError();
 }
 

@@ -53,6 +53,7 @@ hipError_t launch_offsets(const uint32_t* skeys, int64_t n, int64_t n_bins, uint
 hipError_t gather3_f64(const double* in, const uint32_t* perm, int64_t n, double* out, hipStream_t s);
 hipError_t gather3_f32(const float* in, const uint32_t* perm, int64_t n, float* out, hipStream_t s);
 hipError_t gather_u32(const uint32_t* in, const uint32_t* perm, int64_t n, uint32_t* out, hipStream_t s);
+hipError_t scatter_u32(const uint32_t* in, const uint32_t* perm, int64_t n, uint32_t* out, hipStream_t s);
 // rows of `width` elements, 3 or 9
 hipError_t scatter_f64(const double* in, const uint32_t* idx, int64_t n, int width, double* out,
                        hipStream_t s);

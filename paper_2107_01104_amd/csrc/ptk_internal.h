@@ -104,10 +104,10 @@ struct ptk_ctx {
   int64_t bin_np = 0, bin_nbins = 0;
   uint32_t* bin_perm = nullptr;
   bool bin_valid = false;
-  // the last call evaluated its particles without binning them: their keys
-  // are in bin_keys, and ptk_get_binning sorts them when it is asked
+  // the last call evaluated its particles without binning them: their keys are
+  // in keys_b (which steps of a resident state leave alone), and
+  // ptk_get_binning sorts them when it is asked
   bool bin_from_keys = false;
-  ptk::DevBuf bin_keys;
   // scratch
   ptk::DevBuf keys_a, keys_b, vals_a, vals_b, offsets, hist;
   // status words in pinned host memory: two for the calls, two for the learned

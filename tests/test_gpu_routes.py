@@ -313,3 +313,60 @@ def test_many_movers_on_every_route(ptk, monkeypatch, storage, scheme):
     for route in ("sorted", "sweep"):
         for i, (a, b) in enumerate(zip(run(route), ref)):
             assert torch.equal(a, b), (route, i)
+
+
+@pytest.mark.parametrize("route", ROUTES)
+def test_scratch_of_a_call(ptk, monkeypatch, route):
+    """A call needs its four arrays of keys and values, the histogram and the
+    offsets, however its particles are evaluated: it fits a device-memory cap
+    that leaves room for no fifth array of 4 bytes a particle."""
+    N, n = 16, 100_003
+    print(f"[routes] scratch, {route}", flush=True)
+    grown = lambda b: (b + b // 8 + 255) // 256 * 256
+    row = ((N + 3) * 12 + 48 + 63) // 64 * 64
+    cap = grown(row * (N + 3) ** 2 + 64) + 4 * grown(4 * n) + grown(4 * 256 * -(-n // 2048)) + (64 << 10)
+    monkeypatch.setenv("PTK_TEST_MAX_BYTES", str(cap))
+    ctx = context(ptk, monkeypatch, route)
+    monkeypatch.delenv("PTK_TEST_MAX_BYTES")
+    ctx.set_field(field(N, 1, "f32"), ptk.LAGRANGE, 4, 0, storage=ptk.F32)
+    X = positions(N, n, 3)
+    ctx.interpolate(X)
+    ctx.interpolate_gradient(X)
+    keys = geometry.bin_keys(X.cpu().numpy(), N, 12, 5)
+    for _ in range(2):
+        assert np.array_equal(ctx.binning()[0].cpu().numpy(), geometry.stable_order(keys))
+    ctx.close()
+
+
+@pytest.mark.parametrize("route", ROUTES)
+@pytest.mark.parametrize("N", [16, 60])
+def test_captured_binning_query(ptk, monkeypatch, route, N):
+    """ptk_get_binning recorded in a graph (one and two digit passes): every
+    replay gives the binning of the last call, as the eager query between them."""
+    n = 5003
+    print(f"[routes] captured binning query, {route} N={N}", flush=True)
+    ctx = context(ptk, monkeypatch, route)
+    ctx.set_field(field(N, 1, "f32"), ptk.LAGRANGE, 4, 0, storage=ptk.F32)
+    X = positions(N, n, 1)
+    ctx.interpolate(X)
+    perm = torch.zeros(n, dtype=torch.int32, device=DEV)
+    off = torch.zeros(geometry.n_bins(N, 12, 5) + 1, dtype=torch.int32, device=DEV)
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        assert ptk.lib.ptk_get_binning(ctx._h, perm.data_ptr(), off.data_ptr(), side.cuda_stream) == ptk.OK
+    for rep in range(4):
+        if rep == 2:
+            X = positions(N, n, 2)
+            ctx.interpolate(X)
+        order = geometry.stable_order(geometry.bin_keys(X.cpu().numpy(), N, 12, 5))
+        perm.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(perm.cpu().numpy(), order), rep
+        eager, eoff, _, _ = ctx.binning()
+        assert np.array_equal(eager.cpu().numpy(), order), rep
+        assert torch.equal(off, eoff)
+    ctx.close()
