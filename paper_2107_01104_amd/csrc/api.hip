@@ -828,7 +828,8 @@ int ensure_transform(ptk_ctx* c, int64_t N, int f64, hipStream_t s) {
 
 // Stores the field of a half spectrum.  Grids the library's own transform is
 // built for take its three passes, straight into the stored rows (16-bit
-// storage, whose scale is the whole field's rms, by way of the plain grid);
+// storage, whose scale is the whole field's rms, by way of the grid values, in the
+// transform's buffer);
 // others go through rocFFT's planes.  Measured with FP64 vorticity
 // into FP32 storage: 64^3 172 us by rocFFT, 157 so; 128^3 185 and 166; 256^3
 // 1041 and 570; 512^3 7.68 ms and 4.33; 1024^3 81.5 and 33.9; into BF16 512^3
@@ -843,17 +844,15 @@ int store_spectrum(ptk_ctx* c, const void* spec, int64_t N, int f64, int kind, i
   const SpecSource src{spec, f64, kind == PTK_SPEC_VORTICITY};
   if (storage == PTK_F64 || storage == PTK_F32)
     return store_field(c, nullptr, f64, interleaved_layout(N), N, storage, k, m, tab, s, next_field, &src);
-  const size_t rb = f64 ? 8 : 4, grid = 3 * (size_t)N * (size_t)N * (size_t)N * rb;
-  PTK_TRY(ensure(c, c->fft_out, grid));
-  PTK_TRY(need(c, c->fft_out, grid, "transform output"));
+  // the real rows over the amplitudes they come from
+  const int64_t rb = f64 ? 8 : 4, row = 2 * spec_transform_row(N, f64);  // real numbers
   {
     Timed t(c, s, PTK_T_IFT);
-    const int64_t row = N * 3 * (int64_t)rb;
-    const SpecTransform p{spec, c->spec.ptr, c->twiddles.ptr, spec_transform_row(N, f64), c->fft_out.ptr, row,
-                          row * N, (int)N, 0, f64};
+    const SpecTransform p{spec, c->spec.ptr, c->twiddles.ptr, spec_transform_row(N, f64), c->spec.ptr, row * rb,
+                          row * rb * N, (int)N, 0, f64};
     PTK_HIP(c, launch_spec_transform(p, N, f64, src.vorticity, s), "transform");
   }
-  return store_field(c, c->fft_out.ptr, f64, interleaved_layout(N), N, storage, k, m, tab, s, next_field);
+  return store_field(c, c->spec.ptr, f64, SrcLayout{1, 3, row, row * N}, N, storage, k, m, tab, s, next_field);
 }
 
 }  // namespace

@@ -7,8 +7,8 @@
 //   k_fft_cols along k2, in place: [x3][x2][k1][a];
 //   k_fft_rows along k1: each row's three components to real values, written
 //     as the stored field's padded, interleaved rows with their periodic
-//     copies (FP64 and FP32 storage), or as the plain grid (16-bit storage,
-//     whose scale needs the whole field first).
+//     copies (FP64 and FP32 storage), or over the row's own amplitudes as grid
+//     values (16-bit storage, whose scale needs the whole field first).
 //
 // The components stay interleaved throughout, as the caller and the stored
 // field have them.  Bound by HBM: each pass reads and writes the amplitudes
@@ -308,22 +308,22 @@ template <int N>
 constexpr int kRows = N >= 1024 ? 1 : N == 512 ? 2 : N == 256 ? 4 : N == 128 ? 8 : 16;
 
 // The stored rows the real rows go to: the padded field (F the storage type),
-// row (x3, x2) at each of its periodic places; or the plain grid
-// [x3][x2][x1][3] in R (halo 0, no copies).
+// row (x3, x2) at each of its periodic places; or the grid values in R, each row
+// at the place of its amplitudes (halo 0, no copies).
 struct RowsOut {
   void* field;
   int64_t row_pitch, plane_pitch;  // bytes
-  int P, lo;                       // padded extent and nodes below the grid (N and 0: plain)
+  int P, lo;                       // padded extent and nodes below the grid (N and 0: in place)
 };
 
 // Real rows of length N from their N/2 + 1 amplitudes [k1][a]: a complex
 // transform of length M = N/2 of Z_k = (X_k + conj X_{M-k}) + i exp(2 pi i k/N)
 // (X_k - conj X_{M-k}), whose real and imaginary parts are the even and odd
 // values.  (The imaginary parts of X_0 and X_M, which a Hermitian spectrum does
-// not have, are left out.)
+// not have, are left out.)  A workgroup's rows are in LDS before it writes any.
 template <typename R, int N, typename F>
 __global__ __launch_bounds__((kRows<N> * 3 * (N / 2 / kRowE))) void k_fft_rows(
-    const Cx<R>* __restrict__ in, int64_t in_row, RowsOut o, const Cx<R>* __restrict__ tw) {
+    const Cx<R>* in, int64_t in_row, RowsOut o, const Cx<R>* __restrict__ tw) {
   constexpr int M = N / 2;
   using P = Plan<M>;
   constexpr int E = kRowE, T = M / E, RW = kRows<N>, NT = RW * 3 * T, ROW = 6 * (M + 1);

@@ -47,3 +47,28 @@ def test_spectrum_aligned_as_a_real_number(ptk, N, prec, kind):
     ctx.particles_step_next_field(0.0)
     assert torch.equal(ctx.get_field(), ref)
     ctx.close()
+
+
+@pytest.mark.parametrize("storage", ["F64", "F32", "BF16", "F16"])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("N", [64, 128])
+def test_device_memory_of_a_transform(ptk, monkeypatch, N, prec, storage):
+    """Beside the field, the transform takes its own buffer alone (rows of the
+    half spectrum on whole 128-byte lines) and small tables: it fits a cap that
+    leaves room for no grid of real values."""
+    print(f"[spectrum] memory, N={N} {prec} -> {storage}", flush=True)
+    grown = lambda b: (b + b // 8 + 255) // 256 * 256
+    cb = 16 if prec == "f64" else 8
+    node = {"F64": 24, "F32": 12}.get(storage, 6)
+    row = ((N + 7) * node + 48 + 63) // 64 * 64
+    cap = grown(N * N * (-(-3 * (N // 2 + 1) * cb // 128) * 128)) + grown(row * (N + 7) ** 2 + 64) + (256 << 10)
+    spec = spectrum(N, prec)
+    ref = ptk.Context(0)
+    ref.set_field_spectral(spec, ptk.SPLINE, 8, 2, storage=getattr(ptk, storage))
+    monkeypatch.setenv("PTK_TEST_MAX_BYTES", str(cap))
+    ctx = ptk.Context(0)
+    monkeypatch.delenv("PTK_TEST_MAX_BYTES")
+    ctx.set_field_spectral(spec, ptk.SPLINE, 8, 2, storage=getattr(ptk, storage))
+    assert torch.equal(ctx.get_field(), ref.get_field()) and ctx.field_scale() == ref.field_scale()
+    ctx.close()
+    ref.close()
