@@ -682,6 +682,10 @@ int check_field_args(ptk_ctx* c, int64_t N, int in_dtype, int storage_dtype, con
   return PTK_OK;
 }
 
+const void* twiddles(const ptk_ctx* c, int64_t N, int f64) {
+  return (const char*)c->twiddles.ptr + spec_twiddle_offset(N, f64);
+}
+
 // A half spectrum that the library's own transform writes into the field.
 struct SpecSource {
   const void* spec;
@@ -736,9 +740,9 @@ int store_field(ptk_ctx* c, const void* u, int in_f64, const SrcLayout& l, int64
     if (!spec)
       return launch_pack(u, in_f64, l, N, storage_dtype, k->I, field, geo.row_pitch, geo.plane_pitch, inv, s);
     Timed t(c, s, PTK_T_IFT);
-    const SpecTransform p{spec->spec,    c->spec.ptr,     c->twiddles.ptr, spec_transform_row(N, spec->f64),
-                          field,         geo.row_pitch,   geo.plane_pitch, (int)geo.P,
-                          geo.halo_lo,   storage_dtype == PTK_F64};
+    const SpecTransform p{spec->spec,  c->spec.ptr,   twiddles(c, N, spec->f64), spec_transform_row(N, spec->f64),
+                          field,       geo.row_pitch, geo.plane_pitch,           (int)geo.P,
+                          geo.halo_lo, storage_dtype == PTK_F64};
     return launch_spec_transform(p, N, spec->f64, spec->vorticity, s);
   };
   if (next_field) {
@@ -802,27 +806,23 @@ int spectrum_to_grid(ptk_ctx* c, const void* spec, int64_t N, int f64, int kind,
   return PTK_OK;
 }
 
-// Buffers and twiddles of the library's own transform of (N, precision).
-int ensure_transform(ptk_ctx* c, int64_t N, int f64, hipStream_t s) {
-  const size_t cb = f64 ? 16 : 8;
+// Buffer and twiddles of the library's own transform of (N, precision).
+int ensure_transform(ptk_ctx* c, int64_t N, int f64) {
+  const size_t cb = f64 ? 16 : 8, tb = spec_twiddle_bytes();
   const size_t mid = (size_t)N * (size_t)N * (size_t)spec_transform_row(N, f64) * cb;
   PTK_TRY(ensure(c, c->spec, mid));
   PTK_TRY(need(c, c->spec, mid, "transform buffer"));
-  if (c->tw_N != N || c->tw_f64 != f64) {
-    c->tw_N = 0;
-    PTK_TRY(ensure(c, c->twiddles, (size_t)N * cb));
-    PTK_TRY(need(c, c->twiddles, (size_t)N * cb, "twiddles"));
-    try {
-      c->tw_host.resize((size_t)N * 2);
-    } catch (const std::bad_alloc&) {
-      return fail(c, PTK_ENOMEM, "host allocation failed");
-    }
-    spec_twiddles(N, f64, c->tw_host.data());
-    PTK_HIP(c, hipMemcpyAsync(c->twiddles.ptr, c->tw_host.data(), (size_t)N * cb, hipMemcpyHostToDevice, s),
-            "twiddle upload");
-    c->tw_N = N;
-    c->tw_f64 = f64;
-  }
+  if (c->have_twiddles) return PTK_OK;
+  PTK_TRY(ensure(c, c->twiddles, tb));
+  PTK_TRY(need(c, c->twiddles, tb, "twiddles"));
+  char* host = new (std::nothrow) char[tb];
+  if (!host) return fail(c, PTK_ENOMEM, "host allocation failed");
+  spec_twiddles(host);
+  // (not on the caller's stream: a capture would only record the copy)
+  const hipError_t e = hipMemcpy(c->twiddles.ptr, host, tb, hipMemcpyHostToDevice);
+  delete[] host;
+  PTK_HIP(c, e, "twiddle upload");
+  c->have_twiddles = true;
   return PTK_OK;
 }
 
@@ -840,7 +840,7 @@ int store_spectrum(ptk_ctx* c, const void* spec, int64_t N, int f64, int kind, i
     PTK_TRY(spectrum_to_grid(c, spec, N, f64, kind, s));
     return store_field(c, c->fft_out.ptr, f64, transform_layout(N), N, storage, k, m, tab, s, next_field);
   }
-  PTK_TRY(ensure_transform(c, N, f64, s));
+  PTK_TRY(ensure_transform(c, N, f64));
   const SpecSource src{spec, f64, kind == PTK_SPEC_VORTICITY};
   if (storage == PTK_F64 || storage == PTK_F32)
     return store_field(c, nullptr, f64, interleaved_layout(N), N, storage, k, m, tab, s, next_field, &src);
@@ -848,8 +848,8 @@ int store_spectrum(ptk_ctx* c, const void* spec, int64_t N, int f64, int kind, i
   const int64_t rb = f64 ? 8 : 4, row = 2 * spec_transform_row(N, f64);  // real numbers
   {
     Timed t(c, s, PTK_T_IFT);
-    const SpecTransform p{spec, c->spec.ptr, c->twiddles.ptr, spec_transform_row(N, f64), c->spec.ptr, row * rb,
-                          row * rb * N, (int)N, 0, f64};
+    const SpecTransform p{spec,     c->spec.ptr,  twiddles(c, N, f64), spec_transform_row(N, f64), c->spec.ptr,
+                          row * rb, row * rb * N, (int)N,              0,                          f64};
     PTK_HIP(c, launch_spec_transform(p, N, f64, src.vorticity, s), "transform");
   }
   return store_field(c, c->spec.ptr, f64, SrcLayout{1, 3, row, row * N}, N, storage, k, m, tab, s, next_field);

@@ -406,22 +406,34 @@ hipError_t run_fft(const SpecTransform& p, bool vort, hipStream_t s) {
 
 bool spec_transform_built(int64_t N) { return N == 64 || N == 128 || N == 256 || N == 512 || N == 1024; }
 
+constexpr int64_t kTwiddles = 64 + 128 + 256 + 512 + 1024;
+
 // complex numbers per row of the intermediate: rows start on 128-byte lines
 int64_t spec_transform_row(int64_t N, int f64) {
   const int64_t line = f64 ? 8 : 16;
   return (3 * (N / 2 + 1) + line - 1) / line * line;
 }
 
-void spec_twiddles(int64_t N, int f64, void* host) {
-  for (int64_t j = 0; j < N; ++j) {
-    const long double w = 6.283185307179586476925286766559L * (long double)j / (long double)N;
+// Tables of every length, FP64 then FP32 ones: length N's starts N - 64 numbers
+// into its precision's (64 + 128 + .. + N/2 = N - 64).
+size_t spec_twiddle_bytes() { return (size_t)kTwiddles * (16 + 8); }
+
+size_t spec_twiddle_offset(int64_t N, int f64) {
+  return f64 ? (size_t)(N - 64) * 16 : (size_t)kTwiddles * 16 + (size_t)(N - 64) * 8;
+}
+
+void spec_twiddles(void* host) {
+  for (int64_t j = 0; j < 1024; ++j) {
+    const long double w = 6.283185307179586476925286766559L * (long double)j / 1024.0L;
     const long double c = cosl(w), s = sinl(w);
-    if (f64) {
-      ((double*)host)[2 * j] = (double)c;
-      ((double*)host)[2 * j + 1] = (double)s;
-    } else {
-      ((float*)host)[2 * j] = (float)c;
-      ((float*)host)[2 * j + 1] = (float)s;
+    for (int64_t N = 64, step = 16; N <= 1024; N *= 2, step /= 2) {
+      if (j % step) continue;
+      double* d = (double*)((char*)host + spec_twiddle_offset(N, 1)) + 2 * (j / step);
+      float* f = (float*)((char*)host + spec_twiddle_offset(N, 0)) + 2 * (j / step);
+      d[0] = (double)c;
+      d[1] = (double)s;
+      f[0] = (float)c;
+      f[1] = (float)s;
     }
   }
 }

@@ -93,7 +93,7 @@ void fft_release(FftState* st);
 struct SpecTransform {
   const void* spec;         // the caller's half spectrum
   void* mid;                // [N][N][spec_transform_row] complex
-  const void* twiddles;     // exp(2 pi i j / N), j < N (spec_twiddles)
+  const void* twiddles;     // exp(2 pi i j / N), j < N: the table at spec_twiddle_offset
   int64_t mid_row;
   void* out;                // rows of P nodes of 3 doubles or floats, lo of them below the grid
   int64_t row_pitch, plane_pitch;  // bytes
@@ -101,7 +101,10 @@ struct SpecTransform {
 };
 bool spec_transform_built(int64_t N);
 int64_t spec_transform_row(int64_t N, int f64);
-void spec_twiddles(int64_t N, int f64, void* host);
+// twiddles of every length and precision, computed on the host
+size_t spec_twiddle_bytes();
+size_t spec_twiddle_offset(int64_t N, int f64);
+void spec_twiddles(void* host);
 hipError_t launch_spec_transform(const SpecTransform& p, int64_t N, int f64, int vorticity, hipStream_t s);
 
 // interp.hip

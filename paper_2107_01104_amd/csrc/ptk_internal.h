@@ -95,10 +95,10 @@ struct ptk_ctx {
   ptk::KernelTables tables;
   // spectral input: transform buffer, the transform's work buffer and plan
   ptk::DevBuf spec, fft_out, fft_work;
-  ptk::DevBuf twiddles;              // of the library's own transform, for (tw_N, tw_f64)
-  std::vector<double> tw_host;
-  int64_t tw_N = 0;
-  int tw_f64 = -1;
+  // of the library's own transform, every length and precision: written once, so
+  // that a transform of one size leaves what another's, or a captured one's, reads
+  ptk::DevBuf twiddles;
+  bool have_twiddles = false;
   ptk::FftState* fft = nullptr;
   // binning of the last interpolate call
   int64_t bin_np = 0, bin_nbins = 0;

@@ -72,3 +72,39 @@ def test_device_memory_of_a_transform(ptk, monkeypatch, N, prec, storage):
     assert torch.equal(ctx.get_field(), ref.get_field()) and ctx.field_scale() == ref.field_scale()
     ctx.close()
     ref.close()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_transforms_recorded_in_graphs_and_eager_ones_in_turn(ptk, prec):
+    """A transform recorded in a graph before any was run at its size, eager ones
+    of that size and another before and between its replays: every field is
+    the one an eager call on a context of its own gives."""
+    print(f"[spectrum] recorded, {prec}", flush=True)
+    spec = {N: spectrum(N, prec, N) for N in (64, 128)}
+    ref = {}
+    for N in spec:
+        ctx = ptk.Context(0)
+        ctx.set_field_spectral(spec[N], ptk.SPLINE, 8, 2, storage=ptk.F64, kind=ptk.SPEC_VORTICITY)
+        ref[N] = ctx.get_field()
+        ctx.close()
+    ctx = ptk.Context(0)
+
+    def eager(N):
+        ctx.set_field_spectral(spec[N], ptk.SPLINE, 8, 2, storage=ptk.F64, kind=ptk.SPEC_VORTICITY)
+        torch.cuda.synchronize()
+        assert torch.equal(ctx.get_field(), ref[N])
+
+    eager(128)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        ctx.set_field_spectral(spec[64], ptk.SPLINE, 8, 2, storage=ptk.F64, kind=ptk.SPEC_VORTICITY)
+    eager(64)
+    for other in (64, 128, 128, 64):
+        eager(other)
+        eager(64)  # (the context's own idea of its field is of the recorded size again)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(ctx.get_field(), ref[64])
+    ctx.close()
