@@ -508,8 +508,9 @@ int ptk_interpolate_learned(ptk_ctx *ctx, const double *X, int64_t Np, float *ou
 /* Host-only self-test of the library's internal checks (the scratch capacity
  * guard that every launch sequence passes before it writes scratch, the byte
  * cap of PTK_TEST_MAX_BYTES, the decoding of the device status word, the launch
- * sizes of the direct kernels).  Needs no device and no context; returns PTK_OK
- * when every check behaves as documented, PTK_EINTERNAL otherwise. */
+ * sizes of the direct kernels, the choice of the route).  Needs no device and
+ * no context; returns PTK_OK when every check behaves as documented,
+ * PTK_EINTERNAL otherwise. */
 int ptk_selftest(void);
 
 #ifdef __cplusplus

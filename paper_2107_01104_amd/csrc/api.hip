@@ -171,6 +171,17 @@ void drain_timers(ptk_ctx* c) {
   c->pending.clear();
 }
 
+FieldGeom field_geom(int64_t N, int I, int storage) {
+  FieldGeom geo;
+  geo.N = N;
+  geo.P = N + I - 1;
+  geo.node_bytes = storage == PTK_F64 ? 24 : storage == PTK_F32 ? 12 : 6;
+  geo.halo_lo = I / 2 - 1;
+  geo.row_pitch = ((geo.P * geo.node_bytes + 48) + 63) / 64 * 64;
+  geo.plane_pitch = geo.row_pitch * geo.P;
+  return geo;
+}
+
 BinGeom bin_geom(const ptk_ctx* c) {
   BinGeom g;
   g.T = c->storage == PTK_F64 ? kTileF64 : kTileF32;
@@ -293,6 +304,18 @@ int bin_sorted(ptk_ctx* c, int64_t Np, int64_t n_bins, bool have_hist, uint32_t*
   return PTK_OK;
 }
 
+// The sweep's workgroups: enough to fill the GPU, so columns are split along x3
+// into nseg segments of wps windows when there are few.
+void split_columns(const BinGeom& g, int64_t* nseg, int64_t* wps) {
+  const int64_t tiles = (int64_t)g.ntx * g.ntx, nw = g.nw;
+  int64_t n = (1024 + tiles - 1) / tiles;
+  if (n > nw) n = nw;
+  if (n < 1) n = 1;
+  if (n < (nw + kMaxWps - 1) / kMaxWps) n = (nw + kMaxWps - 1) / kMaxWps;
+  *wps = (nw + n - 1) / n;
+  *nseg = (nw + *wps - 1) / *wps;
+}
+
 InterpArgs base_args(const ptk_ctx* c, bool next_field = false) {
   InterpArgs a;
   std::memset(&a, 0, sizeof(a));
@@ -306,13 +329,7 @@ InterpArgs base_args(const ptk_ctx* c, bool next_field = false) {
   a.ntx = g.ntx;
   a.n_tiles = (int64_t)g.ntx * g.ntx;
   a.nw = g.nw;
-  // enough workgroups to fill the GPU: split columns along x3 when there are few
-  int64_t nseg = (1024 + a.n_tiles - 1) / a.n_tiles;
-  if (nseg > a.nw) nseg = a.nw;
-  if (nseg < 1) nseg = 1;
-  if (nseg < (a.nw + kMaxWps - 1) / kMaxWps) nseg = (a.nw + kMaxWps - 1) / kMaxWps;
-  a.wps = (a.nw + nseg - 1) / nseg;
-  a.nseg = (a.nw + a.wps - 1) / a.wps;
+  split_columns(g, &a.nseg, &a.wps);
   a.offsets = (const uint32_t*)c->offsets.ptr;
   a.coef = c->coef.ptr;
   a.flag = flag_words(c);
@@ -327,38 +344,59 @@ enum class Route {
   kDirectSorted  // the same in bin order (a state of several steps is re-binned after each)
 };
 
-// The way that takes the least time for Np particles on the context's field,
-// by estimates in microseconds fitted to single calls on grids of 32^3 to 1024^3
-// with 0.001 to 1 particles a cell (I = 4, 6, 8; every storage type).  Results
-// do not depend on the choice (the kernels agree bit for bit), only time does.
-//   direct: a launch, then each particle's I^2 stencil rows, which come from HBM
-//     or the memory-side cache (31 ns per 10^3 rows with FP32 nodes), or from L2
-//     where the field fits it.  In bin order neighbouring particles share
-//     rows: 0.4 to 0.62 of that from 0.007 particles a cell on, nothing gained
-//     below 0.002.
-//   binned routes: the sort, about 70 us of launches and 35 us per 10^6.
-//   sweep: every plane of the field staged (6 us per 10^6 FP32 nodes), then
-//     120 us per 10^6 particles once there are about 512 workgroups.
-// Measured, FP32, I = 8, values (direct / in bin order / sweep): 512^3 with
-// 134217 particles 318 / 361 / 974 us, 402653: 861 / 644 / 1074, 1342177: 2712 /
-// 1197 / 1180; 1024^3 with 3.2e6: 7348 / 4288 / 6995; 64^3 with 78643: 71 / 138 /
-// 119, 262144: 163 / 204 / 149.
+// What the parts of an evaluation take: microseconds for 10^6 particles, stencil
+// rows or grid nodes.  Fitted together with the rule below to single calls of
+// each route: 2138 calls on 8^3 to 1024^3 with 0.0005 to 1000 particles a node, I = 4, 6
+// and 8, FP64, FP32 and BF16 storage, values and gradients.
+struct RouteCost {
+  double particle, row;      // direct: a particle, and issuing one of its I^2 rows
+  double memory;             // a row that comes from HBM
+  double stage;              // sweep: a node into LDS
+  double sums, sum_row;      // its sums on the whole GPU: a particle, and one of its I^2 rows
+  double alone;              // a particle in one workgroup, nanoseconds
+};
+const RouteCost kRouteCost[3][2] = {  // storage FP64, FP32, 16-bit; values, gradient
+    {{1.0, 8.9, 41.0, 13.0, 79.0, 2.3, 34.0}, {26.0, 12.0, 41.0, 15.0, 118.0, 4.0, 65.0}},
+    {{15.0, 4.1, 31.0, 7.0, 40.0, 1.0, 25.0}, {68.0, 4.2, 31.0, 8.4, 75.0, 1.9, 43.0}},
+    {{6.4, 9.5, 16.0, 4.7, 27.0, 1.4, 27.0}, {45.0, 12.0, 16.0, 5.7, 87.0, 1.8, 48.0}}};
+
+// The way that takes the least time for Np particles, spread evenly over the
+// context's field.  Results do not depend on the choice (the kernels agree bit
+// for bit), only time does.
+//   direct: a launch and each particle's rows.  Their memory time is nearly
+//     nothing while an XCD's L2 holds the field (4 MB), half of HBM's at 32 MB, and
+//     grows slowly from there.
+//   in bin order: the sort, 16 us of launches, 29 for each digit after the first and
+//     8.6 a digit and 10^6 particles; then neighbours share their rows' lines, the
+//     more the closer they are.
+//   sweep: the sort; every plane of the field staged, partly beside the sums, which
+//     wait for the fullest workgroup where the grid has few.
+// Measured, FP32, I = 8, values, us (direct / in bin order / sweep): 512^3 with
+// 67108 particles 158 / 209 / 867, 671088: 1365 / 742 / 1097, 4026531: 8073 /
+// 2631 / 1294; 64^3 with 26214: 32 / 73 / 67, 262144: 144 / 144 / 97; 16^3 with
+// 1228800: 394 / 373 / 6311.  Over all the calls the choice takes 1.0022 times
+// the best route's time in the geometric mean, 1.19 at most; more than 1.05 times the
+// sweep's in five.  (Single constants for rows and sums, steps for the sharing
+// and a sweep scaled by its count of windows alone took 1.017 in the mean, 3.05
+// at most and more than 1.05 times the sweep's in 52: 48^3 BF16, I = 8, 442368
+// particles 432 us where the sweep takes 141.)
 Route route_of(const ptk_ctx* c, int64_t Np, bool grad) {
   if (c->test_route >= 0) return (Route)c->test_route;
   const BinGeom g = bin_geom(c);
-  const bool f64 = c->storage == PTK_F64, f32 = c->storage == PTK_F32;
-  const double n = 1e-6 * (double)Np, nodes = 1e-6 * (double)c->geom.N * (double)c->geom.N * (double)c->geom.N;
-  const double row = f64 ? (grad ? 69.0 : 48.0) : f32 ? 31.0 : 22.0;
-  const double bytes = (double)c->geom.plane_pitch * (double)c->geom.P;
-  const double rows = n * row * c->I * c->I * (bytes <= 8e6 ? 0.4 : 1.0);
-  const double sort = 70.0 + 35.0 * n;
-  const double groups = (double)n_bins_of(g);  // of at least one window
-  const double direct = 30.0 + rows;
-  const bool wide = f32 && c->I == 8;
-  const double shared = n < 0.002 * nodes ? 1.0 : n < 0.007 * nodes ? (wide ? 0.65 : 0.8) : wide ? 0.4 : 0.62;
-  const double sorted = 30.0 + sort + rows * shared;
-  const double sweep = 30.0 + sort + nodes * (f64 ? 15.0 : grad ? 8.0 : 6.0) +
-                       n * (f64 ? 250.0 : grad ? 170.0 : 120.0) * (groups < 512.0 ? 512.0 / groups : 1.0);
+  const RouteCost& k = kRouteCost[c->storage == PTK_F64 ? 0 : c->storage == PTK_F32 ? 1 : 2][grad];
+  const double N = (double)c->geom.N, nodes = 1e-6 * N * N * N, n = 1e-6 * (double)Np, I2 = c->I * c->I;
+  const double lines = std::log2((double)c->geom.plane_pitch * (double)c->geom.P / 4e6);
+  const double far = lines < 0.0 ? 0.02 : lines < 3.0 ? 0.02 + 0.46 / 3.0 * lines : 0.48 + 0.035 * (lines - 3.0);
+  const double shared = std::fmin(1.0, std::fmax(0.08, std::pow(0.00075 * nodes / n, 0.36)));
+  const double passes = std::fmax(1.0, (bits_for(n_bins_of(g)) + 7) / 8);
+  const double sort = 16.0 + 29.0 * (passes - 1.0) + 8.6 * passes * n;
+  const double own = n * (k.particle + I2 * k.row), rows = n * I2 * k.memory * far;
+  const double direct = own + rows, sorted = sort + own + rows * shared;
+  int64_t nseg, wps;
+  split_columns(g, &nseg, &wps);
+  const double edge = std::fmin(1.0, g.T / N), fullest = edge * edge * std::fmin(1.0, (double)(g.W * wps) / N);
+  const double stage = nodes * k.stage, sums = n * std::fmax(k.sums + I2 * k.sum_row, 1e3 * k.alone * fullest);
+  const double sweep = sort + stage + sums - 0.3 * std::fmin(stage, sums);
   if (direct <= sorted && direct <= sweep) return Route::kDirect;
   return sorted <= sweep ? Route::kDirectSorted : Route::kSweep;
 }
@@ -698,13 +736,7 @@ struct SpecSource {
 int store_field(ptk_ctx* c, const void* u, int in_f64, const SrcLayout& l, int64_t N, int storage_dtype,
                 const ptk_kernel* k, int m, const KernelTables& tab, hipStream_t s, bool next_field = false,
                 const SpecSource* spec = nullptr) {
-  FieldGeom geo;
-  geo.N = N;
-  geo.P = N + k->I - 1;
-  geo.node_bytes = storage_dtype == PTK_F64 ? 24 : storage_dtype == PTK_F32 ? 12 : 6;
-  geo.halo_lo = k->I / 2 - 1;
-  geo.row_pitch = ((geo.P * geo.node_bytes + 48) + 63) / 64 * 64;
-  geo.plane_pitch = geo.row_pitch * geo.P;
+  const FieldGeom geo = field_geom(N, k->I, storage_dtype);
   const size_t field_bytes = (size_t)(geo.plane_pitch * geo.P) + 64;
 
   // per-component scale for 16-bit storage
@@ -2268,6 +2300,25 @@ int ptk_selftest(void) {
       first += n;
     }
     expect(first == np);
+  }
+  // the route rule at calls whose best route was measured, by a fifth or more
+  const struct {
+    int64_t N;
+    int storage, I, grad;
+    int64_t np;
+    Route best;
+  } routes[] = {{32, PTK_F64, 4, 0, 1000, Route::kDirect},      {512, PTK_F32, 8, 0, 67108, Route::kDirect},
+                {512, PTK_F32, 8, 0, 671088, Route::kDirectSorted}, {512, PTK_F32, 8, 0, 4026531, Route::kSweep},
+                {48, PTK_BF16, 8, 0, 442368, Route::kSweep},    {96, PTK_BF16, 4, 0, 3538944, Route::kSweep},
+                {64, PTK_BF16, 4, 1, 1048576, Route::kSweep},   {384, PTK_F16, 4, 1, 5662310, Route::kSweep},
+                {48, PTK_F64, 8, 0, 442368, Route::kSweep},     {512, PTK_F64, 8, 1, 671088, Route::kDirectSorted},
+                {1024, PTK_F32, 8, 1, 2147483, Route::kDirectSorted}, {12, PTK_F32, 8, 0, 172800, Route::kDirect},
+                {256, PTK_F32, 6, 0, 5033164, Route::kSweep},   {67, PTK_F16, 6, 1, 0, Route::kDirect}};
+  for (const auto& q : routes) {
+    c.storage = q.storage;
+    c.I = q.I;
+    c.geom = field_geom(q.N, q.I, q.storage);
+    expect(route_of(&c, q.np, q.grad != 0) == q.best);
   }
   return bad == 0 ? PTK_OK : PTK_EINTERNAL;
 }
