@@ -164,7 +164,7 @@ constexpr int kDirGroups = kDirThreads / 16;  // particles per block
 
 // A launch may not reach 2^32 work-items, and a particle takes 16: calls of 2^28
 // particles and more (small grids, or I = 4 on the largest) go in slices of
-// half that, this launch's from particle first on.
+// half that, this launch's from particle a.first on.
 constexpr int64_t kDirSlice = (int64_t)1 << 27;
 static_assert(kDirSlice % kDirGroups == 0 && kDirSlice * 16 < (int64_t)1 << 32, "whole blocks, below 2^32 work-items");
 
@@ -176,11 +176,11 @@ int64_t direct_slice(int64_t np, int64_t first, unsigned* blocks, int* threads) 
 }
 
 template <int ST, int I, bool GRAD>
-__global__ __launch_bounds__(kDirThreads) void k_direct(InterpArgs a, BinGeom g, uint32_t* keys, int64_t first) {
+__global__ __launch_bounds__(kDirThreads) void k_direct(InterpArgs a, BinGeom g, uint32_t* keys) {
   using V = typename StoreT<ST>::acc;
   const int l16 = threadIdx.x & 15, j = l16 & 7, h = l16 >> 3;
   const int jj = j < I ? j : I - 1;
-  const int64_t p = first + (int64_t)blockIdx.x * kDirGroups + (threadIdx.x >> 4);
+  const int64_t p = a.first + (int64_t)blockIdx.x * kDirGroups + (threadIdx.x >> 4);
   if (p >= a.np) return;  // (whole DPP rows: a particle's 16 lanes stay or leave together)
   const int64_t row = a.xrow ? (int64_t)a.xrow[p] : p;
   double x[3];
@@ -215,12 +215,18 @@ __global__ __launch_bounds__(kDirThreads) void k_direct(InterpArgs a, BinGeom g,
 // rounded binary64 one.  GRAD: the last step evaluates the gradient at its
 // start position.
 template <int ST, int I, bool GRAD>
-__global__ __launch_bounds__(kDirThreads) void k_direct_steps(InterpArgs a, DirectSteps s, int64_t first) {
+__global__ __launch_bounds__(kDirThreads) void k_direct_steps(InterpArgs a, DirectSteps s) {
   using V = typename StoreT<ST>::acc;
   const int l16 = threadIdx.x & 15, j = l16 & 7, h = l16 >> 3;
   const int jj = j < I ? j : I - 1;
-  const int64_t p = first + (int64_t)blockIdx.x * kDirGroups + (threadIdx.x >> 4);
-  if (p >= a.np) return;  // (before any read: positions and history are written in place)
+  const int64_t p = a.first + (int64_t)blockIdx.x * kDirGroups + (threadIdx.x >> 4);
+  // Lanes without a particle leave before any read: positions and history are
+  // written in place, and another particle's may be at any moment.  (The empty
+  // asm has the arguments that follow fetched together with those the branch
+  // waits for; behind it they cost a call of 20 us another 0.3.)
+  asm volatile("" ::"s"(a.xrow), "s"(a.coef), "s"(a.field), "s"(a.row_pitch), "s"(a.plane_pitch), "s"(a.invd), "s"(a.N),
+               "s"(s.X), "s"(s.hl), "s"(s.nsteps), "s"(s.kind), "s"(s.dt));
+  if (p >= a.np) return;
   const int64_t row = a.xrow ? (int64_t)a.xrow[p] : p;
   double x[3];
 #pragma unroll
@@ -312,21 +318,22 @@ __global__ __launch_bounds__(kDirThreads) void k_direct_steps(InterpArgs a, Dire
 }
 
 template <int ST, int I>
-static hipError_t direct_one(const InterpArgs& a, const BinGeom& g, uint32_t* keys, const DirectSteps* st,
+static hipError_t direct_one(InterpArgs a, const BinGeom& g, uint32_t* keys, const DirectSteps* st,
                              hipStream_t s) {
-  for (int64_t first = 0, n; first < a.np; first += n) {
+  int64_t n;
+  for (a.first = 0; a.first < a.np; a.first += n) {
     unsigned grid;
     int threads;
-    n = direct_slice(a.np, first, &grid, &threads);
+    n = direct_slice(a.np, a.first, &grid, &threads);
     if (st) {
       if (a.grad)
-        k_direct_steps<ST, I, true><<<grid, threads, 0, s>>>(a, *st, first);
+        k_direct_steps<ST, I, true><<<grid, threads, 0, s>>>(a, *st);
       else
-        k_direct_steps<ST, I, false><<<grid, threads, 0, s>>>(a, *st, first);
+        k_direct_steps<ST, I, false><<<grid, threads, 0, s>>>(a, *st);
     } else if (a.grad) {
-      k_direct<ST, I, true><<<grid, threads, 0, s>>>(a, g, keys, first);
+      k_direct<ST, I, true><<<grid, threads, 0, s>>>(a, g, keys);
     } else {
-      k_direct<ST, I, false><<<grid, threads, 0, s>>>(a, g, keys, first);
+      k_direct<ST, I, false><<<grid, threads, 0, s>>>(a, g, keys);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

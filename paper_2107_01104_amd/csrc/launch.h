@@ -118,6 +118,7 @@ struct InterpArgs {
   const double* X;          // positions: bin-ordered particle p's is row xrow[p] (row p if xrow is NULL)
   const uint32_t* xrow;
   int64_t np;               // number of particles
+  int64_t first;            // the launch's first one (direct kernels; set by their launcher)
   const uint32_t* offsets;  // [n_bins + 1]
   const uint32_t* orig;     // destination index of each bin-ordered particle, or NULL
   const uint32_t* grad_orig;  // destination index of its gradient row, or NULL (= orig)
