@@ -684,7 +684,8 @@ void ptk_destroy(ptk_ctx* c) {
                       &c->rb_block, &c->spec, &c->fft_out, &c->fft_work, &c->twiddles, &c->aoff, &c->aperm, &c->aperm_p,
                       &c->ori_p, &c->ori_pn, &c->ori_r1, &c->ori_r2, &c->ori_ps, &c->ori_h[0], &c->ori_h[1],
                       &c->ori_h[2], &c->ori_h[3], &c->ori_hb[0], &c->ori_hb[1], &c->ori_hb[2], &c->ori_hb[3],
-                      &c->gint2, &c->io};
+                      &c->in_vh[0], &c->in_vh[1], &c->in_vh[2], &c->in_vh[3], &c->in_vhb[0], &c->in_vhb[1],
+                      &c->in_vhb[2], &c->in_vhb[3], &c->gint2, &c->io};
     for (DevBuf* b : bufs) release(*b);
     if (c->flag) (void)hipHostFree(const_cast<int*>(c->flag));
     fft_release(c->fft);
