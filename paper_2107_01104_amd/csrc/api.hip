@@ -861,12 +861,11 @@ int ensure_transform(ptk_ctx* c, int64_t N, int f64) {
 
 // Stores the field of a half spectrum.  Grids the library's own transform is
 // built for take its three passes, straight into the stored rows (16-bit
-// storage, whose scale is the whole field's rms, by way of the grid values, in the
-// transform's buffer);
-// others go through rocFFT's planes.  Measured with FP64 vorticity
-// into FP32 storage: 64^3 172 us by rocFFT, 157 so; 128^3 185 and 166; 256^3
-// 1041 and 570; 512^3 7.68 ms and 4.33; 1024^3 81.5 and 33.9; into BF16 512^3
-// 8.17 and 5.71.
+// storage, whose scale is the whole field's rms, by way of the grid values, in
+// the transform's buffer); others go through rocFFT's planes.  Measured with FP64
+// vorticity into FP32 storage, by rocFFT and so: 64^3 172 and 149 us; 128^3 185 and
+// 153; 256^3 1041 and 547; 512^3 7.68 and 4.17 ms; 1024^3 81.5 and 31 to 34; into BF16
+// 512^3 8.17 and 5.76.
 int store_spectrum(ptk_ctx* c, const void* spec, int64_t N, int f64, int kind, int storage, const ptk_kernel* k, int m,
                    const KernelTables& tab, hipStream_t s, bool next_field) {
   if (!spec_transform_built(N)) {

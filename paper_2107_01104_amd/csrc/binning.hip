@@ -86,8 +86,6 @@ constexpr int kSortThreads = 256;
 constexpr int kSortItems = 8;
 constexpr int kTile = kSortThreads * kSortItems;  // 2048
 
-// n_dev (optional): the element count held on the device; n is then an upper
-// bound that sized the grid, and tiles past the count contribute nothing.
 // tiles of a sort of n elements, or of min(n, *n_dev) when the count lives on
 // the device; the digit histograms are laid out [digit][tiles]
 __device__ __forceinline__ int64_t sort_tiles(int64_t n, const uint32_t* n_dev) {
@@ -116,6 +114,9 @@ __global__ __launch_bounds__(256) void k_keys_hist(const double* __restrict__ X,
   if (threadIdx.x <= mask) hist[(int64_t)threadIdx.x * n_tiles + blockIdx.x] = h[threadIdx.x];
 }
 
+// n_dev (optional, here and below): the element count held on the device; n is
+// then an upper bound that sized the grid, and tiles past the count contribute
+// nothing.
 __global__ __launch_bounds__(256) void k_radix_hist(const uint32_t* __restrict__ keys, int64_t n,
                                                     const uint32_t* __restrict__ n_dev, int shift, uint32_t mask,
                                                     uint32_t* __restrict__ hist, int64_t n_tiles) {

@@ -57,15 +57,6 @@ __device__ __forceinline__ double locate(double x, int N, double invd, int* c, d
   return y;
 }
 
-__device__ __forceinline__ double wrap(double x) {
-  const double L = 6.283185307179586;
-  double q = floor(x / L);
-  double y = x - L * q;
-  if (y < 0.0) y = y + L;
-  if (y >= L) y = 0.0;
-  return y;
-}
-
 __device__ __forceinline__ bool in_domain3(double a, double b, double c) {
   return in_domain(a) && in_domain(b) && in_domain(c);
 }

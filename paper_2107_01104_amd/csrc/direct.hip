@@ -15,9 +15,9 @@
 // Bound by the memory pipeline: a particle's 64 rows (I = 8) are 96-byte
 // segments at arbitrary 4-byte offsets, about 1.6 cache lines each.  Measured
 // against the sort and sweep before it: 2e5 particles on 512^3 (FP32, I = 8,
-// value + gradient) 1332 us a call, now 474 (1.2 GB of stencil nodes: 2.6 TB/s);
-// 1000 on 32^3 (FP64, I = 4) 71 -> 32 us; a Heun step of 10^4 on 32^3 as one
-// call 169 -> 34 us.
+// value + gradient) 1332 us a call, now 460 (1.2 GB of stencil nodes: 2.6 TB/s);
+// 1000 on 32^3 (FP64, I = 4) 71 us, 32 so and 20 since the status words left the
+// device; a Heun step of 10^4 on 32^3 as one call 169, 34 and 21 us.
 #include "interp_device.h"
 
 namespace ptk {

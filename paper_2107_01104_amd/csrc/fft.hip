@@ -14,7 +14,7 @@
 // field have them.  Bound by HBM: each pass reads and writes the amplitudes
 // once.  A general transform library needs a pass to separate the components
 // and apply Biot-Savart and one to pack its planes besides its own passes:
-// FP64 vorticity into FP32 storage, 512^3 7.68 ms with rocFFT, 4.33 here (the
+// FP64 vorticity into FP32 storage, 512^3 7.68 ms with rocFFT, 4.17 here (the
 // passes 1.49, 1.42 and 1.49 ms under a profiler, at 4.5, 4.6 and 3.4 TB/s);
 // 1024^3 81.5 and 33.9 ms (14.5, 10.8 and 9.2).
 //
@@ -26,8 +26,6 @@
 //
 // Inverse transforms, unnormalised: x_n = sum_k X_k exp(+2 pi i k n / N).
 #include <cmath>
-#include <new>
-#include <vector>
 
 #include "device_common.h"
 #include "launch.h"
@@ -122,12 +120,12 @@ __device__ __forceinline__ void butterfly(Cx<R>* a) {
 // Radices of a length
 template <int N>
 struct Plan;
-template <> struct Plan<32> { static constexpr int r1 = 8, r2 = 4, r3 = 1, r4 = 1; };
-template <> struct Plan<64> { static constexpr int r1 = 8, r2 = 8, r3 = 1, r4 = 1; };
-template <> struct Plan<128> { static constexpr int r1 = 8, r2 = 4, r3 = 4, r4 = 1; };
-template <> struct Plan<256> { static constexpr int r1 = 8, r2 = 8, r3 = 4, r4 = 1; };
-template <> struct Plan<512> { static constexpr int r1 = 8, r2 = 8, r3 = 8, r4 = 1; };
-template <> struct Plan<1024> { static constexpr int r1 = 16, r2 = 16, r3 = 4, r4 = 1; };
+template <> struct Plan<32> { static constexpr int r1 = 8, r2 = 4, r3 = 1; };
+template <> struct Plan<64> { static constexpr int r1 = 8, r2 = 8, r3 = 1; };
+template <> struct Plan<128> { static constexpr int r1 = 8, r2 = 4, r3 = 4; };
+template <> struct Plan<256> { static constexpr int r1 = 8, r2 = 8, r3 = 4; };
+template <> struct Plan<512> { static constexpr int r1 = 8, r2 = 8, r3 = 8; };
+template <> struct Plan<1024> { static constexpr int r1 = 16, r2 = 16, r3 = 4; };
 
 // index of element i in a column's LDS copy: a gap after every r1 elements, so
 // that the first exchange's writes (r1 apart from thread to thread) spread
@@ -221,13 +219,9 @@ __device__ __forceinline__ void transform(Cx<R>* v, R* lds, int t, const Cx<R>* 
     exchange<N, E, P::r2, P::r1, P::r3, NC>(v, lds, t);
     stage<N, E, P::r3, P::r1 * P::r2, TN>(v, t, tw);
   }
-  if constexpr (P::r4 > 1) {
-    exchange<N, E, P::r3, P::r1 * P::r2, P::r4, NC>(v, lds, t);
-    stage<N, E, P::r4, P::r1 * P::r2 * P::r3, TN>(v, t, tw);
-  }
 }
 template <int N>
-constexpr int kLast = Plan<N>::r4 > 1 ? Plan<N>::r4 : Plan<N>::r3 > 1 ? Plan<N>::r3 : Plan<N>::r2;
+constexpr int kLast = Plan<N>::r3 > 1 ? Plan<N>::r3 : Plan<N>::r2;
 
 // Columns per workgroup and elements per thread: whole k1 (3 columns each), 192
 // bytes or more of every row where 1024 threads and the LDS allow it.  (Rows'

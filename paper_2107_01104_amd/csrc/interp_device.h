@@ -86,16 +86,6 @@ __device__ __forceinline__ double bcast2(double v) {
   return __builtin_bit_cast(double, bcast2_64<L0, L1>(__builtin_bit_cast(long, v)));
 }
 
-// sum over the 16 lanes of the row (every lane gets the total)
-template <typename V>
-__device__ __forceinline__ V rowsum(V v) {
-  v += dpp<0xB1>(v);   // quad_perm [1,0,3,2]
-  v += dpp<0x4E>(v);   // quad_perm [2,3,0,1]
-  v += dpp<0x141>(v);  // row_half_mirror
-  v += dpp<0x140>(v);  // row_mirror
-  return v;
-}
-
 // Reduce-scatter of a particle's three value partials over the 16 lanes of a
 // row (lane l16 = j + 8h): after it, lane (h, j) holds the row's total of
 // value 2h + (j >> 2) (value 3 is the zero padding), summed over all 16 lanes.
