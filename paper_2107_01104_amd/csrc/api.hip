@@ -1033,11 +1033,11 @@ int ptk_get_binning(ptk_ctx* c, uint32_t* perm, uint32_t* offsets, void* stream)
             radix_sort_keys(kb, ka, (uint32_t*)c->vals_a.ptr, (uint32_t*)c->vals_b.ptr, c->bin_np, nullptr, false,
                             bits_for(c->bin_nbins), (uint32_t*)c->hist.ptr, false, &sk, &c->bin_perm, s),
             "radix sort");
-    PTK_HIP(c, launch_offsets(sk, c->bin_np, c->bin_nbins, (uint32_t*)c->offsets.ptr, s), "bin offsets");
-    // the keys back to the caller's order, where a further call (or the replay of
-    // a captured one) finds them
+    // with the keys back to the caller's order, where a further call (or the replay
+    // of a captured one) finds them
     uint32_t* back = sk == kb ? ka : kb;
-    PTK_HIP(c, scatter_u32(sk, c->bin_perm, c->bin_np, back, s), "keep keys");
+    PTK_HIP(c, launch_offsets(sk, c->bin_np, c->bin_nbins, (uint32_t*)c->offsets.ptr, s, c->bin_perm, back),
+            "bin offsets");
     if (back != kb)
       PTK_HIP(c, hipMemcpyAsync(kb, back, (size_t)c->bin_np * 4, hipMemcpyDeviceToDevice, s), "keep keys");
   }

@@ -266,10 +266,12 @@ __global__ __launch_bounds__(1024) void k_scan_rows(uint32_t* __restrict__ a, in
 }
 
 // offsets[b] = first sorted index with key >= b, for b in [0, n_bins]
-__global__ __launch_bounds__(256) void k_offsets(const uint32_t* __restrict__ skeys, int64_t n,
-                                                 int64_t n_bins, uint32_t* __restrict__ offsets) {
+__global__ __launch_bounds__(256) void k_offsets(const uint32_t* __restrict__ skeys, int64_t n, int64_t n_bins,
+                                                 uint32_t* __restrict__ offsets, const uint32_t* __restrict__ perm,
+                                                 uint32_t* __restrict__ unsorted) {
   int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i > n) return;
+  if (unsorted && i < n) unsorted[perm[i]] = skeys[i];
   int64_t lo = (i == 0) ? -1 : (int64_t)skeys[i - 1];
   int64_t hi = (i == n) ? n_bins : (int64_t)skeys[i];
   if (hi > n_bins) hi = n_bins;  // keys are < n_bins by construction; never write past the array
@@ -339,14 +341,6 @@ __global__ __launch_bounds__(256) void k_gather_u32(const uint32_t* __restrict__
   int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (k >= n) return;
   out[k] = in[perm[k]];
-}
-
-__global__ __launch_bounds__(256) void k_scatter_u32(const uint32_t* __restrict__ in,
-                                                     const uint32_t* __restrict__ perm, int64_t n,
-                                                     uint32_t* __restrict__ out) {
-  int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (k >= n) return;
-  out[perm[k]] = in[k];
 }
 
 // ---------------------------------------------------------------------------
@@ -625,9 +619,9 @@ hipError_t launch_iota(uint32_t* p, int64_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_offsets(const uint32_t* skeys, int64_t n, int64_t n_bins, uint32_t* offsets,
-                          hipStream_t s) {
-  k_offsets<<<blocks_for(n + 1, 256), 256, 0, s>>>(skeys, n, n_bins, offsets);
+hipError_t launch_offsets(const uint32_t* skeys, int64_t n, int64_t n_bins, uint32_t* offsets, hipStream_t s,
+                          const uint32_t* perm, uint32_t* unsorted) {
+  k_offsets<<<blocks_for(n + 1, 256), 256, 0, s>>>(skeys, n, n_bins, offsets, perm, unsorted);
   return hipGetLastError();
 }
 
@@ -646,12 +640,6 @@ hipError_t gather3_f32(const float* in, const uint32_t* perm, int64_t n, float* 
 hipError_t gather_u32(const uint32_t* in, const uint32_t* perm, int64_t n, uint32_t* out, hipStream_t s) {
   if (n == 0) return hipSuccess;
   k_gather_u32<<<blocks_for(n, 256), 256, 0, s>>>(in, perm, n, out);
-  return hipGetLastError();
-}
-
-hipError_t scatter_u32(const uint32_t* in, const uint32_t* perm, int64_t n, uint32_t* out, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  k_scatter_u32<<<blocks_for(n, 256), 256, 0, s>>>(in, perm, n, out);
   return hipGetLastError();
 }
 

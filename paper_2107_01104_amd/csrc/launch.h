@@ -48,12 +48,13 @@ hipError_t rebin_incremental(const uint32_t* okeys, const uint32_t* ooff, const 
                              int64_t n_bins, int key_bits, const RebinScratch& w, uint32_t* perm, uint32_t* skeys,
                              uint32_t* noff, hipStream_t s);
 hipError_t launch_iota(uint32_t* p, int64_t n, hipStream_t s);  // p[i] = i
-hipError_t launch_offsets(const uint32_t* skeys, int64_t n, int64_t n_bins, uint32_t* offsets,
-                          hipStream_t s);
+// the bins' offsets from the sorted keys; unsorted (optional): where the keys
+// go in the order they had before the sort that perm describes (not skeys)
+hipError_t launch_offsets(const uint32_t* skeys, int64_t n, int64_t n_bins, uint32_t* offsets, hipStream_t s,
+                          const uint32_t* perm = nullptr, uint32_t* unsorted = nullptr);
 hipError_t gather3_f64(const double* in, const uint32_t* perm, int64_t n, double* out, hipStream_t s);
 hipError_t gather3_f32(const float* in, const uint32_t* perm, int64_t n, float* out, hipStream_t s);
 hipError_t gather_u32(const uint32_t* in, const uint32_t* perm, int64_t n, uint32_t* out, hipStream_t s);
-hipError_t scatter_u32(const uint32_t* in, const uint32_t* perm, int64_t n, uint32_t* out, hipStream_t s);
 // rows of `width` elements, 3 or 9
 hipError_t scatter_f64(const double* in, const uint32_t* idx, int64_t n, int width, double* out,
                        hipStream_t s);
