@@ -266,7 +266,8 @@ int ptk_interpolate_noalloc(ptk_ctx *ctx, const double *X, int64_t Np, void *out
  * Particles are re-binned after every position update to the stable order of
  * their new bins (only the particles whose bin changed are sorted, then merged
  * with the others) and kept in bin order internally (particles that are few for
- * the grid need no bins and are stepped in place); results are returned in the
+ * the grid need no bins: they are stepped in place, in the order of X or in bin
+ * order, which is then renewed every few steps); results are returned in the
  * order of X. */
 int ptk_advance_particles(ptk_ctx *ctx, double *X, int64_t Np, void *rhs_hist, int *hist_len,
                           int scheme, double dt, int nsteps, void *grad_out, void *stream);

@@ -341,8 +341,20 @@ InterpArgs base_args(const ptk_ctx* c, bool next_field = false) {
 enum class Route {
   kSweep,        // binned, by the tile-column sweep (interp.hip)
   kDirect,       // in the order given, straight from the field (direct.hip)
-  kDirectSorted  // the same in bin order (a state of several steps is re-binned after each)
+  kDirectSorted  // the same in bin order
 };
+
+// Steps a state on kDirectSorted takes before it is sorted again: an order that
+// is not kept up loses what neighbours share, the faster the longer the steps,
+// which the library cannot weigh against its grid ahead of them.  Tracers in a field
+// with k up to N/3, us a step late in a run with steps of 0.05 / 0.3 / 1 cells:
+//   1.1e6 on 512^3, FP32, I = 8, Euler: every 8 1097 / 1114 / 1144, 16 1097 / 1133 /
+//     1208, 32 1101 / 1174 / 1320, at the load alone 1142 / 1590 / 1939; swept 1148
+//     to 1172.
+//   4e6 on 512^3, FP32, I = 4, Heun in one call: every 8 777 / 804 / 868, 16 709 /
+//     774 / 930, 32 654 / 770 / 1053, at the load alone 909 / 1855 / 2482, re-binned
+//     at every step 1579 / 1604 / 1652; swept 1954 to 2080.
+constexpr int kSortSteps = 8;
 
 // What the parts of an evaluation take: microseconds for 10^6 particles, stencil
 // rows or grid nodes.  Fitted together with the rule below to single calls of
@@ -380,7 +392,7 @@ const RouteCost kRouteCost[3][2] = {  // storage FP64, FP32, 16-bit; values, gra
 // and a sweep scaled by its count of windows alone took 1.017 in the mean, 3.05
 // at most and more than 1.05 times the sweep's in 52: 48^3 BF16, I = 8, 442368
 // particles 432 us where the sweep takes 141.)
-Route route_of(const ptk_ctx* c, int64_t Np, bool grad) {
+Route route_of(const ptk_ctx* c, int64_t Np, bool grad, double per_sort = 1.0, double load = 0.0, double rebin = 0.0) {
   if (c->test_route >= 0) return (Route)c->test_route;
   const BinGeom g = bin_geom(c);
   const RouteCost& k = kRouteCost[c->storage == PTK_F64 ? 0 : c->storage == PTK_F32 ? 1 : 2][grad];
@@ -391,14 +403,28 @@ Route route_of(const ptk_ctx* c, int64_t Np, bool grad) {
   const double passes = std::fmax(1.0, (bits_for(n_bins_of(g)) + 7) / 8);
   const double sort = 16.0 + 29.0 * (passes - 1.0) + 8.6 * passes * n;
   const double own = n * (k.particle + I2 * k.row), rows = n * I2 * k.memory * far;
-  const double direct = own + rows, sorted = sort + own + rows * shared;
+  const double direct = own + rows, sorted = (load + sort) / per_sort + own + rows * shared;
   int64_t nseg, wps;
   split_columns(g, &nseg, &wps);
   const double edge = std::fmin(1.0, g.T / N), fullest = edge * edge * std::fmin(1.0, (double)(g.W * wps) / N);
   const double stage = nodes * k.stage, sums = n * std::fmax(k.sums + I2 * k.sum_row, 1e3 * k.alone * fullest);
-  const double sweep = sort + stage + sums - 0.3 * std::fmin(stage, sums);
+  const double sweep = sort + rebin + stage + sums - 0.3 * std::fmin(stage, sums);
   if (direct <= sorted && direct <= sweep) return Route::kDirect;
   return sorted <= sweep ? Route::kDirectSorted : Route::kSweep;
+}
+
+// The route of steps: a state in bin order is sorted again every kSortSteps, and
+// one that the call itself loads and stores (one_shot) takes 40 us for that and
+// one sort if its steps are fewer; a swept one is re-binned for every
+// evaluation, 25 us and 10 for 10^6 particles beyond a call's sort.  Measured over 2022
+// sizes, schemes and kinds of steps on 24^3 to 400^3 (fields with k up to N/3, 0.2
+// cells a step): 1.0095 times the best route's time in the mean, 1.52 at most, more
+// than 1.05 times the sweep's in 7, 1.17 at most.  128^3 with 60 000 (FP32, I = 8)
+// 74 us a resident Heun step in bin order, 197 swept, 204 directly.
+Route step_route(const ptk_ctx* c, int64_t Np, bool grad, int scheme, int steps, bool one_shot) {
+  const int n = steps < kSortSteps ? steps : kSortSteps;
+  return route_of(c, Np, grad, (double)n * (scheme == PTK_HEUN ? 2.0 : 1.0), one_shot ? 40.0 : 0.0,
+                  25.0 + 1e-5 * (double)Np);
 }
 
 // Device scratch of one interpolate call: sort keys and values (double
@@ -1061,11 +1087,17 @@ const double kABW[5][4] = {{0, 0, 0, 0},
                            {23.0 / 12.0, -16.0 / 12.0, 5.0 / 12.0, 0},
                            {55.0 / 24.0, -59.0 / 24.0, 37.0 / 24.0, -9.0 / 24.0}};
 
-// Sorts the caller's particles into bin order and makes them the loaded
+// Whether a state to be kept for steps to come is sorted when it is loaded.
+bool load_binned(const ptk_ctx* c, int64_t Np, int depth) {
+  return step_route(c, Np, false, depth ? PTK_AB2 : PTK_HEUN, kSortSteps, false) != Route::kDirect;
+}
+
+// Sorts the caller's particles into bin order (if binned) and makes them the loaded
 // state: positions gathered into xs, caller index into orig, the hl valid
 // history entries of rhs_hist ([K][Np][3], caller order) gathered, the bins'
 // sorted keys and offsets in skeys / aoff.  Argument checks are the caller's.
-int adv_load(ptk_ctx* c, const double* X, int64_t Np, const void* rhs_hist, int hl, int K, hipStream_t s) {
+int adv_load(ptk_ctx* c, const double* X, int64_t Np, const void* rhs_hist, int hl, int K, bool binned,
+             hipStream_t s) {
   auto& st = c->adv;
   st.valid = false;
   const int64_t N = c->geom.N;
@@ -1100,7 +1132,6 @@ int adv_load(ptk_ctx* c, const double* X, int64_t Np, const void* rhs_hist, int 
   uint32_t* keys = (uint32_t*)c->keys_a.ptr;
   int* flag = flag_words(c);
   clear_flag(c);
-  const bool binned = route_of(c, Np, false) != Route::kDirect;
   if (Np > 0) {
     Timed t(c, s, PTK_T_KEYS);
     // (and the domain check)
@@ -1140,6 +1171,7 @@ int adv_load(ptk_ctx* c, const double* X, int64_t Np, const void* rhs_hist, int 
   st.ori = false;
   st.inert = false;
   st.binned = binned;
+  st.age = binned ? 0 : kSortSteps;
   st.Np = Np;
   st.N = N;
   st.vb = vb;
@@ -1371,21 +1403,18 @@ int adv_steps(ptk_ctx* c, int scheme, double dt, int nsteps, void* grad_out, hip
   };
 
   if (!final_X) clear_flag(c);  // (the one-shot form: adv_load did, and its kernels may be running)
-  // Without bins the state stays in the order it has; the other routes keep it
-  // in bin order, re-binned after every step, since an order that is not kept
-  // loses what neighbours share (1.1e6 tracers on 512^3, FP32, I = 8, Euler:
-  // sorted once, 1101 us a step at first, 1720 after 0.8 and 2050 after 4 units of
-  // time with rms u = 1; re-binned 985 throughout; swept 1165).
-  const Route route = route_of(c, Np, ori);
-  const bool binned = route != Route::kDirect, direct = route != Route::kSweep;
-  if (binned && !st.binned) {
-    // the particles were loaded or stepped without bins (on another field): sort them
-    // (in the re-binning's buffers; a recorded interpolate binning stays)
-    if (st.xrow) {
-      PTK_HIP(c, gather3_f64(st.xcur, st.xrow, Np, st.xnext, s), "gather positions");
+  // Puts a state that is not (or no longer) in bin order into it, in the
+  // re-binning's buffers (a recorded interpolate binning stays): for the sweep
+  // the positions stay where they are, read through the permutation that the
+  // next re-binning replaces, for direct steps they move.
+  auto sort_state = [&](bool move) -> int {
+    auto gather_x = [&](const uint32_t* rows) -> int {
+      PTK_HIP(c, gather3_f64(st.xcur, rows, Np, st.xnext, s), "gather positions");
       std::swap(st.xcur, st.xnext);
       st.xrow = nullptr;
-    }
+      return PTK_OK;
+    };
+    if (st.xrow) PTK_TRY(gather_x(st.xrow));
     uint32_t *perm = nullptr, *sk = nullptr;
     {
       Timed t(c, s, PTK_T_SORT);
@@ -1397,28 +1426,49 @@ int adv_steps(ptk_ctx* c, int scheme, double dt, int nsteps, void* grad_out, hip
                               (uint32_t*)c->mv_b.ptr, Np, nullptr, false, bits_for(n_bins), (uint32_t*)c->hist.ptr,
                               true, &sk, &perm, s),
               "radix sort");
-      PTK_HIP(c, launch_offsets(sk, Np, n_bins, (uint32_t*)c->aoff.ptr, s), "bin offsets");
-      PTK_HIP(c, hipMemcpyAsync(c->skeys.ptr, sk, (size_t)Np * 4, hipMemcpyDeviceToDevice, s), "sorted keys");
-      PTK_HIP(c, hipMemcpyAsync(c->aperm.ptr, perm, (size_t)Np * 4, hipMemcpyDeviceToDevice, s), "copy order");
+      if (!move) {
+        PTK_HIP(c, launch_offsets(sk, Np, n_bins, (uint32_t*)c->aoff.ptr, s), "bin offsets");
+        PTK_HIP(c, hipMemcpyAsync(c->skeys.ptr, sk, (size_t)Np * 4, hipMemcpyDeviceToDevice, s), "sorted keys");
+        PTK_HIP(c, hipMemcpyAsync(c->aperm.ptr, perm, (size_t)Np * 4, hipMemcpyDeviceToDevice, s), "copy order");
+        perm = (uint32_t*)c->aperm.ptr;
+      }
     }
-    PTK_TRY(carry((const uint32_t*)c->aperm.ptr));
-    st.xrow = (uint32_t*)c->aperm.ptr;
-  }
-  st.binned = binned;
-  if (!binned && !pst) {
-    // tracers: the whole call in one launch, positions and history in place
+    PTK_TRY(carry(perm));
+    if (move)
+      PTK_TRY(gather_x(perm));
+    else
+      st.xrow = perm;
+    st.age = 0;
+    return PTK_OK;
+  };
+  const Route route = step_route(c, Np, ori, scheme, final_X ? nsteps : kSortSteps, final_X != nullptr);
+  const bool sweep = route == Route::kSweep, direct = !sweep, sorted = route == Route::kDirectSorted;
+  if (sweep && !st.binned) PTK_TRY(sort_state(false));  // (loaded or stepped without bins, on another field)
+  st.binned = sweep;
+  if (sweep) st.age = 0;
+  // direct steps in bin order: the order is put right again every kSortSteps
+  auto due = [&]() { return sorted && st.age >= kSortSteps; };
+  auto aged = [&](int steps) { st.age = steps < kSortSteps - st.age ? st.age + steps : kSortSteps; };
+  if (direct && !pst) {
+    // tracers: many steps a launch, positions and history in place
     InterpArgs a = base_args(c);
-    a.xrow = st.xrow;
     a.np = Np;
-    a.grad = grad_out;
-    a.grad_orig = st.orig;
     a.out_f64 = vf64;
     const InterpArgs next = base_args(c, stage2_next);
     DirectSteps d = direct_steps(scheme, dt, hl, next);
-    d.X = st.xcur;
-    for (int j = 0; j < K; ++j) d.hist[j] = st.h[j];
-    PTK_TRY(run_direct_steps(c, a, d, nsteps, s));
-    if (K) st.hl = hl = d.hl;
+    for (int done = 0, part; done < nsteps; done += part) {
+      if (due()) PTK_TRY(sort_state(true));
+      part = nsteps - done;
+      if (sorted && part > kSortSteps - st.age) part = kSortSteps - st.age;
+      a.xrow = st.xrow;
+      a.grad = done + part == nsteps ? grad_out : nullptr;
+      a.grad_orig = st.orig;
+      d.X = st.xcur;
+      for (int j = 0; j < K; ++j) d.hist[j] = st.h[j];
+      PTK_TRY(run_direct_steps(c, a, d, part, s));
+      aged(part);
+      if (K) st.hl = hl = d.hl;
+    }
     if (final_X) {
       PTK_TRY(adv_store(c, final_X, final_hist, s));
       st.valid = false;
@@ -1427,6 +1477,7 @@ int adv_steps(ptk_ctx* c, int scheme, double dt, int nsteps, void* grad_out, hip
   }
   for (int step = 0; step < nsteps; ++step) {
     const bool last = step == nsteps - 1;
+    if (due()) PTK_TRY(sort_state(true));
     void* k1 = st.k1;
     // u(X_n), and its gradient, at the bin-ordered positions
     {
@@ -1470,8 +1521,8 @@ int adv_steps(ptk_ctx* c, int scheme, double dt, int nsteps, void* grad_out, hip
       PTK_TRY(update(kEulerOrPredict, inert ? vel(st.p, nullptr) : vel(k1, nullptr)));
       if (pst) PTK_TRY(orient(kEulerOrPredict, vel(st.r1, nullptr), st.pn, unit));
     } else if (scheme == PTK_HEUN) {
-      // predictor (into xnext), re-binned for the sweep; u at the predictor is
-      // written back in the step's bin order
+      // predictor (into xnext), re-binned; u at the predictor is written
+      // back in the step's bin order
       PTK_TRY(update(kEulerOrPredict, inert ? vel(st.p, nullptr) : vel(k1, nullptr)));
       if (pst) PTK_TRY(orient(kEulerOrPredict, vel(st.r1, nullptr), st.ps, 0));
       uint32_t* pp = direct ? nullptr : (uint32_t*)c->aperm_p.ptr;
@@ -1557,8 +1608,9 @@ int adv_steps(ptk_ctx* c, int scheme, double dt, int nsteps, void* grad_out, hip
       st.valid = false;
       break;
     }
-    if (!binned) {
+    if (direct) {
       // nothing moves: the new positions are in the same order in xnext
+      aged(1);
       st.xrow = nullptr;
       std::swap(st.xcur, st.xnext);
       if (pst) std::swap(st.p, st.pn);
@@ -1602,7 +1654,7 @@ int ptk_advance_particles(ptk_ctx* c, double* X, int64_t Np, void* rhs_hist, int
   hipStream_t s = S(stream);
   // the one-shot form runs on the buffers of the loaded state
   c->adv.valid = false;
-  if (route_of(c, Np, false) == Route::kDirect) {
+  if (step_route(c, Np, false, scheme, nsteps, true) == Route::kDirect) {
     // on the caller's arrays, in their order
     InterpArgs a = base_args(c);
     a.np = Np;
@@ -1617,7 +1669,7 @@ int ptk_advance_particles(ptk_ctx* c, double* X, int64_t Np, void* rhs_hist, int
     if (K) *hist_len = d.hl;
     return PTK_OK;
   }
-  PTK_TRY(adv_load(c, X, Np, rhs_hist, K ? *hist_len : 0, K, s));
+  PTK_TRY(adv_load(c, X, Np, rhs_hist, K ? *hist_len : 0, K, true, s));
   const int r = adv_steps(c, scheme, dt, nsteps, grad_out, s, X, rhs_hist);
   if (K && r == PTK_OK) *hist_len = c->adv.hl;
   c->adv.valid = false;
@@ -1638,7 +1690,7 @@ int ptk_particles_load(ptk_ctx* c, const double* X, int64_t Np, const void* rhs_
   DeviceGuard g(c->device);
   if (g.err != hipSuccess) return hip_fail(c, g.err, "hipSetDevice");
   hipStream_t s = S(stream);
-  PTK_TRY(adv_load(c, X, Np, rhs_hist, hist_len, hist_depth, s));
+  PTK_TRY(adv_load(c, X, Np, rhs_hist, hist_len, hist_depth, load_binned(c, Np, hist_depth), s));
   const int r = check_flag(c, s);
   if (r != PTK_OK) c->adv.valid = false;
   return r;
@@ -1940,7 +1992,7 @@ int ptk_particles_restore(ptk_ctx* c, const char* path, void* stream) {
   PTK_HIP(c, hipHostMalloc(&h.p, kIoChunk, hipHostMallocDefault), "pinned host buffer");
   PTK_TRY(read_device(c, fc.f, src, total, h, s));
   c->adv.valid = false;
-  PTK_TRY(adv_load(c, (const double*)src, Np, src + x3, hl, hd.depth, s));
+  PTK_TRY(adv_load(c, (const double*)src, Np, src + x3, hl, hd.depth, load_binned(c, Np, hd.depth), s));
   PTK_TRY(check_flag(c, s));
   if (axes)
     PTK_TRY(ptk_particles_set_orientation(c, (const double*)(src + x3 + (size_t)hl * v3),

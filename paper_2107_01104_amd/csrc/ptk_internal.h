@@ -129,6 +129,7 @@ struct ptk_ctx {
     // the particles are in bin order, with skeys and aoff their sorted keys
     // and offsets (not while they are stepped without bins)
     bool binned = false;
+    int age = 0;  // steps since the particles were put into bin order (not counted on from kSortSteps, api.hip)
     int64_t Np = 0, N = 0;
     int vb = 0;   // bytes per velocity component of the history
     int K = 0;    // history depth (Adams-Bashforth order) it was loaded for

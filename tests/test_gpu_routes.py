@@ -121,11 +121,11 @@ def test_direct_steps_at_the_edges_of_a_block(ptk, monkeypatch, n):
 @pytest.mark.parametrize("kind,one_shot", [("tracers", False), ("tracers", True), ("axes", False), ("inertia", False)])
 @pytest.mark.parametrize("scheme", ["EULER", "HEUN", "AB3"])
 def test_steps_in_bin_order_keep_it(ptk, monkeypatch, kind, scheme, one_shot):
-    """Steps evaluated in bin order re-bin after each of them (but a one-shot
-    call's last), with the sweep's results bit for bit; a state that was not
-    sorted when it was loaded is sorted first."""
+    """Steps evaluated in bin order sort the state again after every eight, with
+    the sweep's results bit for bit (which re-bins after each, but for a
+    one-shot call's last)."""
     print(f"[routes] bin order kept: {kind} {scheme} one_shot={one_shot}", flush=True)
-    N, n, steps = 24, 9001, 7
+    N, n, steps = 24, 9001, 27
     g = torch.Generator(device=DEV).manual_seed(3)
     u = torch.randn((N, N, N, 3), generator=g, device=DEV)
     X0 = (torch.rand((n, 3), generator=g, device=DEV, dtype=torch.float64) * 3 - 1) * L
@@ -149,8 +149,8 @@ def test_steps_in_bin_order_keep_it(ptk, monkeypatch, kind, scheme, one_shot):
                 ctx.particles_set_orientation(p, 0.7)
             elif kind == "inertia":
                 ctx.particles_set_inertia(p, 0.2)
-            ctx.particles_advance(sch, 2e-2, 2)
-            ctx.particles_advance(sch, 2e-2, steps - 2, grad_out=gr)
+            ctx.particles_advance(sch, 2e-2, 5)
+            ctx.particles_advance(sch, 2e-2, steps - 5, grad_out=gr)
             ctx.particles_store(X, hist=h)
             if kind == "axes":
                 ctx.particles_get_orientation(p, hist=ph)
@@ -161,9 +161,9 @@ def test_steps_in_bin_order_keep_it(ptk, monkeypatch, kind, scheme, one_shot):
         return sorts, [X, p, gr, ph, vh] + ([h] if depth else [])
 
     sorts, a = run("sorted")
-    assert sorts == 1 + steps - (1 if one_shot else 0)
+    assert sorts == 1 + (steps - 1) // 8
     swept, b = run("sweep")
-    assert swept == sorts + (steps if scheme == "HEUN" else 0)  # (the predictor's bins too)
+    assert swept == 1 + steps - (1 if one_shot else 0) + (steps if scheme == "HEUN" else 0)  # (the predictor's bins too)
     for x, y in zip(a, b):
         assert torch.equal(x, y)
     none, d = run("direct")
@@ -370,3 +370,48 @@ def test_captured_binning_query(ptk, monkeypatch, route, N):
         assert np.array_equal(eager.cpu().numpy(), order), rep
         assert torch.equal(off, eoff)
     ctx.close()
+
+
+@pytest.mark.parametrize("kind", ["tracers", "axes", "inertia"])
+@pytest.mark.parametrize("scheme", ["HEUN", "AB3"])
+def test_steps_through_every_route_in_turn(ptk, kind, scheme):
+    """A resident state whose field's kernel and storage change: swept, direct
+    and in bin order by the rule, in runs shorter and longer than a sort lasts,
+    agrees with the rows of a set that is always read directly."""
+    print(f"[routes] in turn: {kind} {scheme}", flush=True)
+    N, n, k = 64, 300_000, 500
+    u = field(N, 8, "f32")
+    g = torch.Generator(device=DEV).manual_seed(5)
+    X0 = (torch.rand((n, 3), generator=g, device=DEV, dtype=torch.float64) * 3 - 1) * L
+    p0 = torch.nn.functional.normalize(torch.randn((n, 3), generator=g, device=DEV, dtype=torch.float64))
+    sch = getattr(ptk, scheme)
+    depth = ptk.AB_ORDER.get(sch, 0)
+
+    def run(X, p):
+        ctx = ptk.Context(0)
+        m = X.shape[0]
+        h = torch.zeros((depth, m, 3), device=DEV) if depth else None
+        ph, vh = (torch.zeros((depth, m, 3), device=DEV, dtype=torch.float64) for _ in range(2))
+        for e, (fam, I, s, storage) in enumerate([(K.SPLINE, 8, 2, ptk.F32), (K.LAGRANGE, 4, 0, ptk.F32),
+                                                  (K.SPLINE, 6, 1, ptk.F32), (K.SPLINE, 8, 2, ptk.BF16),
+                                                  (K.LAGRANGE, 4, 0, ptk.F32), (K.SPLINE, 8, 2, ptk.F32)]):
+            ctx.set_field(u, fam, I, s, storage=storage)
+            if e == 0:
+                ctx.particles_load(X, hist_depth=depth)
+                if kind == "axes":
+                    ctx.particles_set_orientation(p, 0.7)
+                elif kind == "inertia":
+                    ctx.particles_set_inertia(p, 0.2)
+            for c in (3, 7, 12):
+                ctx.particles_advance(sch, 2e-3, c)
+        ctx.particles_store(X, hist=h)
+        if kind == "axes":
+            ctx.particles_get_orientation(p, hist=ph)
+        elif kind == "inertia":
+            ctx.particles_get_inertia(p, v_hist=vh, r_hist=ph)
+        ctx.close()
+        return [X, p] + [t.transpose(0, 1) for t in (ph, vh)] + ([h.transpose(0, 1)] if depth else [])
+
+    a, b = run(X0.clone(), p0.clone()), run(X0[:k].clone(), p0[:k].clone())
+    for x, y in zip(a, b):
+        assert torch.equal(x[:k], y)
