@@ -1087,9 +1087,10 @@ const double kABW[5][4] = {{0, 0, 0, 0},
                            {23.0 / 12.0, -16.0 / 12.0, 5.0 / 12.0, 0},
                            {55.0 / 24.0, -59.0 / 24.0, 37.0 / 24.0, -9.0 / 24.0}};
 
-// Whether a state to be kept for steps to come is sorted when it is loaded.
+// Whether a state to be kept for steps to come is sorted when it is loaded: where
+// the sweep needs its bins (direct steps in bin order sort it when they begin).
 bool load_binned(const ptk_ctx* c, int64_t Np, int depth) {
-  return step_route(c, Np, false, depth ? PTK_AB2 : PTK_HEUN, kSortSteps, false) != Route::kDirect;
+  return step_route(c, Np, false, depth ? PTK_AB2 : PTK_HEUN, kSortSteps, false) == Route::kSweep;
 }
 
 // Sorts the caller's particles into bin order (if binned) and makes them the loaded
